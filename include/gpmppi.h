@@ -268,11 +268,15 @@ gpmppi_status gpmppi_grad_noalloc(gpmppi_ctx *ctx, const float *x0_d, const floa
  * rotate = 1, 4 waves, no output split, one workgroup per compute unit per
  * 80 KB of LDS (at most 2), longest items first. */
 typedef struct {
-    int32_t groups;      /* sample groups of 32 lanes per workgroup: 1 or 2 (2 only where the k operand fits LDS) */
-    int32_t rotate;      /* 1: each workgroup starts its walk over W at a block-dependent row-pair; 0: at pair 0 */
+    int32_t groups;      /* sample groups of 32 lanes per workgroup: 1 or 2 (2 only where the k operand fits LDS).
+                          * FP32 and BF16x3 forms: unsplit workgroups own 16, 32 or, at the largest admissible
+                          * group count only, 64 samples, chosen by K and M; the results do not depend on it */
+    int32_t rotate;      /* 1: each workgroup starts its walk over W at a block-dependent row tile; 0: at the
+                          * first (FP32 and BF16x3 forms: with split = 1 only, the results do not depend on it) */
     int32_t wg_per_cu;   /* batches: persistent workgroups per compute unit, 1 or 2 (LDS permitting) */
     int32_t order;       /* batches: 0 = items longest first, 1 = problem order */
-    int32_t waves;       /* wave64s per rollout workgroup: 4 or 8, or 12 for the wave-specialised
+    int32_t waves;       /* wave64s per rollout workgroup: 4 or 8 (FP32 and BF16x3 forms without split: always
+                          * eight, whichever is given), or 12 for the wave-specialised
                           * rollout of the BF16 forms at M_pad = 1024 (contexts, groups = the largest
                           * that fits: eight waves stream W through the matrix cores while four
                           * generate the next kernel vectors on the VALU and carry the sample state,
@@ -284,7 +288,7 @@ typedef struct {
     double ms;           /* tune: mean rollout time of this shape in ms; ignored by set */
 } gpmppi_tuning;
 
-/* Autotuner: times every admissible shape (groups x rotate x waves x split) with HIP events on `stream`
+/* Autotuner: times the admissible shapes (groups x rotate x waves x split, where they differ) with HIP events on `stream`
  * (1 warm-up + reps rollouts each, reps in [1, 100], into internal scratch
  * costs; x0_d [5] and U_d [T][2] as for gpmppi_rollout), installs the fastest
  * and writes it, with its time, to *chosen (may be NULL).  Synchronises. */

@@ -7,6 +7,8 @@
 // and the packing of W, alpha and the scaled inputs into the FP32 / BF16
 // layouts the rollout streams.  Padding rows/columns (M <= i < Mpad) carry
 // the identity in A and are zeroed when packing.
+#include <cmath>
+
 #include "device_common.hpp"
 #include "kernels.hpp"
 
@@ -191,19 +193,19 @@ hipError_t alpha_for_targets(const GpBuildBuffers &b, int Mpad, const double *y_
 }
 
 __global__ void combine_alpha_kernel(const double *alpha_terr, int n_terr, int Mpad, TerrainWeights w,
-                                     double *out64, float *alpha32) {
+                                     double sf2, float *alpha32, float *alphas) {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= Mpad) return;
     double a = 0.0;
     for (int i = 0; i < n_terr; ++i) a += w.w[i] * alpha_terr[(size_t)i * Mpad + j];
-    if (out64) out64[j] = a;
     alpha32[j] = (float)a;
+    alphas[j] = (float)(a * sf2 * 0x1p-15);
 }
 
-hipError_t combine_alpha(const double *alpha_terr, int n_terr, int Mpad, TerrainWeights w, double *out64,
-                         float *alpha32, hipStream_t st) {
+hipError_t combine_alpha(const double *alpha_terr, int n_terr, int Mpad, TerrainWeights w, double sf2,
+                         float *alpha32, float *alphas, hipStream_t st) {
     hipLaunchKernelGGL(combine_alpha_kernel, dim3((Mpad + 255) / 256), dim3(256), 0, st, alpha_terr, n_terr, Mpad, w,
-                       out64, alpha32);
+                       sf2, alpha32, alphas);
     return hipGetLastError();
 }
 
@@ -289,10 +291,25 @@ hipError_t launch_terrain_means(const float *q, int n, const GpDev &g, const dou
     return hipGetLastError();
 }
 
+// Scale of each row of W for the FP16 splits: with max_j |sf W_ij| in [2^(e-1), 2^e) the
+// row is packed as sf W 2^(14 - e), and wrs = 2^(e - 29) turns its product with the
+// kernel values scaled by 2^15 / sf^2 back into (W k)_i / sf.  One wave per row.
+__global__ void row_scale_kernel(const double *W, int M, int Mpad, double sf, float *wrs) {
+    const int i = blockIdx.x;
+    double m = 0.0;
+    if (i < M)
+        for (int j = threadIdx.x; j <= i; j += 64) m = fmax(m, fabs(W[(size_t)i * Mpad + j]));
+    for (int d = 32; d >= 1; d >>= 1) m = fmax(m, __shfl_xor(m, d, 64));
+    int e = 0;
+    if (m > 0.0) (void)frexp(sf * m, &e);
+    if (threadIdx.x == 0) wrs[i] = ldexpf(1.0f, e - 29);
+}
+
 // Packs the W blocks in the rollout's pair-major order: block index
 // b = 2 (u (u + 1) + it) + side holds rows of tile t = 2u + side and columns of
 // block column it (it <= 2u + 1); entries above the diagonal or beyond M are 0.
-__global__ void pack_w_kernel(const double *W, int M, int Mpad, float4 *w32, uint4 *wbh, uint4 *wbl) {
+__global__ void pack_w_kernel(const double *W, int M, int Mpad, double sf, const float *wrs, float4 *w32, uint4 *wbh,
+                              uint4 *wbl, uint4 *wfh, uint4 *wfl) {
     const int blk = blockIdx.x, lane = threadIdx.x;
     const int side = blk & 1, half_idx = blk >> 1;   // half_idx = u (u + 1) + it
     int u = 0;
@@ -331,10 +348,30 @@ __global__ void pack_w_kernel(const double *W, int M, int Mpad, float4 *w32, uin
         wbh[(size_t)blk * 128 + h * 64 + lane] = H;
         wbl[(size_t)blk * 128 + h * 64 + lane] = Lo;
     }
+    // FP16 hi / lo terms of the scaled row (the row's scale is 2^-15 / wrs)
+    const double scale = sf * 0x1p-15 / (double)wrs[i];
+    for (int h = 0; h < 2; ++h) {
+        uint16_t hi[8], lo[8];
+        for (int e = 0; e < 8; ++e) {
+            const int j = 32 * it + 16 * h + 8 * half + e;
+            const double x = (i < M && j < M && j <= i) ? W[(size_t)i * Mpad + j] * scale : 0.0;
+            const _Float16 xh = (_Float16)(float)x;
+            const _Float16 xl = (_Float16)(float)(x - (double)xh);
+            __builtin_memcpy(&hi[e], &xh, 2);
+            __builtin_memcpy(&lo[e], &xl, 2);
+        }
+        wfh[(size_t)blk * 128 + h * 64 + lane] =
+            make_uint4(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16),
+                       hi[4] | ((uint32_t)hi[5] << 16), hi[6] | ((uint32_t)hi[7] << 16));
+        wfl[(size_t)blk * 128 + h * 64 + lane] =
+            make_uint4(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16),
+                       lo[4] | ((uint32_t)lo[5] << 16), lo[6] | ((uint32_t)lo[7] << 16));
+    }
 }
 
 __global__ void pack_vec_kernel(const double *Z, const double *alpha, int M, int Mpad, double s0, double s1,
-                                double s2, double s3, double c2, float *zs, float *al, float *zs2, float *cz) {
+                                double s2, double s3, double c2, double sf2, float *zs, float *al, float *als,
+                                float *zs2, float *cz) {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= Mpad) return;
     double z[4] = {0.0, 0.0, 0.0, 0.0}, a = 0.0;
@@ -353,6 +390,7 @@ __global__ void pack_vec_kernel(const double *Z, const double *alpha, int M, int
         zz += (double)zf[d] * (double)zf[d];
     }
     al[j] = (float)a;
+    als[j] = (float)(a * sf2 * 0x1p-15);
     cz[j] = (float)(c2 - zz);
 }
 
@@ -383,57 +421,56 @@ __device__ __forceinline__ void split3_bf16(float x, uint16_t &h, uint16_t &m, u
 // up with points 8 (l / 32) + r (r < 8) and 16 + 8 (l / 32) + r - 8: the k operand
 // of the variance products in its lane order without any exchange.
 // zop[(jt * 2 + step) * 64 + lane] = 8 BF16 slots 8 (lane / 32) .. + 7 of row lane % 32.
-__global__ void pack_zop_kernel(const float *zs2, const float *cz, int Mpad, uint4 *zop) {
+// zop16: the same 32 slots as one 16 x 16 x 32 product per 16 points: product p's row 4a + c
+// holds point 8a + 4p + c, so that the accumulators of the two products give lane l the
+// points 8 (l / 16) + r; zop16[(jt * 2 + p) * 64 + lane] = slots 8 (lane / 16) .. + 7 of
+// row lane % 16.
+__global__ void pack_zop_kernel(const float *zs2, const float *cz, int Mpad, uint4 *zop, uint4 *zop16) {
     const int NT = Mpad / 32;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= NT * 128) return;
     const int lane = i & 63, step = (i >> 6) & 1, jt = i >> 7;
-    const int rho = lane & 31, half = lane >> 5;
-    const int a = rho >> 3, bb = (rho >> 2) & 1, c = rho & 3;
-    const int j = 32 * jt + 16 * (a >> 1) + 8 * bb + 4 * (a & 1) + c;
-    uint16_t zh[4], zm[4], zl[4], ch, cm, cl;
-    for (int d = 0; d < 4; ++d) split3_bf16(zs2[4 * j + d], zh[d], zm[d], zl[d]);
-    split3_bf16(cz[j], ch, cm, cl);
-    const uint16_t one = 0x3f80;
-    uint16_t slot[16];
-    if (step == 0) {
+    // slots 0 .. 31 of point j: zh zh zm zh | zm zl (c2 - |zs|^2) h m l, 1 1 1, 0 0
+    auto slots = [&](int j, uint16_t (&slot)[32]) {
+        uint16_t zh[4], zm[4], zl[4], ch, cm, cl;
+        for (int d = 0; d < 4; ++d) split3_bf16(zs2[4 * j + d], zh[d], zm[d], zl[d]);
+        split3_bf16(cz[j], ch, cm, cl);
+        const uint16_t one = 0x3f80;
         for (int d = 0; d < 4; ++d) {
-            slot[d] = zh[d];
-            slot[4 + d] = zh[d];
-            slot[8 + d] = zm[d];
-            slot[12 + d] = zh[d];
+            slot[d] = slot[4 + d] = slot[12 + d] = zh[d];
+            slot[8 + d] = slot[16 + d] = zm[d];
+            slot[20 + d] = zl[d];
         }
-    } else {
-        for (int d = 0; d < 4; ++d) {
-            slot[d] = zm[d];
-            slot[4 + d] = zl[d];
-        }
-        slot[8] = ch;
-        slot[9] = cm;
-        slot[10] = cl;
-        slot[11] = one;
-        slot[12] = one;
-        slot[13] = one;
-        slot[14] = 0;
-        slot[15] = 0;
-    }
-    const uint16_t *sv = slot + 8 * half;
-    uint4 v;
-    v.x = sv[0] | ((uint32_t)sv[1] << 16);
-    v.y = sv[2] | ((uint32_t)sv[3] << 16);
-    v.z = sv[4] | ((uint32_t)sv[5] << 16);
-    v.w = sv[6] | ((uint32_t)sv[7] << 16);
-    zop[i] = v;
+        slot[24] = ch;
+        slot[25] = cm;
+        slot[26] = cl;
+        slot[27] = slot[28] = slot[29] = one;
+        slot[30] = slot[31] = 0;
+    };
+    auto pack = [](const uint16_t *sv) {
+        return make_uint4(sv[0] | ((uint32_t)sv[1] << 16), sv[2] | ((uint32_t)sv[3] << 16),
+                          sv[4] | ((uint32_t)sv[5] << 16), sv[6] | ((uint32_t)sv[7] << 16));
+    };
+    uint16_t slot[32];
+    const int rho = lane & 31, a = rho >> 3, bb = (rho >> 2) & 1, c = rho & 3;
+    slots(32 * jt + 16 * (a >> 1) + 8 * bb + 4 * (a & 1) + c, slot);
+    zop[i] = pack(slot + 16 * step + 8 * (lane >> 5));
+    const int r16 = lane & 15;
+    slots(32 * jt + 8 * (r16 >> 2) + 4 * step + (r16 & 3), slot);
+    zop16[i] = pack(slot + 8 * (lane >> 4));
 }
 
-hipError_t pack_gp_output(const GpBuildBuffers &b, int M, int Mpad, const double scale[4], double c2, uint4 *zop,
-                          float *zs, float *alpha, float *zs2, float *cz, float4 *w32, uint4 *wbh, uint4 *wbl,
+hipError_t pack_gp_output(const GpBuildBuffers &b, int M, int Mpad, const double scale[4], double sf2, const GpPacked &p,
                           hipStream_t st) {
     const int NP = (Mpad / 32 + 1) / 2;
-    hipLaunchKernelGGL(pack_w_kernel, dim3(2 * NP * (NP + 1)), dim3(64), 0, st, b.W, M, Mpad, w32, wbh, wbl);
+    hipLaunchKernelGGL(row_scale_kernel, dim3(Mpad), dim3(64), 0, st, b.W, M, Mpad, std::sqrt(sf2), p.wrs);
+    hipLaunchKernelGGL(pack_w_kernel, dim3(2 * NP * (NP + 1)), dim3(64), 0, st, b.W, M, Mpad, std::sqrt(sf2), p.wrs,
+                       p.w32, p.wbh, p.wbl, p.wfh, p.wfl);
     hipLaunchKernelGGL(pack_vec_kernel, dim3((Mpad + 255) / 256), dim3(256), 0, st, b.Z, b.alpha, M, Mpad,
-                       scale[0], scale[1], scale[2], scale[3], c2, zs, alpha, zs2, cz);
-    hipLaunchKernelGGL(pack_zop_kernel, dim3((Mpad / 32 * 128 + 255) / 256), dim3(256), 0, st, zs2, cz, Mpad, zop);
+                       scale[0], scale[1], scale[2], scale[3], std::log2(sf2), sf2, p.zs, p.alpha, p.alphas, p.zs2,
+                       p.cz);
+    hipLaunchKernelGGL(pack_zop_kernel, dim3((Mpad / 32 * 128 + 255) / 256), dim3(256), 0, st, p.zs2, p.cz, Mpad, p.zop,
+                       p.zop16);
     return hipGetLastError();
 }
 

@@ -35,6 +35,19 @@ struct GpDev {
     int NT;                 // Mpad / 32
 };
 
+// What rollout_core.hpp reads besides:
+//  wfh/wfl packed FP16 hi / lo splits of sf W, every row scaled by a power of two
+//  wrs    [2][Mpad] what undoes a row's scale and the k operand's on the product
+//  alphas [2][Mpad] alpha sf^2 / 2^15, for kernel values scaled by 2^15 / sf^2
+//  zop16  zop as 16x16x32 products
+struct GpCore : GpDev {
+    const uint4 *wfh;
+    const uint4 *wfl;
+    const float *wrs;
+    const float *alphas;
+    const uint4 *zop16;
+};
+
 struct Geometry {
     int path_kind;          // 0 circle, 1 polyline
     float cx, cy, R;
@@ -58,7 +71,7 @@ struct Dyn {
 };
 
 struct RolloutArgs {
-    GpDev gp;
+    GpCore gp;
     Geometry geo;
     CostWeights cw;
     Dyn dyn;
@@ -66,7 +79,9 @@ struct RolloutArgs {
     uint64_t seed;
     const uint32_t *step_counter;   // if non-NULL, seed + *step_counter keys the noise
     int K, T;
-    int rotate;                     // start each block's walk over W at a block-dependent pair
+    int rotate;                     // start each block's walk over W at a block-dependent unit (FP32 and BF16x3
+                                    // forms: output-split launches)
+    int world_lds;                  // 16-sample blocks: the track and obstacles fit LDS beside the plan
     const float *x0;                // [5]
     const float *U;                 // [T][2]
     float *costs;                   // [K]
@@ -96,9 +111,21 @@ struct UpdateArgs {
     uint32_t *flags;
 };
 
-size_t rollout_lds_bytes(int precision, int G, int Mpad);
-// largest sample-group count whose LDS plan fits a compute unit (1 or 2)
+// sample groups of 32 the launch shape of a context may name (1 or 2)
 int rollout_groups(int precision, int Mpad);
+// A rollout workgroup's block: 16 G samples in a layout of rollout_core.hpp (CoreLayout).
+struct CoreShape {
+    int G, layout;
+};
+CoreShape core_shape(int precision, int Mpad, int K, int groups, int cus);
+CoreShape batch_shape(int Mpad, bool big);
+int core_lds(int precision, int Mpad, CoreShape s);   // dynamic LDS of a workgroup
+// The BF16 form's kernels (rollout_bf16.hip): G sample groups of 32 and NW waves per workgroup.
+size_t rollout_bf16_lds(int G, int Mpad);
+hipError_t launch_rollout_bf16(const RolloutArgs &a, int G, int NW, int split, hipStream_t st);
+int rollout_split_capacity_bf16(int Mpad, int NW);
+hipError_t launch_rollout_batch_bf16(const RolloutArgs *probs_d, const int2 *items_d, int n_items, uint32_t *counter,
+                                     int G, int NW, int Mpad_max, int grid, hipStream_t st);
 // G sample groups of 32 per workgroup (<= rollout_groups), NW wave64s per workgroup (4 or 8; 12: the
 // wave-specialised rollout, where rollout_pipe_admissible).
 // split = 1: each sample block's two GP outputs on two workgroups (G = 1 only; a.xrec, a.xep, a.repair
@@ -115,7 +142,7 @@ hipError_t launch_rollout_pipe(const RolloutArgs &a, int precision, int G, hipSt
 constexpr int kXchRecPerBlock = 4 * 4 * 32;   // exchange records per sample block
 constexpr int kXchSpin = 1 << 18;               // default polls of an exchange wait (~0.3 s)
 hipError_t launch_rollout_batch(const RolloutArgs *probs_d, const int2 *items_d, int n_items, uint32_t *counter,
-                                int precision, int G, int NW, int Mpad_max, int grid, hipStream_t st);
+                                int precision, int GS, int lds, int grid, hipStream_t st);
 hipError_t launch_update_batch(const UpdateArgs *probs_d, const int2 *items_d, int n_items, hipStream_t st);
 hipError_t launch_plant_shift_batch(float *x, float *U, const long long *U_off, const int *T, const Dyn *dyn,
                                     float amplitude, const uint32_t *step_counter, float *x_hist, int n,
@@ -160,9 +187,9 @@ struct TerrainWeights {
     double w[8];
 };
 // alpha_bar = sum_i w_i alpha_i (FP64 alpha_terr [n_terr][Mpad] of one output),
-// written to out64 and, in FP32, to alpha32 [Mpad].
-hipError_t combine_alpha(const double *alpha_terr, int n_terr, int Mpad, TerrainWeights w, double *out64,
-                         float *alpha32, hipStream_t st);
+// written in FP32 to alpha32 [Mpad] and, times sf2 / 2^15, to alphas [Mpad].
+hipError_t combine_alpha(const double *alpha_terr, int n_terr, int Mpad, TerrainWeights w, double sf2,
+                         float *alpha32, float *alphas, hipStream_t st);
 hipError_t launch_terrain_means(const float *q, int n, const GpDev &g, const double *alpha_terr, int n_terr,
                                 float *out, hipStream_t st);
 // Differentiation form (the adjoint rollout and its reductions).
@@ -213,8 +240,14 @@ hipError_t launch_grad(const GradArgs &a, const GradLaunch &l, hipStream_t st);
 // Q = A^-1 = W^T W packed dense (FP32 operand order); overwrites b.A.
 hipError_t pack_q(const GpBuildBuffers &b, int M, int Mpad, float4 *q32, hipStream_t st);
 hipError_t alpha_for_targets(const GpBuildBuffers &b, int Mpad, const double *y_d, double *alpha_d, hipStream_t st);
-hipError_t pack_gp_output(const GpBuildBuffers &b, int M, int Mpad, const double scale[4], double c2, uint4 *zop, float *zs,
-                          float *alpha, float *zs2, float *cz, float4 *w32, uint4 *wbh, uint4 *wbl,
+// Device arrays of one output that pack_gp_output fills (see GpDev).
+struct GpPacked {
+    uint4 *zop, *zop16;
+    float *zs, *alpha, *alphas, *zs2, *cz, *wrs;
+    float4 *w32;
+    uint4 *wbh, *wbl, *wfh, *wfl;
+};
+hipError_t pack_gp_output(const GpBuildBuffers &b, int M, int Mpad, const double scale[4], double sf2, const GpPacked &p,
                           hipStream_t st);
 
 }  // namespace gpmppi

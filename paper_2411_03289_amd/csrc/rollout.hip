@@ -1,148 +1,12 @@
 // K-sample x T-step rollout of the GP-augmented chance-constrained MPPI
-// controller on gfx950 (Alg. 1 Step 1 with Eqs. 1-3, 10, 11-16).
-//
-// Work decomposition: one workgroup of NW wave64s (NW = 4 or 8) owns
-// B = 32 G samples (G = 1 or 2 column groups of the 32x32 matrix-core tiles).
-// Every wave keeps the state x (5) and covariance Sigma (15 symmetric entries)
-// of all B samples in registers for the whole horizon, lane l holding sample
-// l % B; the waves split the training points and the blocks of W between them.
-//
-// Per step:
-//  0. noise and sampled control; position, heading and A Sigma A^T, none of
-//     which needs the GP at this step (the GP variance reaches the position
-//     block of Sigma one step later).
-//  Per GP output o (gp_tiles.hpp):
-//  1. kernel vector k_oj = sf^2 exp(-|q - z_j|^2_ell / 2) for every sample and
-//     training point; k goes to LDS in the matrix-core operand layout and the
-//     GP mean k^T alpha is summed in FP32.
-//  2. variance: v = W k with W = L^-1 lower triangular, on the matrix cores:
-//     each wave walks its share of the 32x32 blocks of W, streamed from L2
-//     through a register ring; each W block serves G sample groups.
-//     s2 = sn^2 + max(0, sf^2 - |v|^2).  Odd steps take the outputs and the
-//     blocks in reverse order, so the blocks walked last stay in L2 for the
-//     next step.  While the later waves finish their blocks, the first waves
-//     run the polyline (first output) and obstacle (second output) loops at
-//     x_{k+1}, Sigma_{k+1}.
-//  3. velocities with the GP mean, the GP variance into Sigma, lane/obstacle
-//     tightening and the stage cost.
-#include "gp_tiles.hpp"
-#include "sample_step.hpp"
+// controller on gfx950 (Alg. 1 Step 1 with Eqs. 1-3, 10, 11-16): the kernels around
+// rollout_core (one workgroup per sample block; FP32 and BF16x3 forms), their output
+// split and persistent batch, and the GP prediction.
+#include "rollout_core.hpp"
 
 namespace gpmppi {
 
-// The rollout of sample block blk (samples blk * B .. blk * B + B - 1) of one
-// problem; called by all threads of a workgroup.
-template <int PREC, int G, int NW = kWaves, int WALK = kWalkAny>
-__device__ __forceinline__ void rollout_block(const RolloutArgs &a, int blk, unsigned char *lds, float *pred,
-                                              float *ored, float *vred) {
-    using S = Shapes<PREC, G, NW>;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, w = tid >> 6;
-    const int sl = lane % S::B;                     // sample within the block
-    const int part = (G == 2) ? w : 2 * w + (lane >> 5);
-    const int sg = blk * S::B + sl;
-    const bool valid = sg < a.K;
-    const bool writer = valid && w == 0 && lane < S::B;
-    const int K = a.K;
-    const int Mpad = a.gp.Mpad;
-    const size_t zs_off = G * kgroup_bytes<PREC>(Mpad);
-
-    NoiseParams np = a.noise;
-    {
-        uint64_t seed = a.seed;
-        if (a.step_counter) seed += (uint64_t)(*a.step_counter);
-        np.key0 = (uint32_t)seed;
-        np.key1 = (uint32_t)(seed >> 32);
-    }
-    const Dyn dy = a.dyn;
-    const CostWeights cw = a.cw;
-    const Geometry &geo = a.geo;
-
-    float X = a.x0[0], Y = a.x0[1], th = a.x0[2], v = a.x0[3], w_ = a.x0[4];
-    Cov P{};
-    float S_ = 0.0f, Sc = 0.0f, disc = 1.0f;
-    float dgoal_min = INFINITY;
-
-    if (writer && a.trace.x_d) {
-        a.trace.x_d[0 * K + sg] = X;
-        a.trace.x_d[1 * K + sg] = Y;
-        a.trace.x_d[2 * K + sg] = th;
-        a.trace.x_d[3 * K + sg] = v;
-        a.trace.x_d[4 * K + sg] = w_;
-    }
-    if (writer && a.trace.sxy_d) {
-        a.trace.sxy_d[0 * K + sg] = 0.0f;
-        a.trace.sxy_d[1 * K + sg] = 0.0f;
-        a.trace.sxy_d[2 * K + sg] = 0.0f;
-    }
-
-    if constexpr (mfma_gen<PREC>()) {   // alpha of both outputs, for the whole horizon
-        stage_alpha<NW>(a.gp, lds, zs_off);
-    } else if constexpr (!scalar_inputs<G>()) {   // inputs of output 0 (the first output of step 0)
-        StagedInputs st;
-        stage_load<PREC, NW>(st, a.gp, 0);
-        stage_store<PREC, NW>(st, a.gp, lds, zs_off);
-    }
-    for (int k = 0; k < a.T; ++k) {
-        // even steps: outputs 0 then 1; odd steps: 1 then 0 (and blocks reversed)
-        const bool rev = (k & 1) != 0;
-        const float2 u = sampled_control(np, k, sg, a.U[2 * k], a.U[2 * k + 1]);
-        const float q[4] = {v, w_, u.x, u.y};
-
-        // ---- the parts of the step that do not need the GP at step k: position and heading
-        // (Eqs. 1, 10) and the covariance propagation A Sigma A^T (Eq. 10); the GP variance
-        // enters Sigma_vv and Sigma_ww below, and reaches the position block one step later
-        float sth, cth;
-        sincosf(th, &sth, &cth);
-        const float dt = dy.dt;
-        const StepJac jac = step_jacobian(dy, v, sth, cth);
-        advance_pose(dy, v, w_, sth, cth, X, Y, th);
-        propagate_cov(P, jac);
-
-        // ---- chance-constraint geometry at (x_{k+1}, Sigma_{k+1}) (Eqs. 13-16); with Step 2
-        // tightening the covariance is the nominal sequence's, shared by all samples
-        float sa = P.p00, sb = P.p01, sc = P.p11;
-        if (a.tight_sxy) {
-            sa = a.tight_sxy[3 * (k + 1)];
-            sb = a.tight_sxy[3 * (k + 1) + 1];
-            sc = a.tight_sxy[3 * (k + 1) + 2];
-        }
-        const float hh = 0.5f * (sa - sc);
-        const float lmax = 0.5f * (sa + sc) + sqrtf(hh * hh + sb * sb);
-        // The polyline loop runs during the first output's contraction and the obstacle loop
-        // during the second's, on the first S::lwaves waves, which finish their share of W first
-        // (with one sample group both half-waves hold the same samples and write the same values).
-        const float Xs = X, Ys = Y;
-        float m[2], s2[2];
-#pragma unroll
-        for (int oo = 0; oo < 2; ++oo) {
-            const int o = rev ? 1 - oo : oo;
-            __syncthreads();   // staged inputs visible; previous k-operand readers are done
-            const float qs[4] = {q[0] * a.gp.scale[o][0], q[1] * a.gp.scale[o][1], q[2] * a.gp.scale[o][2],
-                                 q[3] * a.gp.scale[o][3]};
-            m[o] = gp_gen<PREC, G, NW>(a.gp, o, qs, part, sl, lds, pred);
-            s2[o] = gp_walk<PREC, G, NW, WALK>(a.gp, o, oo == 0 ? 1 - o : -1, rev, a.rotate, blk, lds, vred, sl,
-                                               [&](int wv) {
-                                                   world_loop<S::lwaves, S::B>(geo, oo, wv, sl, Xs, Ys, sa, sb, sc,
-                                                                               lmax, ored);
-                                               });
-        }
-
-        advance_velocities(dy, u, m[0], m[1], v, w_);
-        // ---- the GP variance into the covariance (Eq. 10)
-        add_gp_variance(P.p33, dt, s2[0]);
-        add_gp_variance(P.p44, dt, s2[1]);
-
-        const StageIn t = stage_inputs<S::lwaves, S::B>(geo, cw, ored, sl, X, Y, v, lmax, dgoal_min);
-        add_stage_cost(cw, geo, t, s2[0], s2[1], disc, S_, Sc);
-        if (writer) write_trace(a.trace, K, sg, k, X, Y, th, v, w_, P, m[0], m[1], s2[0], s2[1], t, u, true);
-    }
-    if (cw.w_term != 0.0f && !(dgoal_min <= cw.goal_tol)) {
-        const float yk = cw.w_term - Sc;
-        S_ = S_ + yk;
-    }
-    if (writer) a.costs[sg] = S_;
-}
+using namespace core;
 
 // ---- output split
 // The two GP outputs of one sample block can run on two workgroups of a doubled
@@ -174,21 +38,37 @@ __device__ __forceinline__ uint32_t xch_tag(uint32_t epoch, int k) {
     return ((epoch & 0x7FFFFu) << 13) | (uint32_t)(k + 1);   // k + 1 <= 4096 < 2^13
 }
 
-// Role `role` of sample block blk (one sample group, G = 1); see above.
-template <int PREC, int NW, int WALK>
+// LDS of the split kernel: one output's k, its row factors and partial sums.
+struct SplitPlan {
+    int rs, mp, vp, ored, bytes;
+};
+template <int PREC, int NW>
+__host__ __device__ constexpr SplitPlan split_plan(int NT) {
+    SplitPlan p{};
+    p.rs = NT * 2 * kTerms * 1024;
+    p.mp = p.rs + (PREC == GPMPPI_FP32 ? NT * 32 * 4 : 0);
+    p.vp = p.mp + kClasses * 32 * 4;
+    p.ored = p.vp + NT * 32 * 4;
+    p.bytes = p.ored + 2 * NW * 32 * 4;
+    return p;
+}
+
+// Role `role` of sample block blk (32 samples); see above.
+template <int PREC, int NW>
 __device__ __forceinline__ void rollout_block_split(const RolloutArgs &a, int blk, int role, unsigned char *lds,
-                                                    float *pred, float *ored, float *vred, float *xv) {
-    constexpr int G = 1;
-    using S = Shapes<PREC, G, NW>;
-    static_assert(S::B == 32, "exchange records hold one 32-sample group");
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, w = tid >> 6;
-    const int sl = lane % S::B;
-    const int part = 2 * w + (lane >> 5);
-    const int sg = blk * S::B + sl;
-    const int K = a.K;
-    const bool writer = role == 0 && sg < K && w == 0 && lane < S::B;
-    const size_t zs_off = kgroup_bytes<PREC>(a.gp.Mpad);
+                                                    float *xv) {
+    constexpr int G = 2, B = 32;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int sl = lane % B, sg = blk * B + sl;
+    const int K = a.K, NT = a.gp.NT;
+    const GpCore &gp = a.gp;
+    const bool writer = role == 0 && sg < K && w == 0 && lane < B;
+    const SplitPlan pl = split_plan<PREC, NW>(NT);
+    float *rs = reinterpret_cast<float *>(lds + pl.rs) - role * NT * 32;   // rows of this role's output
+    float *mp = reinterpret_cast<float *>(lds + pl.mp);
+    float *vp = reinterpret_cast<float *>(lds + pl.vp);
+    float *ored = reinterpret_cast<float *>(lds + pl.ored);
 
     NoiseParams np = a.noise;
     {
@@ -226,52 +106,61 @@ __device__ __forceinline__ void rollout_block_split(const RolloutArgs &a, int bl
         a.trace.sxy_d[1 * K + sg] = 0.0f;
         a.trace.sxy_d[2 * K + sg] = 0.0f;
     }
-    if constexpr (mfma_gen<PREC>()) {
-        stage_alpha<NW>(a.gp, lds, zs_off);
-    } else {   // the inputs of this role's output, for the whole horizon
-        StagedInputs st;
-        stage_load<PREC, NW>(st, a.gp, role);
-        stage_store<PREC, NW>(st, a.gp, lds, zs_off);
-    }
+    if constexpr (PREC == GPMPPI_FP32)
+        for (int i = tid; i < NT * 32; i += 64 * NW) rs[role * NT * 32 + i] = gp.wrs[role * NT * 32 + i];
+    const WTerms<PREC> wt = wterms<PREC>(gp, lane);
+    const UnitList ul = unit_list<NW>(w, NT, 1, role, a.rotate ? blk : 0);
+    // this role's output at query q: mean (complete after the barrier), then the variance
+    auto mean_of = [&](const float q[4]) {
+        GenIn<PREC> in;
+        if (w < NT) gen_load<PREC>(in, gp, role, w, lane);
+        gen_output<PREC, G, NW>(gp, role, q, w, lane, lds, mp, in,
+                                [&](GenIn<PREC> &t, int jt) { gen_load<PREC>(t, gp, role, jt, lane); });
+        __syncthreads();
+        return gp_mean_of(mp, B, sl);
+    };
+    WFrag<PREC> none[1];   // every block of W streams from L2 each step
+    UnitCursor first;
+    resident_load<PREC, 0>(none, wt, first, ul);
+    auto contract = [&]() {
+        walk_units<PREC, G, 0, true>(wt, none, first, lane, ul, lds, role, NT, rs, vp - role * NT * B);
+    };
 
     StageIn prev{};        // role 0: the previous step's cost inputs, completed by that step's s2 of output 1
     float s20_prev = 0.0f;
     for (int k = 0; k < a.T; ++k) {
-        const bool rev = (k & 1) != 0;
         const uint32_t tag = xch_tag(epoch, k);
         const float2 u = sampled_control(np, k, sg, a.U[2 * k], a.U[2 * k + 1]);
-        const float qs[4] = {v * a.gp.scale[role][0], w_ * a.gp.scale[role][1], u.x * a.gp.scale[role][2],
-                             u.y * a.gp.scale[role][3]};
+        const float q[4] = {v, w_, u.x, u.y};
         float sth, cth;
         sincosf(th, &sth, &cth);
         if (role == 1) {
             advance_pose(dy, v, w_, sth, cth, X, Y, th);
-            const float Xs = X, Ys = Y;
             __syncthreads();   // the previous step's k-operand and loop-result readers are done
-            const float m1 = gp_gen<PREC, G, NW>(a.gp, 1, qs, part, sl, lds, pred);
+            const float m1 = mean_of(q);
             if (w == 0) xch_put(slot(k, 1), lane, m1, tag);
-            const float s21 = gp_walk<PREC, G, NW, WALK>(a.gp, 1, -1, rev, a.rotate, blk, lds, vred, sl, [&](int wv) {
-                world_loop<NW, S::B>(geo, 0, wv, sl, Xs, Ys, 0.0f, 0.0f, 0.0f, 0.0f, ored);
-                if (wv == 0) {
-                    const float m0 = xch_get(slot(k, 0), lane, tag, spin, broken);
-                    if (lane < 32) xv[lane] = m0;
-                    if (lane == 0) xv[kXvFail] = broken ? 1.0f : 0.0f;
-                }
-            });
+            contract();
+            world_share<NW, B>(geo, w, lane, X, Y, 0.0f, 0.0f, 0.0f, 0.0f, ored, true, false);
+            if (w == 0) {
+                const float m0 = xch_get(slot(k, 0), lane, tag, spin, broken);
+                if (lane < 32) xv[lane] = m0;
+                if (lane == 0) xv[kXvFail] = broken ? 1.0f : 0.0f;
+            }
+            __syncthreads();
             if (xv[kXvFail] != 0.0f) {   // the partner did not answer: leave the block to the repair
                 alone = true;
                 break;
             }
             if (w == 0) {
-                xch_put(slot(k, 2), lane, s21, tag);
+                xch_put(slot(k, 2), lane, gp_variance<PREC>(gp, 1, row_classes(vp, NT, B, sl)), tag);
                 if (geo.path_kind != 0) {
                     float best = INFINITY;
 #pragma unroll
-                    for (int p = 0; p < NW; ++p) best = fminf(best, ored[p * S::B + sl]);
+                    for (int p = 0; p < NW; ++p) best = fminf(best, ored[p * B + sl]);
                     xch_put(slot(k, 3), lane, best, tag);
                 }
             }
-            advance_velocities(dy, u, xv[sl], m1, v, w_);
+            step_velocities(dy, u, xv[sl], m1, v, w_);
             continue;
         }
 
@@ -279,7 +168,7 @@ __device__ __forceinline__ void rollout_block_split(const RolloutArgs &a, int bl
         const StepJac jac = step_jacobian(dy, v, sth, cth);
         advance_pose(dy, v, w_, sth, cth, X, Y, th);
         __syncthreads();
-        const float m0 = gp_gen<PREC, G, NW>(a.gp, 0, qs, part, sl, lds, pred);
+        const float m0 = mean_of(q);
         if (w == 0) xch_put(slot(k, 0), lane, m0, tag);
 
         // ---- chance-constraint geometry at (x_{k+1}, Sigma_{k+1}) (Eqs. 13-16): the position
@@ -292,43 +181,46 @@ __device__ __forceinline__ void rollout_block_split(const RolloutArgs &a, int bl
             sb = a.tight_sxy[3 * (k + 1) + 1];
             sc = a.tight_sxy[3 * (k + 1) + 2];
         }
-        const float hh = 0.5f * (sa - sc);
-        const float lmax = 0.5f * (sa + sc) + sqrtf(hh * hh + sb * sb);
-        const float Xs = X, Ys = Y;
-        const float s20 = gp_walk<PREC, G, NW, WALK>(a.gp, 0, -1, rev, a.rotate, blk, lds, vred, sl, [&](int wv) {
-            world_loop<NW, S::B>(geo, 1, wv, sl, Xs, Ys, sa, sb, sc, lmax, ored);
-            if (wv == 0) {
-                const float m1 = xch_get(slot(k, 1), lane, tag, spin, broken);
-                const uint32_t tp = xch_tag(epoch, k - 1);
-                const float s21p = k > 0 ? xch_get(slot(k - 1, 2), lane, tp, spin, broken) : 0.0f;
-                const float bestp =
-                    k > 0 && geo.path_kind != 0 ? xch_get(slot(k - 1, 3), lane, tp, spin, broken) : 0.0f;
-                if (lane < 32) {
-                    xv[lane] = m1;
-                    xv[32 + lane] = s21p;
-                    xv[64 + lane] = bestp;
-                }
-                if (lane == 0) xv[kXvFail] = broken ? 1.0f : 0.0f;
+        const float lmax = lambda_max(sa, sb, sc);
+        contract();
+        world_share<NW, B>(geo, w, lane, X, Y, sa, sb, sc, lmax, ored, false, true);
+        if (w == 0) {
+            const float m1 = xch_get(slot(k, 1), lane, tag, spin, broken);
+            const uint32_t tp = xch_tag(epoch, k - 1);
+            const float s21p = k > 0 ? xch_get(slot(k - 1, 2), lane, tp, spin, broken) : 0.0f;
+            const float bestp = k > 0 && geo.path_kind != 0 ? xch_get(slot(k - 1, 3), lane, tp, spin, broken) : 0.0f;
+            if (lane < 32) {
+                xv[lane] = m1;
+                xv[32 + lane] = s21p;
+                xv[64 + lane] = bestp;
             }
-        });
+            if (lane == 0) xv[kXvFail] = broken ? 1.0f : 0.0f;
+        }
+        __syncthreads();
         if (xv[kXvFail] != 0.0f) {   // the partner did not answer: leave the block to the repair
             alone = true;
             break;
         }
+        const float s20 = gp_variance<PREC>(gp, 0, row_classes(vp, NT, B, sl));
         const float m1 = xv[sl];
         if (k > 0) {   // step k - 1 completed: its second variance into Sigma_ww, its lane distance, its cost
             const float s21p = xv[32 + sl];
             add_gp_variance(P.p44, dt, s21p);
             if (geo.path_kind != 0) prev.dl = sqrtf(xv[64 + sl]);
-            add_stage_cost(cw, geo, prev, s20_prev, s21p, disc, S_, Sc);
-            if (writer) write_deferred_trace(a.trace, K, sg, k - 1, s21p, prev);
+            core_stage_cost(cw, geo, prev, s20_prev, s21p, disc, S_, Sc);
+            if (writer) {
+                write_variances(a.trace, K, sg, k - 1, s20_prev, s21p);
+                write_margins(a.trace, K, sg, k - 1, prev);
+            }
         }
         propagate_cov(P, jac);
-        advance_velocities(dy, u, m0, m1, v, w_);
+        step_velocities(dy, u, m0, m1, v, w_);
         add_gp_variance(P.p33, dt, s20);
-        prev = stage_inputs<NW, S::B, false>(geo, cw, ored, sl, X, Y, v, lmax, dgoal_min);
+        prev = stage_geometry(geo, cw, X, Y, v, lmax, dgoal_min);
+#pragma unroll
+        for (int p = 0; p < NW; ++p) prev.om = fminf(prev.om, ored[(NW + p) * B + sl]);
         s20_prev = s20;
-        if (writer) write_trace(a.trace, K, sg, k, X, Y, th, v, w_, P, m0, m1, s20, 0.0f, prev, u, false, false);
+        if (writer) write_step(a.trace, K, sg, k, X, Y, th, v, w_, P, m0, m1, u);
     }
     if (role == 0 && !alone) {
         const uint32_t tl = xch_tag(epoch, a.T - 1);
@@ -336,8 +228,11 @@ __device__ __forceinline__ void rollout_block_split(const RolloutArgs &a, int bl
         if (geo.path_kind != 0) prev.dl = sqrtf(xch_get(slot(a.T - 1, 3), lane, tl, spin, broken));
         alone = __syncthreads_or(broken) != 0;
         if (!alone) {
-            add_stage_cost(cw, geo, prev, s20_prev, s21p, disc, S_, Sc);
-            if (writer) write_deferred_trace(a.trace, K, sg, a.T - 1, s21p, prev);
+            core_stage_cost(cw, geo, prev, s20_prev, s21p, disc, S_, Sc);
+            if (writer) {
+                write_variances(a.trace, K, sg, a.T - 1, s20_prev, s21p);
+                write_margins(a.trace, K, sg, a.T - 1, prev);
+            }
             if (cw.w_term != 0.0f && !(dgoal_min <= cw.goal_tol)) {
                 const float yk = cw.w_term - Sc;
                 S_ = S_ + yk;
@@ -361,51 +256,43 @@ __device__ __forceinline__ void rollout_block_split(const RolloutArgs &a, int bl
     }
 }
 
-template <int PREC, int NW, int WALK>
+template <int PREC, int NW>
 __global__ __launch_bounds__(64 * NW) void rollout_split_kernel(RolloutArgs a) {
-    using S = Shapes<PREC, 1, NW>;
     extern __shared__ __align__(16) unsigned char lds[];
-    __shared__ float pred[S::rparts * S::B];
-    __shared__ float ored[2 * NW * S::B];   // both loops on every wave (rollout_block_split)
-    __shared__ float vred[NW * S::B];
     __shared__ float xv[kXvFail + 1];
     const int role = __builtin_amdgcn_readfirstlane((int)(blockIdx.x & 1));
-    rollout_block_split<PREC, NW, WALK>(a, blockIdx.x >> 1, role, lds, pred, ored, vred, xv);
+    rollout_block_split<PREC, NW>(a, blockIdx.x >> 1, role, lds, xv);
 }
 
 // a.repair == NULL: every block.  Otherwise the repair launch after an output
-// split (G = 1): only the blocks the split launch marked, whose marks it clears.
-template <int PREC, int G, int NW, int WALK>
-__global__ __launch_bounds__(64 * NW) void rollout_kernel(RolloutArgs a) {
-    using S = Shapes<PREC, G, NW>;
+// split (32-sample blocks): only the blocks the split launch marked, whose marks it clears.
+template <int PREC, int G, int LAYOUT>
+__global__ __launch_bounds__(64 * kCoreWaves) void rollout_kernel(RolloutArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];
-    __shared__ float pred[S::rparts * S::B];
-    __shared__ float ored[2 * S::lwaves * S::B];
-    __shared__ float vred[NW * S::B];
-    if (a.repair && __hip_atomic_load(a.repair + blockIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return;
-    rollout_block<PREC, G, NW, WALK>(a, blockIdx.x, lds, pred, ored, vred);
-    if (a.repair && threadIdx.x == 0)
+    if (G == 2 && a.repair &&
+        __hip_atomic_load(a.repair + blockIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)
+        return;
+    rollout_core<PREC, G, LAYOUT>(a, blockIdx.x, lds);
+    if (G == 2 && a.repair && threadIdx.x == 0)
         __hip_atomic_store(a.repair + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The problems of a batch, read-only for the whole launch: through the constant
 // address space their fields come in by scalar loads the compiler may repeat
 // where they are used, as a kernel argument's do, instead of vector loads kept
-// live in registers across the item (which spilled the eight-wave shapes).
+// live in registers across the item.
 typedef const RolloutArgs __attribute__((address_space(4))) ConstRolloutArgs;
 
 // Persistent rollout of many independent problems: every workgroup takes
 // (problem, sample block) items from a shared counter until the list (sorted
 // longest first) is exhausted.  Results do not depend on which workgroup
-// runs an item.  *counter must be 0 at launch.
-template <int PREC, int G, int NW>
-__global__ __launch_bounds__(64 * NW) void rollout_batch_kernel(ConstRolloutArgs *probs, const int2 *items,
-                                                                 int n_items, uint32_t *counter) {
-    using S = Shapes<PREC, G, NW>;
+// runs an item.  *counter must be 0 at launch.  Problems whose whole layout fits run
+// 32-sample blocks of it; GS > 0: the others run blocks of 16 GS samples of the sweep
+// layout.
+template <int PREC, int GS>
+__global__ __launch_bounds__(64 * kCoreWaves) void rollout_batch_kernel(ConstRolloutArgs *probs, const int2 *items,
+                                                                         int n_items, uint32_t *counter) {
     extern __shared__ __align__(16) unsigned char lds[];
-    __shared__ float pred[S::rparts * S::B];
-    __shared__ float ored[2 * S::lwaves * S::B];
-    __shared__ float vred[NW * S::B];
     __shared__ int next_item;
     for (;;) {
         __syncthreads();   // every thread has read the previous item
@@ -416,7 +303,12 @@ __global__ __launch_bounds__(64 * NW) void rollout_batch_kernel(ConstRolloutArgs
         const int2 pb = items[it];
         const int p = __builtin_amdgcn_readfirstlane(pb.x);
         const int b = __builtin_amdgcn_readfirstlane(pb.y);
-        rollout_block<PREC, G, NW>(*(const RolloutArgs *)&probs[p], b, lds, pred, ored, vred);
+        const RolloutArgs &a = *(const RolloutArgs *)&probs[p];
+        if (a.gp.NT <= kResidentTiles) {
+            rollout_core<PREC, 2, kWholeResident>(a, b, lds);
+        } else {
+            if constexpr (GS > 0) rollout_core<PREC, GS, kSweep>(a, b, lds);
+        }
     }
 }
 
@@ -457,8 +349,9 @@ __global__ __launch_bounds__(kThreads) void gp_predict_kernel(GpDev g, const flo
     }
 }
 
-// Sample groups per block: two when both groups' k operand and the staged
-// inputs fit the 160 KB LDS of a CDNA4 compute unit, else one.
+// Sample groups of 32 the launch shape allows: two when two groups' k operand of one
+// output (and the staged inputs of the prediction kernel) fit the 160 KB LDS of a CDNA4
+// compute unit, else one.
 static int groups_for(int precision, int Mpad) {
     const size_t budget = 160 * 1024 - 8 * 1024;
     size_t need2 = 0;
@@ -470,13 +363,7 @@ static int groups_for(int precision, int Mpad) {
     return need2 <= budget ? 2 : 1;
 }
 
-size_t rollout_lds_bytes(int precision, int G, int Mpad) {
-    switch (precision) {
-        case GPMPPI_FP32: return G == 2 ? dyn_lds_bytes<GPMPPI_FP32, 2>(Mpad) : dyn_lds_bytes<GPMPPI_FP32, 1>(Mpad);
-        case GPMPPI_BF16: return G == 2 ? dyn_lds_bytes<GPMPPI_BF16, 2>(Mpad) : dyn_lds_bytes<GPMPPI_BF16, 1>(Mpad);
-        default: return G == 2 ? dyn_lds_bytes<GPMPPI_BF16X3, 2>(Mpad) : dyn_lds_bytes<GPMPPI_BF16X3, 1>(Mpad);
-    }
-}
+int rollout_groups(int precision, int Mpad) { return groups_for(precision, Mpad); }
 
 template <typename F>
 static hipError_t set_lds(F *fn, size_t bytes) {
@@ -484,115 +371,132 @@ static hipError_t set_lds(F *fn, size_t bytes) {
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-// One problem: the kernel carries only the walk over W that its size takes.
-template <int PREC, int G, int NW, int WALK>
-static hipError_t launch_rollout_w(const RolloutArgs &a, hipStream_t st) {
-    const size_t lds = dyn_lds_bytes<PREC, G>(a.gp.Mpad);
-    hipError_t e = set_lds(rollout_kernel<PREC, G, NW, WALK>, lds);
+// The block of one problem: the smallest that still gives every compute unit at most one
+// workgroup, as the horizon is a serial chain and a block's step gets longer with its
+// samples; 64 samples where the blocks outnumber the compute units anyway.  big: 64-sample
+// blocks are allowed.
+template <int PREC>
+static CoreShape core_shape_t(int NT, int K, bool big, int cus) {
+    const int whole = NT <= kResidentTiles ? kWholeResident : kWholeStream;
+    const bool w1 = core_plan<PREC, 1, false>(NT).bytes <= kCoreLdsMax;
+    const long long n16 = (K + 15) / 16;
+    if (w1 && n16 <= cus) return CoreShape{1, whole};
+    if (whole == kWholeResident) return CoreShape{2, whole};
+    return CoreShape{big && n16 > 2LL * cus ? 4 : 2, kSweep};
+}
+
+CoreShape core_shape(int precision, int Mpad, int K, int groups, int cus) {
+    const bool big = groups == groups_for(precision, Mpad);   // the largest group count: 64-sample blocks allowed
+    return precision == GPMPPI_FP32 ? core_shape_t<GPMPPI_FP32>(Mpad / 32, K, big, cus)
+                                    : core_shape_t<GPMPPI_BF16X3>(Mpad / 32, K, big, cus);
+}
+
+// A batched problem's block (see rollout_batch_kernel); big: the batch's sweep blocks hold
+// 64 samples.
+CoreShape batch_shape(int Mpad, bool big) {
+    if (Mpad / 32 <= kResidentTiles) return CoreShape{2, kWholeResident};
+    return CoreShape{big ? 4 : 2, kSweep};
+}
+
+template <int PREC>
+static int core_lds_t(int NT, CoreShape s) {
+    if (s.layout == kSweep) return s.G == 4 ? core_plan<PREC, 4, true>(NT).bytes : core_plan<PREC, 2, true>(NT).bytes;
+    return s.G == 1 ? core_plan<PREC, 1, false>(NT).bytes : core_plan<PREC, 2, false>(NT).bytes;
+}
+
+int core_lds(int precision, int Mpad, CoreShape s) {
+    return precision == GPMPPI_FP32 ? core_lds_t<GPMPPI_FP32>(Mpad / 32, s) : core_lds_t<GPMPPI_BF16X3>(Mpad / 32, s);
+}
+
+template <int PREC, int G, int LAYOUT>
+static hipError_t launch_core(const RolloutArgs &args, hipStream_t st) {
+    RolloutArgs a = args;
+    int lds = core_lds_t<PREC>(a.gp.NT, CoreShape{G, LAYOUT});
+    const long long world = 20LL * a.geo.P + 16LL * a.geo.n_obs;
+    a.world_lds = G == 1 && LAYOUT != kSweep && lds + world <= kCoreLdsMax;
+    if (a.world_lds) lds += (int)world;
+    if (lds > kCoreLdsMax) return hipErrorInvalidValue;
+    hipError_t e = set_lds(rollout_kernel<PREC, G, LAYOUT>, lds);
     if (e != hipSuccess) return e;
-    const dim3 grid((a.K + 32 * G - 1) / (32 * G));
-    hipLaunchKernelGGL((rollout_kernel<PREC, G, NW, WALK>), grid, dim3(64 * NW), lds, st, a);
+    const dim3 grid((a.K + 16 * G - 1) / (16 * G));
+    hipLaunchKernelGGL((rollout_kernel<PREC, G, LAYOUT>), grid, dim3(64 * kCoreWaves), lds, st, a);
     return hipGetLastError();
 }
 
-template <int PREC, int G, int NW>
-static hipError_t launch_rollout_t(const RolloutArgs &a, hipStream_t st) {
-    return walk_by_rows(a.gp.NT, NW) ? launch_rollout_w<PREC, G, NW, kWalkRows>(a, st)
-                                     : launch_rollout_w<PREC, G, NW, kWalkPairs>(a, st);
+template <int PREC>
+static hipError_t launch_core_p(const RolloutArgs &a, CoreShape s, hipStream_t st) {
+    if (s.layout == kSweep) return s.G == 4 ? launch_core<PREC, 4, kSweep>(a, st) : launch_core<PREC, 2, kSweep>(a, st);
+    if (s.layout == kWholeStream) return launch_core<PREC, 1, kWholeStream>(a, st);
+    return s.G == 1 ? launch_core<PREC, 1, kWholeResident>(a, st) : launch_core<PREC, 2, kWholeResident>(a, st);
 }
 
-// Workgroups of fn (64 NW threads, lds bytes of dynamic LDS) resident at once on the device.
-template <typename F>
-static hipError_t resident_blocks(F *fn, int NW, size_t lds, int &n) {
-    int dev = 0, ncu = 0, per_cu = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e == hipSuccess)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(fn), 64 * NW, lds);
-    n = e == hipSuccess ? per_cu * ncu : 0;
-    return e;
+static int device_cus() {
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
+        return 1;
+    return ncu;
 }
 
-template <int PREC, int NW, int WALK>
-static hipError_t split_capacity_w(int Mpad, int &n) {
-    const size_t lds = dyn_lds_bytes<PREC, 1>(Mpad);
-    hipError_t e = set_lds(rollout_split_kernel<PREC, NW, WALK>, lds);
-    if (e != hipSuccess) return e;
-    return resident_blocks(rollout_split_kernel<PREC, NW, WALK>, NW, lds, n);
-}
-
+// Largest sample count whose split launch at this shape can be resident at once.
 template <int PREC, int NW>
 static int split_capacity_t(int Mpad) {
-    int n = 0;
-    const hipError_t e = walk_by_rows(Mpad / 32, NW) ? split_capacity_w<PREC, NW, kWalkRows>(Mpad, n)
-                                                    : split_capacity_w<PREC, NW, kWalkPairs>(Mpad, n);
-    return e == hipSuccess ? 32 * (n / 2) : 0;
-}
-
-template <int PREC, int NW, int WALK>
-static hipError_t launch_rollout_split_w(const RolloutArgs &a, hipStream_t st) {
-    if (!a.xrec || !a.xep || !a.repair) return hipErrorInvalidValue;
-    const size_t lds = dyn_lds_bytes<PREC, 1>(a.gp.Mpad);
-    int cap = 0;
-    hipError_t e = split_capacity_w<PREC, NW, WALK>(a.gp.Mpad, cap);
-    if (e != hipSuccess) return e;
-    const int nblk = (a.K + 31) / 32;
-    if (2 * nblk > cap) return hipErrorCooperativeLaunchTooLarge;   // both roles of every block resident together
-    hipLaunchKernelGGL((rollout_split_kernel<PREC, NW, WALK>), dim3(2 * nblk), dim3(64 * NW), lds, st, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    // the repair launch: the unsplit kernel recomputes the blocks whose exchange gave up
-    return launch_rollout_w<PREC, 1, NW, WALK>(a, st);
+    const int lds = split_plan<PREC, NW>(Mpad / 32).bytes;
+    int per_cu = 0;
+    if (lds > kCoreLdsMax - 1024 || set_lds(rollout_split_kernel<PREC, NW>, lds) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu,
+                                                     reinterpret_cast<const void *>(rollout_split_kernel<PREC, NW>),
+                                                     64 * NW, lds) != hipSuccess)
+        return 0;
+    return 32 * (per_cu * device_cus() / 2);
 }
 
 template <int PREC, int NW>
 static hipError_t launch_rollout_split_t(const RolloutArgs &a, hipStream_t st) {
-    return walk_by_rows(a.gp.NT, NW) ? launch_rollout_split_w<PREC, NW, kWalkRows>(a, st)
-                                     : launch_rollout_split_w<PREC, NW, kWalkPairs>(a, st);
+    if (!a.xrec || !a.xep || !a.repair) return hipErrorInvalidValue;
+    if (a.K > split_capacity_t<PREC, NW>(a.gp.Mpad))
+        return hipErrorCooperativeLaunchTooLarge;   // both roles of every block resident together
+    const int nblk = (a.K + 31) / 32;
+    const SplitPlan plan = split_plan<PREC, NW>(a.gp.NT);
+    hipLaunchKernelGGL((rollout_split_kernel<PREC, NW>), dim3(2 * nblk), dim3(64 * NW), plan.bytes, st, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    // the repair launch: the unsplit kernel recomputes the blocks whose exchange gave up
+    return launch_core_p<PREC>(a, CoreShape{2, a.gp.NT <= kResidentTiles ? kWholeResident : kSweep}, st);
 }
 
 template <int PREC>
-static hipError_t launch_rollout_p(const RolloutArgs &a, int G, int NW, int split, hipStream_t st) {
+static hipError_t launch_rollout_p(const RolloutArgs &a, int groups, int NW, int split, hipStream_t st) {
     if (split) return NW == 8 ? launch_rollout_split_t<PREC, 8>(a, st) : launch_rollout_split_t<PREC, kWaves>(a, st);
-    if (NW == 8) return G == 2 ? launch_rollout_t<PREC, 2, 8>(a, st) : launch_rollout_t<PREC, 1, 8>(a, st);
-    return G == 2 ? launch_rollout_t<PREC, 2, kWaves>(a, st) : launch_rollout_t<PREC, 1, kWaves>(a, st);
+    RolloutArgs b = a;
+    b.repair = nullptr;   // an unsplit launch computes every block
+    return launch_core_p<PREC>(b, core_shape(PREC, a.gp.Mpad, a.K, groups, device_cus()), st);
 }
 
-template <int PREC, int G, int NW>
+template <int PREC, int GS>
 static hipError_t launch_rollout_batch_t(const RolloutArgs *probs, const int2 *items, int n_items, uint32_t *counter,
-                                         int Mpad_max, int grid, hipStream_t st) {
-    const size_t lds = dyn_lds_bytes<PREC, G>(Mpad_max);
-    hipError_t e = set_lds(rollout_batch_kernel<PREC, G, NW>, lds);
+                                         int lds, int grid, hipStream_t st) {
+    hipError_t e = set_lds(rollout_batch_kernel<PREC, GS>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((rollout_batch_kernel<PREC, G, NW>), dim3(grid), dim3(64 * NW), lds, st,
+    hipLaunchKernelGGL((rollout_batch_kernel<PREC, GS>), dim3(grid), dim3(64 * kCoreWaves), lds, st,
                        (ConstRolloutArgs *)probs, items, n_items, counter);
     return hipGetLastError();
 }
 
 template <int PREC>
 static hipError_t launch_rollout_batch_p(const RolloutArgs *probs, const int2 *items, int n_items, uint32_t *counter,
-                                         int G, int NW, int Mpad_max, int grid, hipStream_t st) {
-    if (NW == 8)
-        return G == 2 ? launch_rollout_batch_t<PREC, 2, 8>(probs, items, n_items, counter, Mpad_max, grid, st)
-                      : launch_rollout_batch_t<PREC, 1, 8>(probs, items, n_items, counter, Mpad_max, grid, st);
-    return G == 2 ? launch_rollout_batch_t<PREC, 2, kWaves>(probs, items, n_items, counter, Mpad_max, grid, st)
-                  : launch_rollout_batch_t<PREC, 1, kWaves>(probs, items, n_items, counter, Mpad_max, grid, st);
+                                         int GS, int lds, int grid, hipStream_t st) {
+    if (GS == 4) return launch_rollout_batch_t<PREC, 4>(probs, items, n_items, counter, lds, grid, st);
+    if (GS == 2) return launch_rollout_batch_t<PREC, 2>(probs, items, n_items, counter, lds, grid, st);
+    return launch_rollout_batch_t<PREC, 0>(probs, items, n_items, counter, lds, grid, st);
 }
 
-int rollout_groups(int precision, int Mpad) { return groups_for(precision, Mpad); }
-
 hipError_t launch_rollout_batch(const RolloutArgs *probs_d, const int2 *items_d, int n_items, uint32_t *counter,
-                                int precision, int G, int NW, int Mpad_max, int grid, hipStream_t st) {
-    if (G < 1 || G > groups_for(precision, Mpad_max) || grid < 1 || (NW != kWaves && NW != 8))
-        return hipErrorInvalidValue;
-    switch (precision) {
-        case GPMPPI_FP32:
-            return launch_rollout_batch_p<GPMPPI_FP32>(probs_d, items_d, n_items, counter, G, NW, Mpad_max, grid, st);
-        case GPMPPI_BF16:
-            return launch_rollout_batch_p<GPMPPI_BF16>(probs_d, items_d, n_items, counter, G, NW, Mpad_max, grid, st);
-        default:
-            return launch_rollout_batch_p<GPMPPI_BF16X3>(probs_d, items_d, n_items, counter, G, NW, Mpad_max, grid,
-                                                         st);
-    }
+                                int precision, int GS, int lds, int grid, hipStream_t st) {
+    if ((GS != 0 && GS != 2 && GS != 4) || grid < 1 || lds > kBatchLdsMax) return hipErrorInvalidValue;
+    if (precision == GPMPPI_FP32)
+        return launch_rollout_batch_p<GPMPPI_FP32>(probs_d, items_d, n_items, counter, GS, lds, grid, st);
+    return launch_rollout_batch_p<GPMPPI_BF16X3>(probs_d, items_d, n_items, counter, GS, lds, grid, st);
 }
 
 hipError_t launch_rollout(const RolloutArgs &args, int precision, int G, int NW, int split, hipStream_t st) {
@@ -605,12 +509,10 @@ hipError_t launch_rollout(const RolloutArgs &args, int precision, int G, int NW,
     if (G < 1 || G > groups_for(precision, args.gp.Mpad) || (NW != kWaves && NW != 8) || (split != 0 && split != 1) ||
         (split && G != 1))
         return hipErrorInvalidValue;
-    RolloutArgs a = args;
-    if (!split) a.repair = nullptr;   // an unsplit launch computes every block
     switch (precision) {
-        case GPMPPI_FP32: return launch_rollout_p<GPMPPI_FP32>(a, G, NW, split, st);
-        case GPMPPI_BF16: return launch_rollout_p<GPMPPI_BF16>(a, G, NW, split, st);
-        default: return launch_rollout_p<GPMPPI_BF16X3>(a, G, NW, split, st);
+        case GPMPPI_FP32: return launch_rollout_p<GPMPPI_FP32>(args, G, NW, split, st);
+        case GPMPPI_BF16: return launch_rollout_bf16(args, G, NW, split, st);
+        default: return launch_rollout_p<GPMPPI_BF16X3>(args, G, NW, split, st);
     }
 }
 
@@ -618,7 +520,7 @@ int rollout_split_capacity(int precision, int Mpad, int NW) {
     if (NW != kWaves && NW != 8) return 0;
     switch (precision) {
         case GPMPPI_FP32: return NW == 8 ? split_capacity_t<GPMPPI_FP32, 8>(Mpad) : split_capacity_t<GPMPPI_FP32, kWaves>(Mpad);
-        case GPMPPI_BF16: return NW == 8 ? split_capacity_t<GPMPPI_BF16, 8>(Mpad) : split_capacity_t<GPMPPI_BF16, kWaves>(Mpad);
+        case GPMPPI_BF16: return rollout_split_capacity_bf16(Mpad, NW);
         default: return NW == 8 ? split_capacity_t<GPMPPI_BF16X3, 8>(Mpad) : split_capacity_t<GPMPPI_BF16X3, kWaves>(Mpad);
     }
 }

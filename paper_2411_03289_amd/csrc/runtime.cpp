@@ -119,6 +119,7 @@ namespace gpmppi {
 gpmppi_status set_error(gpmppi_status st, const char *msg) { return fail(st, "%s", msg); }
 }  // namespace gpmppi
 
+constexpr int kSweepLayout = 2;   // CoreShape::layout of blocks in the sweep layout
 constexpr int kGradMaxMpad = 512;   // the adjoint's LDS plan holds k and r for 32 samples
 
 // Scratch memory of the allocation-free entry point (gpmppi_grad_noalloc): one
@@ -171,7 +172,9 @@ struct gpmppi_ctx {
     int xspin = kXchSpin;                 // polls per output-split exchange wait
     float4 *w32 = nullptr;
     uint4 *wbh = nullptr, *wbl = nullptr;
-    uint4 *zop = nullptr;            // BF16 exponent-product operands per output
+    uint4 *wfh = nullptr, *wfl = nullptr;      // FP16 splits of the scaled W
+    float *wrs = nullptr, *alphas = nullptr;   // their row factors; scaled alpha
+    uint4 *zop = nullptr, *zop16 = nullptr;    // BF16 exponent-product operands per output
     long long w32_stride = 0, wb_stride = 0, zop_stride = 0;
     float4 *q32 = nullptr;           // dense packed Q = A^-1 per output (differentiation form, Mpad <= 512)
     long long q_stride = 0;          // float4 per output
@@ -193,7 +196,7 @@ struct gpmppi_ctx {
     float *cost_scratch = nullptr;   // [K]
     float *tight = nullptr;          // [T+1][3] nominal Sigma_XY (Step 2 tightening)
     // host copies
-    GpDev gp{};
+    GpCore gp{};
     Geometry geo{};
     CostWeights cw{};
     Dyn dyn{};
@@ -314,12 +317,12 @@ gpmppi_status build_gps(gpmppi_ctx *c, const gpmppi_gp gp[2]) {
         uint32_t notpd = 0;
         HIP_TRY(hipMemcpy(&notpd, c->flags + 1, sizeof notpd, hipMemcpyDeviceToHost));
         if (notpd) return fail(GPMPPI_E_NOT_PD, "GP %d: K(Z,Z) + sn^2 I is not positive definite", o);
-        const double c2 = 2.0 * gp[o].log_sf / std::log(2.0);
-        HIP_TRY(pack_gp_output(b, M, Mpad, scale, c2, c->zop + o * c->zop_stride, c->zs + (size_t)o * Mpad * 4,
-                               c->alpha + (size_t)o * Mpad,
-                               c->zs2 + (size_t)o * Mpad * 4, c->cz + (size_t)o * Mpad,
-                               c->w32 + o * c->w32_stride, c->wbh + o * c->wb_stride, c->wbl + o * c->wb_stride,
-                               nullptr));
+        const size_t mo = (size_t)o * Mpad;
+        const GpPacked packed{c->zop + o * c->zop_stride, c->zop16 + o * c->zop_stride, c->zs + 4 * mo, c->alpha + mo,
+                              c->alphas + mo, c->zs2 + 4 * mo, c->cz + mo, c->wrs + mo, c->w32 + o * c->w32_stride,
+                              c->wbh + o * c->wb_stride, c->wbl + o * c->wb_stride, c->wfh + o * c->wb_stride,
+                              c->wfl + o * c->wb_stride};
+        HIP_TRY(pack_gp_output(b, M, Mpad, scale, sf2, packed, nullptr));
         if (c->q32) HIP_TRY(pack_q(b, M, Mpad, c->q32 + (size_t)o * c->q_stride, nullptr));
         HIP_TRY(hipDeviceSynchronize());
         for (int d = 0; d < 4; ++d) c->gp.scale[o][d] = (float)scale[d];
@@ -447,8 +450,13 @@ gpmppi_status gpmppi_init(const gpmppi_params *params, const gpmppi_gp gp[2], co
     c->w32 = track(dev_alloc<float4>((size_t)2 * c->w32_stride, st));
     c->wbh = track(dev_alloc<uint4>((size_t)2 * c->wb_stride, st));
     c->wbl = track(dev_alloc<uint4>((size_t)2 * c->wb_stride, st));
+    c->wfh = track(dev_alloc<uint4>((size_t)2 * c->wb_stride, st));
+    c->wfl = track(dev_alloc<uint4>((size_t)2 * c->wb_stride, st));
+    c->wrs = track(dev_alloc<float>((size_t)2 * Mpad, st));
+    c->alphas = track(dev_alloc<float>((size_t)2 * Mpad, st));
     c->zop_stride = (long long)(Mpad / 32) * 128;
     c->zop = track(dev_alloc<uint4>((size_t)2 * c->zop_stride, st));
+    c->zop16 = track(dev_alloc<uint4>((size_t)2 * c->zop_stride, st));
     if (Mpad <= kGradMaxMpad) {
         c->q_stride = (long long)(Mpad / 32) * (Mpad / 32) * 256;
         c->q32 = track(dev_alloc<float4>((size_t)2 * c->q_stride, st));
@@ -511,6 +519,11 @@ gpmppi_status gpmppi_init(const gpmppi_params *params, const gpmppi_gp gp[2], co
     c->gp.w32 = c->w32;
     c->gp.wbh = c->wbh;
     c->gp.wbl = c->wbl;
+    c->gp.wfh = c->wfh;
+    c->gp.wfl = c->wfl;
+    c->gp.wrs = c->wrs;
+    c->gp.alphas = c->alphas;
+    c->gp.zop16 = c->zop16;
     c->gp.w32_stride = c->w32_stride;
     c->gp.wb_stride = c->wb_stride;
     c->gp.zop = c->zop;
@@ -617,8 +630,9 @@ gpmppi_status gpmppi_set_terrain_weights(gpmppi_ctx *c, const double *w) {
     }
     const int Mpad = c->Mpad;
     for (int o = 0; o < 2; ++o) {
-        HIP_TRY(combine_alpha(c->alpha_terr + (size_t)o * c->n_terr * Mpad, c->n_terr, Mpad, tw, nullptr,
-                              c->alpha + (size_t)o * Mpad, nullptr));
+        HIP_TRY(combine_alpha(c->alpha_terr + (size_t)o * c->n_terr * Mpad, c->n_terr, Mpad, tw,
+                              std::exp(2.0 * c->log_sf[o]), c->alpha + (size_t)o * Mpad,
+                              c->alphas + (size_t)o * Mpad, nullptr));
         c->gp.vscale[o] = (float)s2;
     }
     HIP_TRY(hipDeviceSynchronize());
@@ -757,6 +771,7 @@ gpmppi_status gpmppi_info(const gpmppi_ctx *c, int32_t *M_pad, double *z_p, doub
 
 struct gpmppi_batch {
     int n = 0, precision = 0, Mpad_max = 0, grid = 0, cus = 1;
+    int GS = 0, lds = 0;                   // sweep block groups of the installed shape (0: none), rollout LDS
     int G = 1, G_max = 1, rotate = 1, wg_per_cu = 1, wg_per_cu_max = 1, order = 0, waves = 4;
     std::vector<gpmppi_ctx *> ctx;
     std::vector<long long> U_off, K_off;   // n + 1 each
@@ -782,18 +797,33 @@ struct gpmppi_batch {
 
 namespace {
 
+// The rollout launch of the installed shape; the work counter must be 0.
+hipError_t batch_rollout(gpmppi_batch *b, hipStream_t st) {
+    if (b->precision == GPMPPI_BF16)
+        return launch_rollout_batch_bf16(b->ra, b->items, b->n_items, b->counters, b->G, b->waves, b->Mpad_max,
+                                         b->grid, st);
+    return launch_rollout_batch(b->ra, b->items, b->n_items, b->counters, b->precision, b->GS, b->lds, b->grid, st);
+}
+
 gpmppi_status batch_enqueue_step(gpmppi_batch *b, hipStream_t st) {
     HIP_TRY(launch_counter_reset(b->counters, st));
-    HIP_TRY(launch_rollout_batch(b->ra, b->items, b->n_items, b->counters, b->precision, b->G, b->waves,
-                                 b->Mpad_max, b->grid, st));
+    HIP_TRY(batch_rollout(b, st));
     HIP_TRY(launch_update_batch(b->ua, b->upd_items, b->n_upd, st));
     return GPMPPI_OK;
 }
 
-// Most persistent workgroups one compute unit holds at this LDS plan (at most 2).
-int wg_capacity(int precision, int G, int Mpad) {
-    const size_t lds = rollout_lds_bytes(precision, G, Mpad);
-    return std::max(1, std::min(2, (int)((160 * 1024) / (lds + 4096))));
+// Most persistent workgroups one compute unit holds at the LDS plan of the batch's largest
+// block (at most 2).
+int batch_lds(const gpmppi_batch *b, int groups) {
+    int lds = 0;
+    for (const gpmppi_ctx *c : b->ctx)
+        lds = std::max(lds, core_lds(b->precision, c->Mpad, batch_shape(c->Mpad, groups == b->G_max)));
+    return lds;
+}
+int wg_capacity(const gpmppi_batch *b, int groups) {
+    if (b->precision == GPMPPI_BF16)
+        return std::max(1, std::min(2, (int)((160 * 1024) / (rollout_bf16_lds(groups, b->Mpad_max) + 4096))));
+    return std::max(1, std::min(2, (160 * 1024) / (batch_lds(b, groups) + 64)));
 }
 
 // Both workgroups of every sample block fit the device at once (output split, one group).
@@ -824,11 +854,15 @@ gpmppi_status check_tuning(const gpmppi_tuning *t, int G_max, int wg_max, bool b
 
 // Rebuilds the item list and launch grid of a batch for a validated shape.
 gpmppi_status batch_install(gpmppi_batch *b, const gpmppi_tuning &t) {
-    const int B = 32 * t.groups;
     std::vector<std::pair<double, int2>> it;
+    int GS = 0;
     for (int p = 0; p < b->n; ++p) {
         const int K = b->ctx[p]->params.K;
-        for (int blk = 0; blk < (K + B - 1) / B; ++blk) it.push_back({b->cost[p], make_int2(p, blk)});
+        const CoreShape s = b->precision == GPMPPI_BF16 ? CoreShape{2 * t.groups, 0}
+                                                        : batch_shape(b->ctx[p]->Mpad, t.groups == b->G_max);
+        if (s.layout == kSweepLayout) GS = s.G;
+        const int B = 16 * s.G;
+        for (int blk = 0; blk < (K + B - 1) / B; ++blk) it.push_back({b->cost[p] * s.G, make_int2(p, blk)});
     }
     if (t.order == 0)
         std::stable_sort(it.begin(), it.end(), [](const auto &a, const auto &c) { return a.first > c.first; });
@@ -839,6 +873,8 @@ gpmppi_status batch_install(gpmppi_batch *b, const gpmppi_tuning &t) {
     HIP_TRY(hipMemcpy(b->ra, b->ra_h.data(), sizeof(RolloutArgs) * b->n, hipMemcpyHostToDevice));
     b->n_items = (int)items.size();
     b->G = t.groups;
+    b->GS = GS;
+    b->lds = b->precision == GPMPPI_BF16 ? 0 : batch_lds(b, t.groups);
     b->rotate = t.rotate;
     b->wg_per_cu = t.wg_per_cu;
     b->order = t.order;
@@ -918,10 +954,11 @@ gpmppi_status gpmppi_tune(gpmppi_ctx *c, const float *x0_d, const float *U_d, ui
     for (int G = 1; G <= G_max; ++G)
         for (int rot = 0; rot <= 1; ++rot)
             for (int nw = 4; nw <= kPipeWaves; nw += 4) {
-                // the wave-specialised shape walks W in one fixed order: rotate does not apply
                 if (nw == kPipeWaves && (rot != 0 || !rollout_pipe_admissible(c->params.precision, G, c->Mpad)))
                     continue;
                 for (int sp = 0; sp <= (G == 1 && nw != kPipeWaves && split_admissible(c, nw) ? 1 : 0); ++sp) {
+                    // FP32 and BF16x3 forms: rotate and four waves are shapes of split launches only
+                    if (c->params.precision != GPMPPI_BF16 && !sp && (rot != 0 || nw == 4)) continue;
                     c->groups = G;
                     c->rotate = rot;
                     c->waves = nw;
@@ -1043,7 +1080,7 @@ gpmppi_status gpmppi_batch_init(int32_t n, const gpmppi_params params[], const g
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, dev);
     b->cus = std::max(1, b->cus);
-    b->wg_per_cu_max = wg_capacity(b->precision, b->G_max, b->Mpad_max);
+    b->wg_per_cu_max = wg_capacity(b, b->G_max);
     if ((st = batch_install(b, gpmppi_tuning{b->G_max, 1, b->wg_per_cu_max, 0, 4, 0, 0.0})) != GPMPPI_OK) {
         delete b;
         return st;
@@ -1055,7 +1092,7 @@ gpmppi_status gpmppi_batch_init(int32_t n, const gpmppi_params params[], const g
 gpmppi_status gpmppi_batch_set_tuning(gpmppi_batch *b, const gpmppi_tuning *t) {
     g_last_error.clear();
     if (!b) return fail(GPMPPI_E_INVALID, "batch is NULL");
-    gpmppi_status st = check_tuning(t, b->G_max, t ? wg_capacity(b->precision, t->groups, b->Mpad_max) : 1, true);
+    gpmppi_status st = check_tuning(t, b->G_max, t ? wg_capacity(b, t->groups) : 1, true);
     if (st != GPMPPI_OK) return st;
     return batch_install(b, *t);
 }
@@ -1074,36 +1111,36 @@ gpmppi_status gpmppi_batch_tune(gpmppi_batch *b, const float *x0_d, const float 
     if (reps < 1 || reps > 100) return fail(GPMPPI_E_INVALID, "reps must lie in [1, 100] (got %d)", reps);
     hipStream_t st = (hipStream_t)stream;
     const gpmppi_tuning keep{b->G, b->rotate, b->wg_per_cu, b->order, b->waves, 0, 0.0};
-    gpmppi_tuning best{0, 0, 0, 0, 4, 0, -1.0};
+    gpmppi_tuning best{0, 0, 0, 0, 8, 0, -1.0};
     for (int G = 1; G <= b->G_max; ++G) {
-        const int wmax = wg_capacity(b->precision, G, b->Mpad_max);
-        for (int rot = 0; rot <= 1; ++rot)
+        const int wmax = wg_capacity(b, G);
+        // FP32 and BF16x3 forms: one wave count, no rotation
+        const bool one = b->precision != GPMPPI_BF16;
+        for (int rot = 0; rot <= (one ? 0 : 1); ++rot)
             for (int w = 1; w <= wmax; ++w)
                 for (int ord = 0; ord <= 1; ++ord)
-                for (int nw = 4; nw <= 8; nw += 4) {
-                    const gpmppi_tuning cand{G, rot, w, ord, nw, 0, 0.0};
-                    gpmppi_status r = batch_install(b, cand);
-                    double ms = 0.0;
-                    if (r == GPMPPI_OK) {
-                        const BatchPtrs q{x0_d, U_d, b->U_scratch, b->cost_scratch, nullptr, seed, nullptr,
-                                          b->U_off_d, b->K_off_d};
-                        r = time_launches(
-                            [&]() -> gpmppi_status {
-                                HIP_TRY(launch_batch_patch(b->ra, b->ua, b->n, q, st));
-                                HIP_TRY(launch_counter_reset(b->counters, st));
-                                HIP_TRY(launch_rollout_batch(b->ra, b->items, b->n_items, b->counters,
-                                                             b->precision, b->G, b->waves, b->Mpad_max, b->grid,
-                                                             st));
-                                return GPMPPI_OK;
-                            },
-                            reps, st, ms);
-                    }
-                    if (r != GPMPPI_OK) {
-                        (void)batch_install(b, keep);
-                        return r;
-                    }
-                    if (best.ms < 0 || ms < best.ms) best = gpmppi_tuning{G, rot, w, ord, nw, 0, ms};
+                for (int nw = one ? 8 : 4; nw <= 8; nw += 4) {
+                const gpmppi_tuning cand{G, rot, w, ord, nw, 0, 0.0};
+                gpmppi_status r = batch_install(b, cand);
+                double ms = 0.0;
+                if (r == GPMPPI_OK) {
+                    const BatchPtrs q{x0_d, U_d, b->U_scratch, b->cost_scratch, nullptr, seed, nullptr,
+                                      b->U_off_d, b->K_off_d};
+                    r = time_launches(
+                        [&]() -> gpmppi_status {
+                            HIP_TRY(launch_batch_patch(b->ra, b->ua, b->n, q, st));
+                            HIP_TRY(launch_counter_reset(b->counters, st));
+                            HIP_TRY(batch_rollout(b, st));
+                            return GPMPPI_OK;
+                        },
+                        reps, st, ms);
                 }
+                if (r != GPMPPI_OK) {
+                    (void)batch_install(b, keep);
+                    return r;
+                }
+                if (best.ms < 0 || ms < best.ms) best = gpmppi_tuning{G, rot, w, ord, nw, 0, ms};
+            }
     }
     gpmppi_status r = batch_install(b, best);
     if (r != GPMPPI_OK) return r;
