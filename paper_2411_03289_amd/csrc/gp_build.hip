@@ -1,12 +1,16 @@
-// Once-per-GP-update build of each residual GP in FP64 on the GPU
-// (Rasmussen & Williams Alg. 2.1 with the explicit inverse factor):
+// Once-per-GP-update build of the residual GPs in FP64 on the GPU
+// (Rasmussen & Williams Alg. 2.1 with the explicit inverse factor), both outputs
+// side by side in every launch:
 //   A = K(Z, Z) + sn^2 I         SE-ARD covariance (Sec. III-A, Sec. V-A)
-//   L = chol(A)                  blocked left-looking Cholesky, 32x32 tiles
-//   W = L^-1                     block-column forward substitution
+//   L = chol(A), W = L^-1        right-looking over block columns of 32, one launch each
 //   alpha = W^T (W y) = A^-1 y
 // and the packing of W, alpha and the scaled inputs into the FP32 / BF16
 // layouts the rollout streams.  Padding rows/columns (M <= i < Mpad) carry
 // the identity in A and are zeroed when packing.
+//
+// Every element is one chain of fused multiply-adds in ascending order of the
+// summed index (the FP64 matrix cores add a product's four terms in that order, each
+// rounded), followed by the division by the pivot.
 #include <cmath>
 
 #include "device_common.hpp"
@@ -15,180 +19,262 @@
 namespace gpmppi {
 
 constexpr int NB = 32;   // tile edge
+constexpr int kBlk = NB * NB;
+typedef double v4d __attribute__((ext_vector_type(4)));
 
-__global__ void kmat_kernel(const double *Z, int M, int Mpad, double i0, double i1, double i2, double i3,
-                            double sf2, double sn2, double *A) {
-    const int j = blockIdx.x * 16 + threadIdx.x;
-    const int i = blockIdx.y * 16 + threadIdx.y;
-    if (i >= Mpad || j >= Mpad) return;
+// The factorization's array: 32x32 blocks, block (b, a) at (b nb + a) 1024.
+//   b >= a  A's block of rows b and columns a, element [column][row]
+//   b < a   block (a, b) of what is left of L W = I, element [row][column]
+// so that one product with the row index from a's vectors and the column index from
+// b's updates either kind.
+__global__ void kmat_kernel(const double *Zs, int M, int Mpad, GpKernelParams kp, double *As) {
+    const int o = blockIdx.z;
+    const int j = blockIdx.x * 16 + threadIdx.y;
+    const int i = blockIdx.y * 16 + threadIdx.x;
+    if (i >= Mpad || j >= Mpad || (i / NB) < (j / NB)) return;
+    const double *Z = Zs + (size_t)o * 4 * M;
+    const double i0 = kp.i[o][0], i1 = kp.i[o][1], i2 = kp.i[o][2], i3 = kp.i[o][3];
     double v;
     if (i < M && j < M) {
         const double d0 = Z[4 * i] - Z[4 * j], d1 = Z[4 * i + 1] - Z[4 * j + 1];
         const double d2 = Z[4 * i + 2] - Z[4 * j + 2], d3 = Z[4 * i + 3] - Z[4 * j + 3];
         const double r2 = d0 * d0 * i0 + d1 * d1 * i1 + d2 * d2 * i2 + d3 * d3 * i3;
-        v = sf2 * exp(-0.5 * r2) + (i == j ? sn2 : 0.0);
+        v = kp.sf2[o] * exp(-0.5 * r2) + (i == j ? kp.sn2[o] : 0.0);
     } else {
         v = (i == j) ? 1.0 : 0.0;
     }
-    A[(size_t)i * Mpad + j] = v;
+    double *A = As + (size_t)o * Mpad * Mpad;
+    A[((size_t)(i / NB) * (Mpad / NB) + j / NB) * kBlk + (j % NB) * NB + i % NB] = v;
 }
 
-// Left-looking update of block column kb: A[ib][kb] -= sum_{pb<kb} L[ib][pb] L[kb][pb]^T
-// for ib = kb + blockIdx.x; the diagonal block is then factored in place.
-__global__ __launch_bounds__(256) void chol_column_kernel(double *A, int Mpad, int kb, uint32_t *flag) {
-    __shared__ double Ta[NB][NB + 1], Tb[NB][NB + 1], C[NB][NB + 1];
-    const int ib = kb + blockIdx.x;
-    const int tid = threadIdx.x;
-    const int row = tid >> 3, c0 = (tid & 7) * 4;   // each thread: 1 row x 4 columns
-    double acc[4];
-    for (int e = 0; e < 4; ++e) acc[e] = A[(size_t)(ib * NB + row) * Mpad + kb * NB + c0 + e];
-    for (int pb = 0; pb < kb; ++pb) {
-        for (int e = tid; e < NB * NB; e += 256) {
-            const int rr = e / NB, cc = e % NB;
-            Ta[rr][cc] = A[(size_t)(ib * NB + rr) * Mpad + pb * NB + cc];
-            Tb[rr][cc] = A[(size_t)(kb * NB + rr) * Mpad + pb * NB + cc];
-        }
-        __syncthreads();
-        for (int p = 0; p < NB; ++p) {
-            const double a = Ta[row][p];
-            for (int e = 0; e < 4; ++e) acc[e] -= a * Tb[c0 + e][p];
-        }
-        __syncthreads();
-    }
-    if (ib != kb) {
-        for (int e = 0; e < 4; ++e) A[(size_t)(ib * NB + row) * Mpad + kb * NB + c0 + e] = acc[e];
-        return;
-    }
-    for (int e = 0; e < 4; ++e) C[row][c0 + e] = acc[e];
-    __syncthreads();
+__device__ __forceinline__ double readlane64(double x, int lane) {
+    uint64_t u;
+    __builtin_memcpy(&u, &x, 8);
+    const uint64_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+    const uint64_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+    u = lo | (hi << 32);
+    __builtin_memcpy(&x, &u, 8);
+    return x;
+}
+
+// Square root s of a normal d (rounded to nearest) and r close to 1 / s: Newton's step for
+// 1 / sqrt(d) coupled with the root (Goldschmidt) from the hardware's estimate, then the root
+// corrected by its remainder (Markstein), twice.  The estimate of the reciprocal is a
+// by-product, so a pivot costs one chain instead of a square root and a division.
+__device__ __forceinline__ void sqrt_rcp(double d, double &s, double &r) {
+    const double y = __builtin_amdgcn_rsq(d);
+    double g = d * y, h = 0.5 * y;
+    double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    e = fma(-h, g, 0.5);
+    h = fma(h, e, h);
+    g = fma(fma(-g, g, d), h, g);
+    s = fma(fma(-g, g, d), h, g);
+    r = 2.0 * h;
+    r = fma(fma(-s, r, 1.0), r, r);
+}
+
+// Solves L x = v for one vector per lane of the upper half wave, L the Cholesky factor of
+// the diagonal block whose rows are the vectors of the lower half: both halves take the
+// same steps, x_c = v_c / L_cc and v_j -= x_c L_jc for j > c (lower half: x is L's row).
+// The quotient is v times the reciprocal, twice corrected by its remainder: the rounded
+// quotient.  Returns whether a pivot was not positive.
+__device__ __forceinline__ bool panel_solve(double (&v)[NB]) {
+    bool bad = false;
+#pragma unroll
     for (int c = 0; c < NB; ++c) {
-        if (tid == 0) {
-            const double d = C[c][c];
-            if (!(d > 0.0)) atomicOr(flag, 1u);
-            C[c][c] = sqrt(d > 0.0 ? d : 1.0);
+        double d = readlane64(v[c], c);
+        if (!(d > 0.0)) {
+            bad = true;
+            d = 1.0;
         }
-        __syncthreads();
-        if (tid > c && tid < NB) C[tid][c] /= C[c][c];
-        __syncthreads();
-        for (int e = tid; e < NB * NB; e += 256) {
-            const int i = e / NB, j = e % NB;
-            if (j > c && i >= j) C[i][j] -= C[i][c] * C[j][c];
-        }
-        __syncthreads();
+        double s, r;
+        sqrt_rcp(d, s, r);
+        double x = v[c] * r;
+        x = fma(fma(-x, s, v[c]), r, x);
+        x = fma(fma(-x, s, v[c]), r, x);
+        v[c] = x;
+#pragma unroll
+        for (int j = c + 1; j < NB; ++j) v[j] = fma(-x, readlane64(x, j), v[j]);
     }
-    for (int e = tid; e < NB * NB; e += 256) {
-        const int i = e / NB, j = e % NB;
-        A[(size_t)(kb * NB + i) * Mpad + kb * NB + j] = (j <= i) ? C[i][j] : 0.0;
-    }
+    return bad;
 }
 
-// L[ib][kb] = A[ib][kb] L[kb][kb]^-T for ib = kb + 1 + blockIdx.x.
-__global__ __launch_bounds__(64) void chol_trsm_kernel(double *A, int Mpad, int kb) {
-    __shared__ double Ld[NB][NB + 1], X[NB][NB + 1];
-    const int ib = kb + 1 + blockIdx.x;
-    const int tid = threadIdx.x;
-    for (int e = tid; e < NB * NB; e += 64) {
-        const int i = e / NB, j = e % NB;
-        Ld[i][j] = A[(size_t)(kb * NB + i) * Mpad + kb * NB + j];
-        X[i][j] = A[(size_t)(ib * NB + i) * Mpad + kb * NB + j];
-    }
-    __syncthreads();
-    if (tid < NB) {
-        const int rr = tid;   // row of X: X[r][c] = (A[r][c] - sum_{p<c} X[r][p] L[c][p]) / L[c][c]
-        for (int c = 0; c < NB; ++c) {
-            double v = X[rr][c];
-            for (int p = 0; p < c; ++p) v -= X[rr][p] * Ld[c][p];
-            X[rr][c] = v / Ld[c][c];
+// Step k of the factorization and of the inverse factor.  The vectors of block m are the
+// rows of L_mk (m > k) or the columns of W_km (m <= k): the solutions of panel_solve for
+// the block (m, k) (the identity for m = k).  A job of four waves solves two blocks a > k
+// and two blocks b, and subtracts the four products from the blocks (b, a); b >= a: the
+// trailing part of A, b <= k: what is left of L W = I.  Jobs n_upd ..: four blocks m of
+// W's row k, written to W (row-major) and, m < k, to block (k, m) as [column][row], where
+// L_km is no longer needed.
+//
+// Bound by the panel's serial chain (32 pivots of a root, a quotient and a rank-one update),
+// so every job repeats the pivot block's factorization instead of waiting for another launch to
+// do it: 9 to 18 us a step.  A whole update of both GPs (host calls, packing) went from
+// 9.9 ms to 0.77 ms at M = 1024; before, each output's block columns took two launches that
+// streamed the columns to the left (58 + 21 us) and one workgroup per column inverted L
+// (1.9 ms), alpha took 0.2 ms per product (one uncoalesced lane per row), now 28 us.
+__global__ __launch_bounds__(256) void factor_step_kernel(double *As, double *Ws, int nb, int k, int n_row, int n_upd,
+                                                          uint32_t *flag) {
+    __shared__ double X[4][kBlk];
+    const int o = blockIdx.y, lane = threadIdx.x & 63, col = lane & 31;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int Mpad = nb * NB;
+    double *A = As + (size_t)o * Mpad * Mpad;
+    const int job = blockIdx.x;
+    const bool upd = job < n_upd;
+    int m, last, a0 = 0, b0 = 0;
+    if (upd) {
+        int I, J = job;   // column pairs J of every row pair I: the trailing pairs up to I, then those of W
+        const int n_col = k / 2 + 1, tri = n_row * (n_row + 1) / 2;
+        if (job < tri) {
+            I = 0;
+            while (J > I) J -= ++I;
+            a0 = k + 1 + 2 * J;
+            b0 = k + 1 + 2 * I;
+        } else {
+            I = (job - tri) / n_col;
+            a0 = k + 1 + 2 * I;
+            b0 = 2 * ((job - tri) % n_col);
         }
-    }
-    __syncthreads();
-    for (int e = tid; e < NB * NB; e += 64) {
-        const int i = e / NB, j = e % NB;
-        A[(size_t)(ib * NB + i) * Mpad + kb * NB + j] = X[i][j];
-    }
-}
-
-// W[:, jb] = L^-1 e_jb by forward substitution over row blocks ib >= jb;
-// block jb = blockIdx.x.  W is lower triangular; blocks above are zeroed.
-__global__ __launch_bounds__(256) void trinv_kernel(const double *L, double *W, int Mpad) {
-    __shared__ double Lt[NB][NB + 1], Xt[NB][NB + 1], R[NB][NB + 1];
-    const int jb = blockIdx.x, nb = Mpad / NB;
-    const int tid = threadIdx.x;
-    const int row = tid >> 3, c0 = (tid & 7) * 4;
-    for (int ib = 0; ib < jb; ++ib)
-        for (int e = tid; e < NB * NB; e += 256)
-            W[(size_t)(ib * NB + e / NB) * Mpad + jb * NB + e % NB] = 0.0;
-    for (int ib = jb; ib < nb; ++ib) {
-        double acc[4];
-        for (int e = 0; e < 4; ++e) acc[e] = (ib == jb && row == c0 + e) ? 1.0 : 0.0;
-        for (int kb = jb; kb < ib; ++kb) {
-            for (int e = tid; e < NB * NB; e += 256) {
-                const int i = e / NB, j = e % NB;
-                Lt[i][j] = L[(size_t)(ib * NB + i) * Mpad + kb * NB + j];
-                Xt[i][j] = W[(size_t)(kb * NB + i) * Mpad + jb * NB + j];
-            }
-            __syncthreads();
-            for (int p = 0; p < NB; ++p) {
-                const double a = Lt[row][p];
-                for (int e = 0; e < 4; ++e) acc[e] -= a * Xt[p][c0 + e];
-            }
-            __syncthreads();
-        }
-        for (int e = 0; e < 4; ++e) R[row][c0 + e] = acc[e];
-        for (int e = tid; e < NB * NB; e += 256) {
-            const int i = e / NB, j = e % NB;
-            Lt[i][j] = L[(size_t)(ib * NB + i) * Mpad + ib * NB + j];
-        }
-        __syncthreads();
-        if (tid < NB) {   // column tid: solve Lt x = R[:, tid]
-            const int c = tid;
-            for (int i = 0; i < NB; ++i) {
-                double v = R[i][c];
-                for (int p = 0; p < i; ++p) v -= Lt[i][p] * R[p][c];
-                R[i][c] = v / Lt[i][i];
-            }
-        }
-        __syncthreads();
-        for (int e = tid; e < NB * NB; e += 256) {
-            const int i = e / NB, j = e % NB;
-            W[(size_t)(ib * NB + i) * Mpad + jb * NB + j] = R[i][j];
-        }
-        __syncthreads();
-    }
-}
-
-__global__ void matvec_lower_kernel(const double *W, const double *x, double *y, int Mpad, int transpose) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= Mpad) return;
-    double acc = 0.0;
-    if (!transpose) {
-        for (int j = 0; j <= i; ++j) acc += W[(size_t)i * Mpad + j] * x[j];
+        m = w < 2 ? a0 + w : b0 + w - 2;
+        last = w < 2 || b0 > k ? nb - 1 : k;
     } else {
-        for (int j = i; j < Mpad; ++j) acc += W[(size_t)j * Mpad + i] * x[j];
+        m = 4 * (job - n_upd) + w;
+        last = k;
     }
-    y[i] = acc;
+    const bool have = m <= last;
+    // this wave's products: blocks (b, a)
+    const int a = a0 + (w & 1), b = b0 + (w >> 1);
+    const bool prod = upd && a < nb && b <= (b0 > k ? nb - 1 : k) && (b0 <= k || b >= a);
+    double *T = A + ((size_t)b * nb + a) * kBlk;
+    v4d acc[2][2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                acc[s][t][r] = prod && b != k ? T[(16 * s + 4 * r + (lane >> 4)) * NB + 16 * t + (lane & 15)] : 0.0;
+    if (have) {
+        double v[NB];
+        const double *src = A + ((size_t)(lane < 32 ? k : m) * nb + k) * kBlk + col;
+#pragma unroll
+        for (int p = 0; p < NB; ++p) v[p] = src[p * NB];
+        if (m == k && lane >= 32) {
+#pragma unroll
+            for (int p = 0; p < NB; ++p) v[p] = p == col ? 1.0 : 0.0;
+        }
+        const bool bad = panel_solve(v);
+        if (bad && job == 0 && lane == 0) atomicOr(flag, 1u << o);
+        if (lane >= 32) {
+            if (upd) {
+#pragma unroll
+                for (int p = 0; p < NB; ++p) X[w][p * NB + col] = v[p];
+            } else {
+                double *W = Ws + (size_t)o * Mpad * Mpad + (size_t)k * NB * Mpad + m * NB + col;
+#pragma unroll
+                for (int p = 0; p < NB; ++p) W[(size_t)p * Mpad] = v[p];
+                if (m < k) {
+                    double2 *C = reinterpret_cast<double2 *>(A + ((size_t)k * nb + m) * kBlk + col * NB);
+#pragma unroll
+                    for (int p = 0; p < NB / 2; ++p) C[p] = make_double2(v[2 * p], v[2 * p + 1]);
+                }
+            }
+        }
+    }
+    if (!upd) return;
+    __syncthreads();
+    if (!prod) return;
+    const double *xa = X[w & 1] + (lane >> 4) * NB + (lane & 15), *xb = X[2 + (w >> 1)] + (lane >> 4) * NB + (lane & 15);
+#pragma unroll
+    for (int p = 0; p < NB; p += 4) {
+        const double va[2] = {-xa[p * NB], -xa[p * NB + 16]}, vb[2] = {xb[p * NB], xb[p * NB + 16]};
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+                acc[s][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(va[s], vb[t], acc[s][t], 0, 0, 0);
+    }
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) T[(16 * s + 4 * r + (lane >> 4)) * NB + 16 * t + (lane & 15)] = acc[s][t][r];
 }
 
-hipError_t build_gp_output(const GpBuildBuffers &b, int M, int Mpad, const double ell[4], double sf2,
-                           double sn2, hipStream_t st) {
-    const int nb = Mpad / NB;
-    hipLaunchKernelGGL(kmat_kernel, dim3(Mpad / 16, Mpad / 16), dim3(16, 16), 0, st, b.Z, M, Mpad,
-                       1.0 / (ell[0] * ell[0]), 1.0 / (ell[1] * ell[1]), 1.0 / (ell[2] * ell[2]),
-                       1.0 / (ell[3] * ell[3]), sf2, sn2, b.A);
-    for (int kb = 0; kb < nb; ++kb) {
-        hipLaunchKernelGGL(chol_column_kernel, dim3(nb - kb), dim3(256), 0, st, b.A, Mpad, kb, b.flag);
-        if (kb + 1 < nb) hipLaunchKernelGGL(chol_trsm_kernel, dim3(nb - kb - 1), dim3(64), 0, st, b.A, Mpad, kb);
+// u = W y (a wave per block row, a lane per row; the blocks below the diagonal as
+// factor_step_kernel left them in As) and alpha = W^T u (a lane per column).  One chain of
+// multiply-adds per entry, the next block's 32 elements loaded beside it.
+template <bool TRANS>
+__global__ __launch_bounds__(64) void matvec_kernel(const double *As, const double *Ws, int nb, const double *xs,
+                                                    size_t x_stride, double *ys, size_t y_stride) {
+    __shared__ double xl[32 * NB];
+    const int o = blockIdx.y, blk = blockIdx.x, lane = threadIdx.x, r = lane & 31;
+    const int Mpad = nb * NB;
+    const double *A = As + (size_t)o * Mpad * Mpad, *W = Ws + (size_t)o * Mpad * Mpad;
+    const double *x = xs + (size_t)o * x_stride;
+    for (int i = lane; i < Mpad; i += 64) xl[i] = x[i];
+    const int first = TRANS ? blk : 0, end = TRANS ? nb : blk + 1;
+    double cur[NB], nxt[NB];
+    auto load = [&](double (&v)[NB], int q) {
+        if (TRANS) {
+            const double *p = W + (size_t)q * NB * Mpad + blk * NB + r;
+#pragma unroll
+            for (int c = 0; c < NB; ++c) v[c] = p[(size_t)c * Mpad];
+        } else if (q < blk) {
+            const double *p = A + ((size_t)blk * nb + q) * kBlk + r;
+#pragma unroll
+            for (int c = 0; c < NB; ++c) v[c] = p[c * NB];
+        } else {
+            const double *p = W + (size_t)(blk * NB + r) * Mpad + blk * NB;
+#pragma unroll
+            for (int c = 0; c < NB; ++c) v[c] = p[c];
+        }
+    };
+    load(cur, first);
+    __syncthreads();
+    double acc = 0.0;
+    for (int q = first; q < end; ++q) {
+        if (q + 1 < end) load(nxt, q + 1);
+#pragma unroll
+        for (int c = 0; c < NB; ++c) acc = fma(cur[c], xl[q * NB + c], acc);
+#pragma unroll
+        for (int c = 0; c < NB; ++c) cur[c] = nxt[c];
     }
-    hipLaunchKernelGGL(trinv_kernel, dim3(nb), dim3(256), 0, st, b.A, b.W, Mpad);
-    hipLaunchKernelGGL(matvec_lower_kernel, dim3((Mpad + 255) / 256), dim3(256), 0, st, b.W, b.y, b.u, Mpad, 0);
-    hipLaunchKernelGGL(matvec_lower_kernel, dim3((Mpad + 255) / 256), dim3(256), 0, st, b.W, b.u, b.alpha, Mpad, 1);
+    if (lane < NB) ys[(size_t)o * y_stride + blk * NB + r] = acc;
+}
+
+// alpha [n_out outputs] for targets y: u is scratch.
+static void launch_alpha(const GpBuildBuffers &b, int Mpad, int n_out, const double *A, const double *W,
+                         const double *y, double *alpha, hipStream_t st) {
+    const int nb = Mpad / NB;
+    hipLaunchKernelGGL(matvec_kernel<false>, dim3(nb, n_out), dim3(64), 0, st, A, W, nb, y, (size_t)Mpad, b.u,
+                       (size_t)Mpad);
+    hipLaunchKernelGGL(matvec_kernel<true>, dim3(nb, n_out), dim3(64), 0, st, A, W, nb, b.u, (size_t)Mpad, alpha,
+                       (size_t)Mpad);
+}
+
+hipError_t factor_gps(const GpBuildBuffers &b, int M, int Mpad, const GpKernelParams &kp, hipStream_t st) {
+    const int nb = Mpad / NB;
+    hipLaunchKernelGGL(kmat_kernel, dim3(Mpad / 16, Mpad / 16, 2), dim3(16, 16), 0, st, b.Z, M, Mpad, kp, b.A);
+    for (int k = 0; k < nb; ++k) {
+        const int n_row = (nb - k) / 2;   // pairs of trailing blocks
+        const int n_upd = n_row * (n_row + 1) / 2 + n_row * (k / 2 + 1);
+        hipLaunchKernelGGL(factor_step_kernel, dim3(n_upd + k / 4 + 1, 2), dim3(256), 0, st, b.A, b.W, nb, k, n_row,
+                           n_upd, b.flag);
+    }
+    launch_alpha(b, Mpad, 2, b.A, b.W, b.y, b.alpha, st);
     return hipGetLastError();
 }
 
-// alpha = W^T (W y) for another target vector y on the same W (b.u is scratch).
-hipError_t alpha_for_targets(const GpBuildBuffers &b, int Mpad, const double *y_d, double *alpha_d, hipStream_t st) {
-    hipLaunchKernelGGL(matvec_lower_kernel, dim3((Mpad + 255) / 256), dim3(256), 0, st, b.W, y_d, b.u, Mpad, 0);
-    hipLaunchKernelGGL(matvec_lower_kernel, dim3((Mpad + 255) / 256), dim3(256), 0, st, b.W, b.u, alpha_d, Mpad, 1);
+// alpha = W^T (W y) for another target vector y of output o on the same W (b.u is scratch).
+hipError_t alpha_for_targets(const GpBuildBuffers &b, int Mpad, int o, const double *y_d, double *alpha_d,
+                             hipStream_t st) {
+    const size_t at = (size_t)o * Mpad * Mpad;
+    launch_alpha(b, Mpad, 1, b.A + at, b.W + at, y_d, alpha_d, st);
     return hipGetLastError();
 }
 
@@ -209,42 +295,46 @@ hipError_t combine_alpha(const double *alpha_terr, int n_terr, int Mpad, Terrain
     return hipGetLastError();
 }
 
-// Q = W^T W = A^-1 (FP64) into Qd, for the adjoint's r = Q k; one thread
-// per entry, the sum running over the rows k >= max(i, j) where W is nonzero.
-__global__ void qmat_kernel(const double *W, int Mpad, double *Qd) {
-    const int j = blockIdx.x * 16 + threadIdx.x;
-    const int i = blockIdx.y * 16 + threadIdx.y;
-    if (i >= Mpad || j >= Mpad) return;
-    double acc = 0.0;
-    for (int k = (i > j ? i : j); k < Mpad; ++k) acc += W[(size_t)k * Mpad + i] * W[(size_t)k * Mpad + j];
-    Qd[(size_t)i * Mpad + j] = acc;
-}
-
-// Dense FP32 packing of Q in the matrix-core operand order of the FP32 W
-// blocks: block b = t NT + it, float4 [b][q][lane], component c holds
-// Q[32t + l%32][32 it + 2(4q+c) + l/32].  Rows/columns beyond M are zero.
-__global__ void pack_q_kernel(const double *Qd, int M, int Mpad, float4 *q32) {
-    const int blk = blockIdx.x, lane = threadIdx.x;
-    const int NT = Mpad / 32;
-    const int t = blk / NT, it = blk % NT;
-    const int i = 32 * t + (lane & 31);
-    const int half = lane >> 5;
-    auto qval = [&](int j) -> float { return (i < M && j < M) ? (float)Qd[(size_t)i * Mpad + j] : 0.0f; };
-    for (int q = 0; q < 4; ++q) {
-        float4 v;
-        v.x = qval(32 * it + 2 * (4 * q + 0) + half);
-        v.y = qval(32 * it + 2 * (4 * q + 1) + half);
-        v.z = qval(32 * it + 2 * (4 * q + 2) + half);
-        v.w = qval(32 * it + 2 * (4 * q + 3) + half);
-        q32[(size_t)blk * 256 + q * 64 + lane] = v;
+// Q = W^T W = A^-1 in FP64 for the adjoint's r = Q k, rounded into the matrix-core
+// operand order of the FP32 W blocks: block b = t NT + it, float4 [b][q][lane], component
+// c holds Q[32t + l%32][32 it + 2(4q+c) + l/32].  Rows/columns beyond M are zero.  A
+// workgroup per block on or below the diagonal, a wave per 16x16 quarter; the block is
+// stored with its mirror image.
+__global__ __launch_bounds__(256) void qmat_kernel(const double *W, int M, int Mpad, float *q32) {
+    const int NT = Mpad / NB;
+    int t = 0, it = blockIdx.x;
+    while (it > t) it -= ++t;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int i0 = NB * t + 16 * (w & 1), j0 = NB * it + 16 * (w >> 1);
+    const double *p = W + (size_t)(NB * t + (lane >> 4)) * Mpad + (lane & 15);
+    v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
+    for (int k = NB * t; k < Mpad; k += NB) {
+        double va[NB / 4], vb[NB / 4];
+#pragma unroll
+        for (int i = 0; i < NB / 4; ++i, p += (size_t)4 * Mpad) {
+            va[i] = p[i0];
+            vb[i] = p[j0];
+        }
+#pragma unroll
+        for (int i = 0; i < NB / 4; ++i) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(va[i], vb[i], acc, 0, 0, 0);
+    }
+    auto put = [&](int i, int j, float v) {
+        const int c = j & 31;
+        q32[((size_t)((i >> 5) * NT + (j >> 5)) * 256 + (c >> 3) * 64 + (i & 31) + 32 * (c & 1)) * 4 + ((c >> 1) & 3)] = v;
+    };
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = i0 + 4 * r + (lane >> 4), j = j0 + (lane & 15);
+        const float v = i < M && j < M ? (float)acc[r] : 0.0f;
+        put(i, j, v);
+        if (t != it) put(j, i, v);
     }
 }
 
-hipError_t pack_q(const GpBuildBuffers &b, int M, int Mpad, float4 *q32, hipStream_t st) {
-    // A (the Cholesky factor's storage) is free once W has been formed
-    hipLaunchKernelGGL(qmat_kernel, dim3(Mpad / 16, Mpad / 16), dim3(16, 16), 0, st, b.W, Mpad, b.A);
-    const int NT = Mpad / 32;
-    hipLaunchKernelGGL(pack_q_kernel, dim3(NT * NT), dim3(64), 0, st, b.A, M, Mpad, q32);
+hipError_t pack_q(const GpBuildBuffers &b, int M, int Mpad, int o, float4 *q32, hipStream_t st) {
+    const int NT = Mpad / NB;
+    hipLaunchKernelGGL(qmat_kernel, dim3(NT * (NT + 1) / 2), dim3(256), 0, st, b.W + (size_t)o * Mpad * Mpad, M, Mpad,
+                       reinterpret_cast<float *>(q32));
     return hipGetLastError();
 }
 
@@ -460,15 +550,16 @@ __global__ void pack_zop_kernel(const float *zs2, const float *cz, int Mpad, uin
     zop16[i] = pack(slot + 8 * (lane >> 4));
 }
 
-hipError_t pack_gp_output(const GpBuildBuffers &b, int M, int Mpad, const double scale[4], double sf2, const GpPacked &p,
-                          hipStream_t st) {
+hipError_t pack_gp_output(const GpBuildBuffers &b, int M, int Mpad, int o, const double scale[4], double sf2,
+                          const GpPacked &p, hipStream_t st) {
     const int NP = (Mpad / 32 + 1) / 2;
-    hipLaunchKernelGGL(row_scale_kernel, dim3(Mpad), dim3(64), 0, st, b.W, M, Mpad, std::sqrt(sf2), p.wrs);
-    hipLaunchKernelGGL(pack_w_kernel, dim3(2 * NP * (NP + 1)), dim3(64), 0, st, b.W, M, Mpad, std::sqrt(sf2), p.wrs,
+    const double *W = b.W + (size_t)o * Mpad * Mpad;
+    hipLaunchKernelGGL(row_scale_kernel, dim3(Mpad), dim3(64), 0, st, W, M, Mpad, std::sqrt(sf2), p.wrs);
+    hipLaunchKernelGGL(pack_w_kernel, dim3(2 * NP * (NP + 1)), dim3(64), 0, st, W, M, Mpad, std::sqrt(sf2), p.wrs,
                        p.w32, p.wbh, p.wbl, p.wfh, p.wfl);
-    hipLaunchKernelGGL(pack_vec_kernel, dim3((Mpad + 255) / 256), dim3(256), 0, st, b.Z, b.alpha, M, Mpad,
-                       scale[0], scale[1], scale[2], scale[3], std::log2(sf2), sf2, p.zs, p.alpha, p.alphas, p.zs2,
-                       p.cz);
+    hipLaunchKernelGGL(pack_vec_kernel, dim3((Mpad + 255) / 256), dim3(256), 0, st, b.Z + (size_t)o * 4 * M,
+                       b.alpha + (size_t)o * Mpad, M, Mpad, scale[0], scale[1], scale[2], scale[3], std::log2(sf2),
+                       sf2, p.zs, p.alpha, p.alphas, p.zs2, p.cz);
     hipLaunchKernelGGL(pack_zop_kernel, dim3((Mpad / 32 * 128 + 255) / 256), dim3(256), 0, st, p.zs2, p.cz, Mpad, p.zop,
                        p.zop16);
     return hipGetLastError();

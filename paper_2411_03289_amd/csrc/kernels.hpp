@@ -171,18 +171,21 @@ hipError_t launch_plant_shift(const float *x, float *x_out, float *U, int T, Dyn
                               uint32_t *step_counter, float *x_hist, float *U0_hist, hipStream_t st);
 hipError_t launch_counter_reset(uint32_t *counter, hipStream_t st);
 
-// FP64 GP build on the device (per output).
+// FP64 GP build on the device, both outputs side by side ([2][..] arrays).
 struct GpBuildBuffers {
-    double *A;        // [Mpad][Mpad] K + sn^2 I, overwritten by L (lower)
-    double *W;        // [Mpad][Mpad] L^-1
-    double *Z;        // [M][4]
-    double *y;        // [Mpad]
-    double *u;        // [Mpad] scratch
-    double *alpha;    // [Mpad]
-    uint32_t *flag;   // non-PD flag
+    double *A;        // [2][Mpad][Mpad] K + sn^2 I and the factorization's blocks (see gp_build.hip)
+    double *W;        // [2][Mpad][Mpad] L^-1, row-major; blocks above the diagonal are not written
+    double *Z;        // [2][M][4]
+    double *y;        // [2][Mpad]
+    double *u;        // [2][Mpad] scratch
+    double *alpha;    // [2][Mpad]
+    uint32_t *flag;   // bit o: output o's matrix is not positive definite
 };
-hipError_t build_gp_output(const GpBuildBuffers &b, int M, int Mpad, const double ell[4], double sf2,
-                           double sn2, hipStream_t st);
+struct GpKernelParams {
+    double i[2][4];   // 1 / ell^2
+    double sf2[2], sn2[2];
+};
+hipError_t factor_gps(const GpBuildBuffers &b, int M, int Mpad, const GpKernelParams &kp, hipStream_t st);
 struct TerrainWeights {
     double w[8];
 };
@@ -237,9 +240,10 @@ constexpr int kGradXchPerBlock = 2 * 4 * 4 * kSamplesPerBlock;   // split exchan
 int grad_split_capacity(int Mpad);
 hipError_t launch_grad(const GradArgs &a, const GradLaunch &l, hipStream_t st);
 
-// Q = A^-1 = W^T W packed dense (FP32 operand order); overwrites b.A.
-hipError_t pack_q(const GpBuildBuffers &b, int M, int Mpad, float4 *q32, hipStream_t st);
-hipError_t alpha_for_targets(const GpBuildBuffers &b, int Mpad, const double *y_d, double *alpha_d, hipStream_t st);
+// Q = A^-1 = W^T W of output o packed dense (FP32 operand order).
+hipError_t pack_q(const GpBuildBuffers &b, int M, int Mpad, int o, float4 *q32, hipStream_t st);
+hipError_t alpha_for_targets(const GpBuildBuffers &b, int Mpad, int o, const double *y_d, double *alpha_d,
+                             hipStream_t st);
 // Device arrays of one output that pack_gp_output fills (see GpDev).
 struct GpPacked {
     uint4 *zop, *zop16;
@@ -247,7 +251,7 @@ struct GpPacked {
     float4 *w32;
     uint4 *wbh, *wbl, *wfh, *wfl;
 };
-hipError_t pack_gp_output(const GpBuildBuffers &b, int M, int Mpad, const double scale[4], double sf2, const GpPacked &p,
-                          hipStream_t st);
+hipError_t pack_gp_output(const GpBuildBuffers &b, int M, int Mpad, int o, const double scale[4], double sf2,
+                          const GpPacked &p, hipStream_t st);
 
 }  // namespace gpmppi

@@ -289,6 +289,33 @@ gpmppi_status validate_world(const gpmppi_obstacles *ob, const gpmppi_path *pa) 
     return GPMPPI_OK;
 }
 
+GpBuildBuffers build_buffers(const gpmppi_ctx *c) {
+    return GpBuildBuffers{c->A64, c->W64, c->Z64, c->y64, c->u64, c->al64, c->flags + 1};
+}
+
+// Factors both outputs of the GPs whose inputs and hyperparameters the context holds, with
+// alpha for the targets in y64; bit o of notpd: output o's matrix is not positive definite.
+gpmppi_status factor_gps(gpmppi_ctx *c, uint32_t &notpd) {
+    const int M = c->M;
+    GpKernelParams kp{};
+    std::vector<double> Z((size_t)2 * 4 * M);
+    for (int o = 0; o < 2; ++o) {
+        std::memcpy(Z.data() + (size_t)o * 4 * M, c->Zh[o].data(), sizeof(double) * 4 * M);
+        for (int d = 0; d < 4; ++d) {
+            const double ell = std::exp(c->log_ell[o][d]);
+            kp.i[o][d] = 1.0 / (ell * ell);
+        }
+        kp.sf2[o] = std::exp(2.0 * c->log_sf[o]);
+        kp.sn2[o] = std::exp(2.0 * c->log_sn[o]);
+    }
+    HIP_TRY(hipMemcpy(c->Z64, Z.data(), sizeof(double) * Z.size(), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemset(c->flags + 1, 0, sizeof(uint32_t)));
+    const GpBuildBuffers b = build_buffers(c);
+    HIP_TRY(factor_gps(b, M, c->Mpad, kp, nullptr));
+    HIP_TRY(hipMemcpy(&notpd, c->flags + 1, sizeof notpd, hipMemcpyDeviceToHost));
+    return GPMPPI_OK;
+}
+
 gpmppi_status build_gps(gpmppi_ctx *c, const gpmppi_gp gp[2]) {
     const int M = c->M, Mpad = c->Mpad;
     for (int o = 0; o < 2; ++o) {
@@ -299,38 +326,36 @@ gpmppi_status build_gps(gpmppi_ctx *c, const gpmppi_gp gp[2]) {
         c->log_sn[o] = gp[o].log_sn;
     }
     c->n_terr = 0;
+    std::vector<double> y((size_t)2 * Mpad, 0.0);
+    for (int o = 0; o < 2; ++o) std::memcpy(y.data() + (size_t)o * Mpad, gp[o].y, sizeof(double) * M);
+    HIP_TRY(hipMemcpy(c->y64, y.data(), sizeof(double) * 2 * Mpad, hipMemcpyHostToDevice));
+    uint32_t notpd = 0;
+    gpmppi_status r = factor_gps(c, notpd);
+    if (r != GPMPPI_OK) return r;
     const double kScale = std::sqrt(0.5 / std::log(2.0));   // sqrt(log2(e) / 2)
     for (int o = 0; o < 2; ++o) {
-        std::vector<double> y(Mpad, 0.0);
-        std::memcpy(y.data(), gp[o].y, sizeof(double) * M);
-        HIP_TRY(hipMemcpy(c->Z64, gp[o].Z, sizeof(double) * 4 * M, hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(c->y64, y.data(), sizeof(double) * Mpad, hipMemcpyHostToDevice));
-        HIP_TRY(hipMemset(c->flags + 1, 0, sizeof(uint32_t)));
-        double ell[4], scale[4];
-        for (int d = 0; d < 4; ++d) {
-            ell[d] = std::exp(gp[o].log_ell[d]);
-            scale[d] = kScale / ell[d];
+        if (notpd & (1u << o)) {
+            (void)hipDeviceSynchronize();
+            return fail(GPMPPI_E_NOT_PD, "GP %d: K(Z,Z) + sn^2 I is not positive definite", o);
         }
+        double scale[4];
+        for (int d = 0; d < 4; ++d) scale[d] = kScale / std::exp(gp[o].log_ell[d]);
         const double sf2 = std::exp(2.0 * gp[o].log_sf), sn2 = std::exp(2.0 * gp[o].log_sn);
-        GpBuildBuffers b{c->A64, c->W64, c->Z64, c->y64, c->u64, c->al64, c->flags + 1};
-        HIP_TRY(build_gp_output(b, M, Mpad, ell, sf2, sn2, nullptr));
-        uint32_t notpd = 0;
-        HIP_TRY(hipMemcpy(&notpd, c->flags + 1, sizeof notpd, hipMemcpyDeviceToHost));
-        if (notpd) return fail(GPMPPI_E_NOT_PD, "GP %d: K(Z,Z) + sn^2 I is not positive definite", o);
+        const GpBuildBuffers b = build_buffers(c);
         const size_t mo = (size_t)o * Mpad;
         const GpPacked packed{c->zop + o * c->zop_stride, c->zop16 + o * c->zop_stride, c->zs + 4 * mo, c->alpha + mo,
                               c->alphas + mo, c->zs2 + 4 * mo, c->cz + mo, c->wrs + mo, c->w32 + o * c->w32_stride,
                               c->wbh + o * c->wb_stride, c->wbl + o * c->wb_stride, c->wfh + o * c->wb_stride,
                               c->wfl + o * c->wb_stride};
-        HIP_TRY(pack_gp_output(b, M, Mpad, scale, sf2, packed, nullptr));
-        if (c->q32) HIP_TRY(pack_q(b, M, Mpad, c->q32 + (size_t)o * c->q_stride, nullptr));
-        HIP_TRY(hipDeviceSynchronize());
+        HIP_TRY(pack_gp_output(b, M, Mpad, o, scale, sf2, packed, nullptr));
+        if (c->q32) HIP_TRY(pack_q(b, M, Mpad, o, c->q32 + (size_t)o * c->q_stride, nullptr));
         for (int d = 0; d < 4; ++d) c->gp.scale[o][d] = (float)scale[d];
         c->gp.c2[o] = (float)(2.0 * gp[o].log_sf / std::log(2.0));
         c->gp.sf2[o] = (float)sf2;
         c->gp.sn2[o] = (float)sn2;
         c->gp.vscale[o] = 1.0f;
     }
+    HIP_TRY(hipDeviceSynchronize());
     return GPMPPI_OK;
 }
 
@@ -465,12 +490,12 @@ gpmppi_status gpmppi_init(const gpmppi_params *params, const gpmppi_gp gp[2], co
     c->seg = track(dev_alloc<float4>((size_t)std::max(1, P), st));
     c->seg_inv = track(dev_alloc<float>((size_t)std::max(1, P), st));
     c->flags = track(dev_alloc<uint32_t>(4, st));
-    c->A64 = track(dev_alloc<double>((size_t)Mpad * Mpad, st));
-    c->W64 = track(dev_alloc<double>((size_t)Mpad * Mpad, st));
-    c->Z64 = track(dev_alloc<double>((size_t)Mpad * 4, st));
-    c->y64 = track(dev_alloc<double>((size_t)Mpad, st));
-    c->u64 = track(dev_alloc<double>((size_t)Mpad, st));
-    c->al64 = track(dev_alloc<double>((size_t)Mpad, st));
+    c->A64 = track(dev_alloc<double>((size_t)2 * Mpad * Mpad, st));
+    c->W64 = track(dev_alloc<double>((size_t)2 * Mpad * Mpad, st));
+    c->Z64 = track(dev_alloc<double>((size_t)2 * Mpad * 4, st));
+    c->y64 = track(dev_alloc<double>((size_t)2 * Mpad, st));
+    c->u64 = track(dev_alloc<double>((size_t)2 * Mpad, st));
+    c->al64 = track(dev_alloc<double>((size_t)2 * Mpad, st));
     c->U_scratch = track(dev_alloc<float>((size_t)2 * params->T, st));
     c->cost_scratch = track(dev_alloc<float>((size_t)params->K, st));
     c->tight = track(dev_alloc<float>((size_t)3 * (params->T + 1) + 1, st));
@@ -590,25 +615,20 @@ gpmppi_status gpmppi_set_terrains(gpmppi_ctx *c, int32_t n_terr, const double *y
     c->alpha_terr = dev_alloc<double>((size_t)2 * n_terr * Mpad, st);
     if (st != GPMPPI_OK) return st;
     c->owned.push_back(c->alpha_terr);
+    // factor both outputs once (the targets do not enter L or W), then one alpha per terrain
+    HIP_TRY(hipMemset(c->y64, 0, sizeof(double) * 2 * Mpad));
+    uint32_t notpd = 0;
+    const gpmppi_status r = factor_gps(c, notpd);
+    if (r != GPMPPI_OK) return r;
     std::vector<double> yp(Mpad, 0.0);
     for (int o = 0; o < 2; ++o) {
-        // factor this output once (the targets do not enter L or W), then one alpha per terrain
-        double ell[4];
-        for (int d = 0; d < 4; ++d) ell[d] = std::exp(c->log_ell[o][d]);
-        HIP_TRY(hipMemcpy(c->Z64, c->Zh[o].data(), sizeof(double) * 4 * M, hipMemcpyHostToDevice));
-        HIP_TRY(hipMemset(c->y64, 0, sizeof(double) * Mpad));
-        HIP_TRY(hipMemset(c->flags + 1, 0, sizeof(uint32_t)));
-        GpBuildBuffers b{c->A64, c->W64, c->Z64, c->y64, c->u64, c->al64, c->flags + 1};
-        HIP_TRY(build_gp_output(b, M, Mpad, ell, std::exp(2.0 * c->log_sf[o]), std::exp(2.0 * c->log_sn[o]),
-                                nullptr));
-        uint32_t notpd = 0;
-        HIP_TRY(hipMemcpy(&notpd, c->flags + 1, sizeof notpd, hipMemcpyDeviceToHost));
-        if (notpd) return fail(GPMPPI_E_NOT_PD, "GP %d: K(Z,Z) + sn^2 I is not positive definite", o);
+        if (notpd & (1u << o)) return fail(GPMPPI_E_NOT_PD, "GP %d: K(Z,Z) + sn^2 I is not positive definite", o);
+        const GpBuildBuffers b = build_buffers(c);
         for (int i = 0; i < n_terr; ++i) {
             std::fill(yp.begin(), yp.end(), 0.0);
             std::memcpy(yp.data(), y + ((size_t)i * 2 + o) * M, sizeof(double) * M);
             HIP_TRY(hipMemcpy(c->y64, yp.data(), sizeof(double) * Mpad, hipMemcpyHostToDevice));
-            HIP_TRY(alpha_for_targets(b, Mpad, c->y64, c->alpha_terr + ((size_t)o * n_terr + i) * Mpad, nullptr));
+            HIP_TRY(alpha_for_targets(b, Mpad, o, c->y64, c->alpha_terr + ((size_t)o * n_terr + i) * Mpad, nullptr));
             HIP_TRY(hipDeviceSynchronize());
         }
     }
