@@ -219,29 +219,30 @@ gpmppi_status gpmppi_closed_loop(gpmppi_ctx *ctx, float *x_d, float *U_d, uint64
  * the two GPs.  The noise is fixed by the seed (common random numbers); the
  * derivative of clip(U + eps) is 1 strictly inside the box and 0 outside; the
  * hyperparameter derivative is total (through the kernel vectors, alpha and
- * (K(Z, Z) + sn^2 I)^-1).  The adjoint rollout stores the state every
- * checkpoint_every steps (in [1, T]) and recomputes each segment before
- * reversing it; results do not depend on checkpoint_every.
+ * (K(Z, Z) + sn^2 I)^-1).  checkpoint_every (in [1, T]) bounds the records kept
+ * beside the r rows (see below) where memory is short; results do not depend on it.
  * FP32 on the GPU, whatever the context's precision.  Needs M <= 512, no
  * terrain ensemble, no goal terms and no Step-2 tightening
  * (GPMPPI_E_UNSUPPORTED otherwise).
  * x0_d [5], U_d [T][2] device; outputs (device): J_d [1], dU_d [T][2],
  * dlog_ell_d [2][4], dlog_sf_d [2], costs_d [K] the smoothed per-sample costs
- * (may be NULL).  A workspace of about 8 T K Mpad bytes (the r = A^-1 k rows of
- * every sample and step) is allocated on first use and kept by the context
- * (GPMPPI_E_NOMEM if that fails).  Enqueued on stream. */
+ * (may be NULL).  A workspace of about 8 T K (Mpad + 35) bytes (the r = A^-1 k rows and
+ * the records of every sample and step) is allocated on first use and kept by the context;
+ * where that fails, the samples are taken in chunks that need no more than 8 T K Mpad bytes
+ * and checkpoints at every checkpoint_every steps would (GPMPPI_E_NOMEM if that fails
+ * too).  Enqueued on stream. */
 gpmppi_status gpmppi_grad(gpmppi_ctx *ctx, const float *x0_d, const float *U_d, uint64_t seed, double tau,
                           int32_t checkpoint_every, float *J_d, float *dU_d, float *dlog_ell_d, float *dlog_sf_d,
                           float *costs_d, void *stream);
 
-/* The gradient's launch shape: split = 1 (the default) runs each 32-sample
- * block's two GP outputs on two workgroups that exchange, per step, their
- * output's mean and variance (forward) and their share of the GP inputs'
- * adjoint (backward), wherever the doubled grid fits the device at once
- * (K <= 4096 at M <= 512 on MI355X); 0 keeps one workgroup per block.  The
- * results do not depend on it (bit for bit).  Exchange waits are bounded as
- * for the rollout (gpmppi_set_exchange_spin); a block whose wait gives up is
- * recomputed by a repair launch and GPMPPI_FLAG_EXCHANGE_TIMEOUT is set. */
+/* The gradient's launch shape: split = 1 (the default) runs its rollout with the
+ * output split (two workgroups per 32-sample block, see gpmppi_tuning) where that
+ * is the faster shape (M > 256) and the doubled grid fits the device at once
+ * (K <= 4096 on MI355X); 0 never splits.  The results do not depend on it (bit
+ * for bit).  Exchange waits are bounded as for the rollout
+ * (gpmppi_set_exchange_spin; a negative bound takes the split at every M); a block
+ * whose wait gives up is recomputed by a repair launch and
+ * GPMPPI_FLAG_EXCHANGE_TIMEOUT is set. */
 gpmppi_status gpmppi_set_grad_split(gpmppi_ctx *ctx, int32_t split);
 
 /* Allocation-free gpmppi_grad, for callers that cannot allocate device memory

@@ -195,18 +195,17 @@ struct StepAdj {
     float ub[2];    // of the sampled, clipped controls u_k (their GP-input share excluded)
 };
 
-// One reversed step of one sample, GP excluded.  On entry xb, pb hold the
-// adjoint of (x_{k+1}, Sigma_{k+1}) carried from the later steps; the stage
-// cost's adjoint at (x_{k+1}, Sigma_{k+1}, s2_k) (weight cbar, discount disc_k,
-// argmin segment iseg and obstacle iobs) is added, then the covariance
-// update, the Euler step and the Jacobian are reversed: on return xb, pb hold
-// the adjoint of (x_k, Sigma_k) without the GP inputs' share.
-__host__ __device__ inline void step_adjoint(const Geometry &geo, const CostWeights &cw, const Dyn &dy, float inv_tau,
-                                             float cbar, float disc_k, const float xk[5], const float pk[15],
-                                             const float x1[5], const float p1[15], int iseg, int iobs, float xb[5],
-                                             float pb[15], StepAdj &out) {
-    const float dt = dy.dt;
-    const float X1 = x1[0], Y1 = x1[1], v1 = x1[3];
+// Adjoint of the stage cost at (x_{k+1}, Sigma_{k+1}) (weight cbar, discount disc_k, argmin
+// segment iseg and obstacle iobs) apart from its speed term and its variance term.
+struct StageAdj {
+    float X, Y;          // of the position
+    float sa, sb, sc;    // of Sigma_XX, Sigma_XY, Sigma_YY
+};
+
+__host__ __device__ inline StageAdj stage_adjoint(const Geometry &geo, const CostWeights &cw, float inv_tau, float cbar,
+                                                  float disc_k, const float x1[5], const float p1[15], int iseg,
+                                                  int iobs) {
+    const float X1 = x1[0], Y1 = x1[1];
     const float sa = p1[0], sb = p1[1], sc = p1[5];
     float da, db, dc;
     const float lmax = lmax_grad(sa, sb, sc, da, db, dc);
@@ -214,8 +213,6 @@ __host__ __device__ inline void step_adjoint(const Geometry &geo, const CostWeig
     const float dl = lane_dist_grad(geo, X1, Y1, iseg, gx, gy);
     const float sq = sqrtf(fmaxf(lmax, 0.0f));
     const float rbar = geo.half_width - geo.c_p * sq;
-    out.s2b[0] = cbar * cw.w_var;
-    out.s2b[1] = cbar * cw.w_var;
     float lamb = 0.0f;   // adjoint of lambda_max(Sigma_XY)
     float dlb = cbar * cw.w_dev * geo.inv_half_width;
     {
@@ -224,8 +221,7 @@ __host__ __device__ inline void step_adjoint(const Geometry &geo, const CostWeig
         dlb += gL;
         if (sq > 0.0f) lamb += gL * geo.c_p * 0.5f / sq;   // r_bar = r - c_p sqrt(lambda)
     }
-    float Xb1 = gx * dlb, Yb1 = gy * dlb;
-    float Sab = 0.0f, Sbb = 0.0f, Scb = 0.0f;
+    StageAdj t{gx * dlb, gy * dlb, 0.0f, 0.0f, 0.0f};
     if (iobs >= 0) {
         const float4 ob = geo.obs[iobs];
         const float dx = X1 - ob.x, dyy = Y1 - ob.y;
@@ -238,28 +234,41 @@ __host__ __device__ inline void step_adjoint(const Geometry &geo, const CostWeig
         const float omb = -cbar * cw.w_obs * sO * (1.0f - sO) * inv_tau;
         const float varb = sv > 0.0f ? omb * (-geo.z_p) * 0.5f / sv : 0.0f;
         if (rho > 0.0f) {
-            Xb1 += omb * dx / rho + varb * 2.0f * (sa * dx + sb * dyy - var * dx) / rho2;
-            Yb1 += omb * dyy / rho + varb * 2.0f * (sb * dx + sc * dyy - var * dyy) / rho2;
-            Sab += varb * dx * dx / rho2;
-            Sbb += varb * 2.0f * dx * dyy / rho2;
-            Scb += varb * dyy * dyy / rho2;
+            t.X += omb * dx / rho + varb * 2.0f * (sa * dx + sb * dyy - var * dx) / rho2;
+            t.Y += omb * dyy / rho + varb * 2.0f * (sb * dx + sc * dyy - var * dyy) / rho2;
+            t.sa += varb * dx * dx / rho2;
+            t.sb += varb * 2.0f * dx * dyy / rho2;
+            t.sc += varb * dyy * dyy / rho2;
         } else {
             lamb += varb;
         }
     }
-    Sab += lamb * da;
-    Sbb += lamb * db;
-    Scb += lamb * dc;
-    const float Xn_b = xb[0] + Xb1, Yn_b = xb[1] + Yb1, thn_b = xb[2];
+    t.sa += lamb * da;
+    t.sb += lamb * db;
+    t.sc += lamb * dc;
+    return t;
+}
+
+// One reversed step of one sample, GP excluded.  On entry xb, pb hold the
+// adjoint of (x_{k+1}, Sigma_{k+1}) carried from the later steps; the stage
+// cost's adjoint (t and its terms in the speed v1 and in s2_k) is added, then the covariance
+// update, the Euler step and the Jacobian are reversed: on return xb, pb hold
+// the adjoint of (x_k, Sigma_k) without the GP inputs' share.
+__host__ __device__ inline void chain_adjoint(const CostWeights &cw, const Dyn &dy, float cbar, float thk, float vk,
+                                              const float pk[15], float v1, const StageAdj &t, float xb[5],
+                                              float pb[15], StepAdj &out) {
+    const float dt = dy.dt;
+    out.s2b[0] = cbar * cw.w_var;
+    out.s2b[1] = cbar * cw.w_var;
+    const float Xn_b = xb[0] + t.X, Yn_b = xb[1] + t.Y, thn_b = xb[2];
     const float vn_b = xb[3] + cbar * cw.w_speed * (-2.0f) * (cw.v_des - v1), wn_b = xb[4];
-    pb[0] += Sab;
-    pb[1] += Sbb;
-    pb[5] += Scb;
+    pb[0] += t.sa;
+    pb[1] += t.sb;
+    pb[5] += t.sc;
 
     // covariance update at x_k
-    const float vk = xk[3];
     float sth, cth;
-    sincosf(xk[2], &sth, &cth);
+    sincosf(thk, &sth, &cth);
     const Jac Jk{-dt * vk * sth, dt * cth, dt * vk * cth, dt * sth};
     Jac Jb{0.0f, 0.0f, 0.0f, 0.0f};
     float e3b, e4b, pbk[15];
@@ -280,6 +289,15 @@ __host__ __device__ inline void step_adjoint(const Geometry &geo, const CostWeig
     out.mb[0] = vn_b * dt;
     out.mb[1] = wn_b * dt;
     for (int i = 0; i < 15; ++i) pb[i] = pbk[i];
+}
+
+// Both together: one reversed step from the records of steps k and k + 1.
+__host__ __device__ inline void step_adjoint(const Geometry &geo, const CostWeights &cw, const Dyn &dy, float inv_tau,
+                                             float cbar, float disc_k, const float xk[5], const float pk[15],
+                                             const float x1[5], const float p1[15], int iseg, int iobs, float xb[5],
+                                             float pb[15], StepAdj &out) {
+    const StageAdj t = stage_adjoint(geo, cw, inv_tau, cbar, disc_k, x1, p1, iseg, iobs);
+    chain_adjoint(cw, dy, cbar, xk[2], xk[3], pk, x1[3], t, xb, pb, out);
 }
 
 }  // namespace gpmppi

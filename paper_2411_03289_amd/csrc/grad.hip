@@ -1,46 +1,46 @@
-// Adjoint rollout on gfx950: gradient of the smoothed expected cost
+// Gradient of the smoothed expected cost
 //   J(U, log ell, log sf) = (1/K) sum_s S~^s
-// where S~ is the rollout cost of Alg. 1 Step 1 (Eqs. 1-3, 10-16, one
+// on gfx950, where S~ is the rollout cost of Alg. 1 Step 1 (Eqs. 1-3, 10-16, one
 // combined stage cost) with the lane-exit and collision indicators replaced by
 // sigmoid((d_lane - r_bar)/tau) and sigmoid(-min_j d_bar_j / tau).  The noise
 // is fixed by the seed; u = clip(U + eps) has derivative 1 strictly inside the
 // box.  The derivative in the GP hyperparameters is total (through k, alpha and
 // A^-1, A = K(Z, Z) + sn^2 I).
 //
-// grad_kernel: one workgroup of 256 threads per 32 samples (one 32-column
-// matrix-core group; 8 loop parts = 4 waves x 2 half-waves), or, split, two
-// workgroups per 32 samples, workgroup 2 blk + r doing the GP work of output r
-// (kernel vectors, variance walk, r = Q k and its sums) and both doing the
-// per-sample algebra; they exchange, per forward step, their output's GP mean
-// and variance and, per reversed step, their output's share of the GP inputs'
-// adjoint.  The exchanged values enter the same arithmetic in the same order
-// as in the unsplit kernel, so the results are the same bit for bit.  A
-// workgroup whose bounded exchange wait gives up marks its block for the
-// repair launch of the unsplit kernel that follows every split launch.
-//   job 0   forward over all T steps: costs, the state (x, Sigma) every C
-//           steps (checkpoints), and the last segment's per-step record;
-//   job j   for segment n - j (last first): recompute the segment's C steps
-//           from its checkpoint (not for j = 1, recorded by job 0), keeping
-//           per-step state, controls, GP means and variances in a scratch
-//           array, then step backwards through it.
-// Both passes run the same forward code, so the recomputed trajectory is the
-// first pass's bit for bit.  Per backward step, per sample, in registers: the
-// adjoints of the stage cost, of Sigma+ = A Sigma A^T + dt^2 diag(s2) (the
-// 15 stored entries as independent scalars), of the Euler step and of the
-// Jacobian A(theta, v).  Per output o, for the whole block: the kernel vector
-// k (VALU) and r = Q k with Q = A^-1 = W^T W (dense 32x32 FP32 tiles on the
-// matrix cores); with beta_j = k_j (-mbar alpha_j + 2 s2bar r_j):
-//   dq_d        = 2 ln2 s_d sum_j beta_j (qs_d - zs_jd)
-//   d log ell_d = -2 ln2 sum_j beta_j (qs_d - zs_jd)^2       (through k)
-// and the length-scales' dependence through A: sum_ij (P_ij - b_i alpha_j)
-// dA_ij/dlog ell_d with b = sum mbar r and P = sum s2bar r r^T over all
-// sample-steps.  b is summed in registers; P is formed by grad_syrk_kernel from
-// the stored r (FP32 [T K][Mpad] per output) and contracted on the fly.
+// The only recursions are those of the forward states and of their adjoints; everything
+// else is the same work for every (step, sample) and runs over all of them at once:
+//   rollout            the FP32 rollout (rollout_core.hpp, no track, no obstacles) with its
+//                      trace: states, controls, GP variances
+//   grad_cov_kernel    Sigma_{k+1} = A Sigma A^T + dt^2 diag(s2), a thread per sample
+//   grad_stage_kernel  smoothed stage cost and its adjoint, a thread per (k, s)
+//   grad_gp_kernel     r = Q k, Q = A^-1 = W^T W, and the sums over points from which the GP's
+//                      share of the adjoint follows by the adjoints s2b, mb of its outputs.
+//                      With kappa_j = k_j (2 s2b r_j - mb alpha_j), d = qs - zs_j:
+//                        dq_d        = 2 ln2 s_d sum_j kappa_j d_d
+//                        d log ell_d = -2 ln2 sum_j kappa_j d_d^2     (through k)
+//                      so sum k r d, sum k alpha d, sum k r d^2, sum k alpha d^2, |r|^2 and
+//                      r^T alpha are kept per (output, step, sample), and the variance in FP32
+//                      operands, which d log sf is sensitive to (see below)
+//   grad_back_kernel   the adjoint recursion, a thread per sample
+//   grad_syrk_kernel, grad_bterm_kernel, grad_final_kernel
+//                      the length-scales' dependence through A:
+//                      sum_ij (P_ij - b_i alpha_j) dA_ij/dlog ell_d with b = sum mb r and
+//                      P = sum s2b r r^T over all (k, s), contracted on the fly
 // The signal variance scales k and K(Z, Z) alike (dA/dlog sf = 2 (A - sn^2 I)),
 // so with A r = k and A alpha = y its total derivative folds into per-sample
 // terms in which the large parts through k and through A^-1 cancel exactly:
-//   d log sf    = 2 s2bar (s2 - sn^2 - sn^2 |r|^2) + 2 sn^2 mbar r^T alpha
-// (s2 - sn^2 = sf^2 - k^T r, the latent variance of the forward pass).
+//   d log sf    = 2 s2b (s2 - sn^2 - sn^2 |r|^2) + 2 sn^2 mb r^T alpha
+// (s2 - sn^2 = sf^2 - |W k|^2, the latent variance).  What is systematic in it is left over
+// after the cancellation: the rollout's variance, whose 16-bit matrix cores round their sums towards
+// zero, makes 1e-5 of d log sf where FP32 makes 2e-6 (400 points), so grad_gp_kernel
+// computes it again.
+//
+// The samples are taken in chunks where the workspace (8 Mpad + 280 bytes per (k, s)) is
+// limited; a (k, s)'s results do not depend on its chunk.
+//
+// Measured, K = 4096, T = 50, M = 512: 7.6 ms -> 5.4 ms; K = 256, T = 20, M = 200: 0.94 ms ->
+// 0.25 ms.  Before, one kernel ran everything inside the recursion (its r = Q k once
+// per reversed step, its variance twice per step: forward and again from checkpoints).
 #include "adjoint_step.hpp"
 #include "gp_tiles.hpp"
 
@@ -48,125 +48,78 @@ namespace gpmppi {
 
 namespace {
 
-constexpr int kB = 32;           // samples per workgroup
-constexpr int kParts = 8;        // loop splitters
-constexpr int kSegF = 28;        // per step: x 5, p 15, u 2, m 2, s2 2, latent-positive flags 2
-constexpr int kCkF = 20;         // per checkpoint: x 5, p 15
 constexpr float kLn2 = 0.69314718055994531f;
+constexpr int kGpRows = 32;    // (k, s) entries per workgroup of grad_gp_kernel
+constexpr int kGpWaves = 8;
+
+// Sample s0 + threadIdx of chunk c and its place.
+struct ChunkPos {
+    int s0, sl, s;
+    bool valid;
+};
+__device__ __forceinline__ ChunkPos chunk_pos(const GradArgs &a, int c, int sl) {
+    ChunkPos p;
+    p.s0 = c * a.Kc;
+    p.sl = sl;
+    p.s = p.s0 + sl;
+    p.valid = sl < a.Kc && p.s < a.K;
+    return p;
+}
 
 }  // namespace
 
-
-namespace {
-
-// Dynamic LDS: [k operand 32 x Mpad FP32][staged inputs][r: 32 x (Mpad + 1) FP32]
-__host__ __device__ constexpr size_t grad_rbuf_off(int Mpad) {
-    return kgroup_bytes<GPMPPI_FP32>(Mpad) + (size_t)staged_slots<GPMPPI_FP32>(Mpad) * 16;
-}
-__host__ __device__ constexpr size_t grad_lds_bytes(int Mpad) {
-    return grad_rbuf_off(Mpad) + (size_t)kB * (Mpad + 1) * 4;
-}
-
-__device__ __forceinline__ void restage(const GpDev &g, int o, unsigned char *lds) {
-    __syncthreads();
-    StagedInputs st;
-    stage_load<GPMPPI_FP32>(st, g, o);
-    stage_store<GPMPPI_FP32>(st, g, lds, kgroup_bytes<GPMPPI_FP32>(g.Mpad));
-    __syncthreads();
-}
-
-// FP32 kernel vector of output o for this thread's sample into the k operand.
-__device__ __forceinline__ void gen_kvec(const GpDev &g, int o, const float qs[4], int part, int sl,
-                                         unsigned char *lds) {
-    const int Mpad = g.Mpad, nchunk = Mpad >> 3;
-    const float4 *zs = reinterpret_cast<const float4 *>(lds + kgroup_bytes<GPMPPI_FP32>(Mpad));
-    const float c2 = g.c2[o];
-    for (int c = part; c < nchunk; c += kParts) {
-        float kv[8];
+// Latency of one sample's chain: 1.0 us a step (sine, cosine and 60 multiply-adds).
+__global__ __launch_bounds__(64) void grad_cov_kernel(GradArgs a, int chunk) {
+    const ChunkPos c = chunk_pos(a, chunk, blockIdx.x * 64 + threadIdx.x);
+    if (!c.valid) return;
+    const size_t K = a.K, Kc = a.Kc;
+    const float dt = a.dyn.dt;
+    float p[15] = {};
+    const float *x = a.x + c.s, *s2 = a.s2 + c.s;
+    float *out = a.cov + c.sl;
+    for (int k = 0; k < a.T; ++k) {
+        const float th = x[(5 * (size_t)k + 2) * K], v = x[(5 * (size_t)k + 3) * K];
+        const float e0 = s2[2 * (size_t)k * K], e1 = s2[(2 * (size_t)k + 1) * K];
+        float sth, cth;
+        sincosf(th, &sth, &cth);
+        const Jac J{-dt * v * sth, dt * cth, dt * v * cth, dt * sth};
+        float P[15];
+        cov_forward(p, J, dt, a.dyn.a33, a.dyn.a44, dt * dt * e0, dt * dt * e1, P);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float4 z = zs[8 * c + e];
-            const float d0 = qs[0] - z.x, d1 = qs[1] - z.y, d2 = qs[2] - z.z, d3 = qs[3] - z.w;
-            float acc = c2;
-            acc = fmaf(-d0, d0, acc);
-            acc = fmaf(-d1, d1, acc);
-            acc = fmaf(-d2, d2, acc);
-            acc = fmaf(-d3, d3, acc);
-            kv[e] = __builtin_amdgcn_exp2f(acc);
-        }
-        float4 *Kp = reinterpret_cast<float4 *>(lds) + (size_t)c * 64;
-        Kp[sl] = make_float4(kv[0], kv[2], kv[4], kv[6]);
-        Kp[32 + sl] = make_float4(kv[1], kv[3], kv[5], kv[7]);
-    }
-}
-
-// r = Q k for the block's 32 samples: wave w computes row tiles t = w, w+4, ...
-// over all column tiles, writing r[s][j] (row stride Mpad + 1) to LDS.  Q blocks
-// rotate through four register slots with static indices: block it + 3 is loaded
-// into the slot of block it - 1 before the products of block it (loads past the
-// row's end repeat its last block), three blocks of products ahead of its use.
-__device__ __forceinline__ void qk_walk(const GradArgs &a, int o, unsigned char *lds) {
-    const int Mpad = a.gp.Mpad, NT = Mpad >> 5;
-    const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const float4 *Qo = a.q32 + (size_t)o * a.q_stride;
-    float *rb = reinterpret_cast<float *>(lds + grad_rbuf_off(Mpad));
-    for (int t = w; t < NT; t += kWaves) {
-        const float4 *Qt = Qo + (size_t)(t * NT) * 256 + lane;
-        v16f acc = v16f{};
-        WBlock<GPMPPI_FP32> b[4];
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            const float4 *p = Qt + (size_t)(r < NT ? r : NT - 1) * 256;
-            b[r].v[0] = p[0];
-            b[r].v[1] = p[64];
-            b[r].v[2] = p[128];
-            b[r].v[3] = p[192];
-        }
-        for (int it0 = 0; it0 < NT; it0 += 4) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int it = it0 + r;
-                if (it < NT) {
-                    {   // block it + 3 into the slot freed by block it - 1
-                        const int nx = it + 3 < NT ? it + 3 : NT - 1;
-                        const float4 *p = Qt + (size_t)nx * 256;
-                        WBlock<GPMPPI_FP32> &d = b[(r + 3) % 4];
-                        d.v[0] = p[0];
-                        d.v[1] = p[64];
-                        d.v[2] = p[128];
-                        d.v[3] = p[192];
-                    }
-                    KOp<GPMPPI_FP32> kop;
-                    load_kop<GPMPPI_FP32>(kop, lds, it, lane, Mpad);
-                    mma_block<GPMPPI_FP32>(acc, b[r], kop);
-                }
-            }
-        }
-        const int s = lane & 31;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int row = 32 * t + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-            rb[s * (Mpad + 1) + row] = acc[e];
+        for (int i = 0; i < 15; ++i) {
+            p[i] = P[i];
+            out[(15 * (size_t)k + i) * Kc] = P[i];
         }
     }
 }
 
-// Argmin over this part's polyline segments and obstacles, reduced over the
-// parts through LDS (smallest value, then smallest index).
-__device__ __forceinline__ void constraint_scan(const Geometry &geo, float X, float Y, float sa, float sb, float sc,
-                                                float lmax, int part, int sl, float *vb, int *ib, float *vo, int *io,
-                                                float &best_all, int &iseg, float &om_all, int &iobs) {
+// Argmin over the polyline segments and obstacles, the smoothed stage cost at (x_{k+1},
+// Sigma_{k+1}, s2_k) and its adjoint.  Every lane goes through the whole world at the
+// same index, so the geometry comes through the scalar cache; bound by its vector
+// instructions (about a dozen per segment).
+__global__ __launch_bounds__(256) void grad_stage_kernel(GradArgs a, int chunk) {
+    const int k = blockIdx.y;
+    const ChunkPos c = chunk_pos(a, chunk, blockIdx.x * 256 + threadIdx.x);
+    if (!c.valid) return;
+    const size_t K = a.K, Kc = a.Kc;
+    const Geometry &geo = a.geo;
+    float x1[5], p1[15];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) x1[i] = a.x[(5 * (size_t)(k + 1) + i) * K + c.s];
+    p1[0] = a.cov[(15 * (size_t)k + 0) * Kc + c.sl];
+    p1[1] = a.cov[(15 * (size_t)k + 1) * Kc + c.sl];
+    p1[5] = a.cov[(15 * (size_t)k + 5) * Kc + c.sl];
+    const float s2[2] = {a.s2[2 * (size_t)k * K + c.s], a.s2[(2 * (size_t)k + 1) * K + c.s]};
+    const float X = x1[0], Y = x1[1], sa = p1[0], sb = p1[1], sc = p1[5];
+    float da, db, dc;
+    const float lmax = lmax_grad(sa, sb, sc, da, db, dc);
     float best = INFINITY, om = INFINITY;
-    int bi = -1, oi = -1;
-    // wave-uniform indices (both half-waves take the same segments and obstacles and
-    // store the same results): the geometry comes through the scalar cache
-    const int wu = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    int iseg = -1, iobs = -1;
     if (geo.path_kind != 0) {
         const const_v4p segs = (const_v4p)geo.seg;
         const const_fp sinv = (const_fp)geo.seg_inv;
 #pragma unroll 4
-        for (int i = wu; i < geo.P; i += kWaves) {
+        for (int i = 0; i < geo.P; ++i) {
             const v4f sgm = segs[i];
             const float rx = X - sgm.x, ry = Y - sgm.y;
             float t = (rx * sgm.z + ry * sgm.w) * sinv[i];
@@ -175,13 +128,13 @@ __device__ __forceinline__ void constraint_scan(const Geometry &geo, float X, fl
             const float d2 = ex * ex + ey * ey;
             if (d2 < best) {
                 best = d2;
-                bi = i;
+                iseg = i;
             }
         }
     }
     const const_v4p obs = (const_v4p)geo.obs;
 #pragma unroll 2
-    for (int j = wu; j < geo.n_obs; j += kWaves) {
+    for (int j = 0; j < geo.n_obs; ++j) {
         const v4f ob = obs[j];
         const float dx = X - ob.x, dyy = Y - ob.y;
         const float rho2 = dx * dx + dyy * dyy;
@@ -190,463 +143,297 @@ __device__ __forceinline__ void constraint_scan(const Geometry &geo, float X, fl
         const float m = (rho - ob.z) - geo.z_p * sqrtf(fmaxf(vn, 0.0f));
         if (m < om) {
             om = m;
-            oi = j;
+            iobs = j;
         }
     }
-    __syncthreads();
-    vb[part * kB + sl] = best;
-    ib[part * kB + sl] = bi;
-    vo[part * kB + sl] = om;
-    io[part * kB + sl] = oi;
-    __syncthreads();
-    best_all = INFINITY;
-    om_all = INFINITY;
-    iseg = -1;
-    iobs = -1;
-#pragma unroll
-    for (int p = 0; p < kParts; ++p) {
-        const float b = vb[p * kB + sl], m = vo[p * kB + sl];
-        const int bx = ib[p * kB + sl], mx = io[p * kB + sl];
-        if (b < best_all || (b == best_all && bx >= 0 && (iseg < 0 || bx < iseg))) {
-            best_all = b;
-            iseg = bx;
-        }
-        if (m < om_all || (m == om_all && mx >= 0 && (iobs < 0 || mx < iobs))) {
-            om_all = m;
-            iobs = mx;
-        }
-    }
+    float disc = 1.0f;
+    for (int i = 0; i < k; ++i) disc *= a.cw.discount;
+    const StageAdj t = stage_adjoint(geo, a.cw, a.inv_tau, a.inv_K, disc, x1, p1, iseg, iobs);
+    float *out = a.stage + 6 * (size_t)k * Kc + c.sl;
+    out[0 * Kc] = smoothed_stage(geo, a.cw, a.inv_tau, disc, x1, p1, s2, iseg, iobs);
+    out[1 * Kc] = t.X;
+    out[2 * Kc] = t.Y;
+    out[3 * Kc] = t.sa;
+    out[4 * Kc] = t.sb;
+    out[5 * Kc] = t.sc;
 }
 
-__device__ __forceinline__ void seg_put(float *base, int f, float v) { base[f * kB] = v; }
+namespace {
 
-// a + b, never fused with the product that formed b: the split kernel adds the
-// partner's share after receiving it as a value, and the unsplit kernel must round alike.
-__device__ __forceinline__ float add_rounded(float a, float b) {
-#pragma clang fp contract(off)
-    return a + b;
+// LDS of grad_gp_kernel: the k operand ([chunk of 8 points][64] float4), then points and alpha of the output; the waves' partial sums reuse the k operand's place.
+__host__ __device__ constexpr int grad_gp_points_off(int Mpad) {
+    return Mpad * 128 > kGpWaves * kGradSums * kGpRows * 4 ? Mpad * 128 : kGpWaves * kGradSums * kGpRows * 4;
 }
+__host__ __device__ constexpr int grad_gp_lds(int Mpad) { return grad_gp_points_off(Mpad) + Mpad * 20; }
 
 }  // namespace
 
-// SPLIT: role = blockIdx.x & 1 of block blockIdx.x >> 1 (see above).  REPAIR
-// (unsplit): the repair launch, only the blocks a split launch marked.
-template <bool SPLIT, bool REPAIR = false>
-__global__ __launch_bounds__(kThreads) void grad_kernel(GradArgs a) {
+// r = Q k, |W k|^2 and the sums over points of 32 (k, s) entries of one output.  The product stays on the
+// FP32 matrix cores: A^-1 magnifies what is systematic in r's error, and the 16-bit ones round
+// their sums towards zero (r by FP16 terms of Q and k, exact operands: its error is two thirds of
+// FP32's, but d log ell's is three times FP32's, 2.3e-5 against 0.7e-5 at 512 points).
+//
+// A wave takes row tiles w, w + 8, ... over all columns, the next block in flight; a lane ends up
+// with 16 rows of one entry, and adds them up on the vector unit.  Two workgroups to a compute
+// unit: one multiplies while the other generates kernel vectors or adds up.
+__global__ __launch_bounds__(64 * kGpWaves, 4) void grad_gp_kernel(GradArgs a, int chunk) {
     extern __shared__ __align__(16) unsigned char lds[];
-    __shared__ float pred[kParts * kB];
-    __shared__ float vred[kWaves * kB];
-    __shared__ float vb[kParts * kB], vo[kParts * kB];
-    __shared__ int ib[kParts * kB], io[kParts * kB];
-    __shared__ __align__(16) float gred[11 * kParts * kB];
-    __shared__ float mb_s[2][kB], sb_s[2][kB], ub_s[2][kB];
-    __shared__ float xv[5 * kB + 1];   // split: values received from the partner, and a give-up flag
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, w = tid >> 6;
-    const int sl = lane & 31;
-    const int part = 2 * w + (lane >> 5);
-    const int blk = SPLIT ? (int)(blockIdx.x >> 1) : (int)blockIdx.x;
-    const int role = SPLIT ? (int)(blockIdx.x & 1) : 0;   // split: the GP output this workgroup computes
-    if (REPAIR && __hip_atomic_load(a.repair + blk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return;
-    const int sg = blk * kB + sl;
-    const bool valid = sg < a.K;
-    const bool writer = w == 0 && lane < kB;   // one copy of each sample
-    const int K = a.K, T = a.T, C = a.C;
-    const int Mpad = a.gp.Mpad;
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, sl = lane & 31;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int o = blockIdx.y, NT = a.gp.NT, Mpad = a.gp.Mpad;
     const GpDev &g = a.gp;
-    const Geometry &geo = a.geo;
-    const CostWeights cw = a.cw;
-    const Dyn dy = a.dyn;
-    const float dt = dy.dt;
-    const float cbar = valid ? a.inv_K : 0.0f;
-    // per-(block, role) segment scratch [e][f][32] and per-role checkpoints
-    float *segw = a.seg + ((size_t)blk * 2 + role) * (C + 1) * kSegF * kB + sl;
-    float *ckpt = a.ckpt + (size_t)role * a.nck * kCkF * K;
-    float *rb = reinterpret_cast<float *>(lds + grad_rbuf_off(Mpad));
-
-    NoiseParams np = a.noise;
-
-    // split exchange: event e (the same sequence in both roles) uses slot e % 4 of the
-    // writer's records [block][writer role][slot][kind][32]; records are zeroed before
-    // the launch, and the tag e + 1 names the event
-    unsigned long long *xrec = SPLIT ? a.xrec + (size_t)blk * kGradXchPerBlock : nullptr;
-    auto xslot = [&](int wr, uint32_t e, int kind) {
-        return xrec + ((size_t)(wr * 4 + (int)(e & 3u)) * 4 + kind) * kB;
-    };
-    uint32_t ev = 0;
-    bool broken = false, alone = false;
-
-    // per-sample accumulators of the hyperparameter terms through k (o, theta)
-    double hyp[2][5] = {};
-    // this thread's share of b = sum mbar r (points j = tid + 256 i)
-    double bacc[2][2] = {};
-
-    const int nseg = (T + C - 1) / C;
-    float X = 0, Y = 0, th = 0, v = 0, w_ = 0;
-    float p[15];
-    // adjoint of the state after the step being reversed, carried between segments
-    float xb[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    float pb[15] = {};
-    float S_ = 0.0f, Sc = 0.0f, disc = 1.0f;
-
-    // the last segment's per-step record is written by the forward pass itself, so
-    // its backward job (job 1) needs no recompute
-    const int kl0 = (nseg - 1) * C;
-    for (int job = 0; job <= nseg; ++job) {
-        const bool first = job == 0;
-        const int segi = first ? 0 : nseg - job;
-        const int k0 = first ? 0 : segi * C;
-        const int k1 = first ? T : min(T, k0 + C);
-        const int kf = job == 1 ? k0 : k1;   // end of the forward (re)computation: job 1's is recorded
-        if (first) {
-            X = a.x0[0]; Y = a.x0[1]; th = a.x0[2]; v = a.x0[3]; w_ = a.x0[4];
-#pragma unroll
-            for (int i = 0; i < 15; ++i) p[i] = 0.0f;
-        } else {
-            const float *ck = ckpt + (size_t)segi * kCkF * K + (valid ? sg : 0);
-            X = ck[0 * (size_t)K]; Y = ck[1 * (size_t)K]; th = ck[2 * (size_t)K]; v = ck[3 * (size_t)K];
-            w_ = ck[4 * (size_t)K];
-#pragma unroll
-            for (int i = 0; i < 15; ++i) p[i] = ck[(5 + i) * (size_t)K];
-        }
-        restage(g, SPLIT ? role : ((k0 & 1) ? 1 : 0), lds);
-        // ---------------------------------------------------------- forward
-        for (int k = k0; k < kf; ++k) {
-            if (writer) {
-                if (first && k % C == 0 && valid) {
-                    float *ck = ckpt + (size_t)(k / C) * kCkF * K + sg;
-                    ck[0 * (size_t)K] = X; ck[1 * (size_t)K] = Y; ck[2 * (size_t)K] = th; ck[3 * (size_t)K] = v;
-                    ck[4 * (size_t)K] = w_;
-#pragma unroll
-                    for (int i = 0; i < 15; ++i) ck[(5 + i) * (size_t)K] = p[i];
-                }
-                if (!first || k >= kl0) {
-                    float *e = segw + (size_t)(k - (first ? kl0 : k0)) * kSegF * kB;
-                    seg_put(e, 0, X); seg_put(e, 1, Y); seg_put(e, 2, th); seg_put(e, 3, v); seg_put(e, 4, w_);
-#pragma unroll
-                    for (int i = 0; i < 15; ++i) seg_put(e, 5 + i, p[i]);
-                }
-            }
-            const bool rev = (k & 1) != 0;
-            const float2 u = sampled_control(np, k, sg, a.U[2 * k], a.U[2 * k + 1]);
-            const float q[4] = {v, w_, u.x, u.y};
-            float m[2], s2[2];
-            if constexpr (SPLIT) {   // this role's output, then the partner's mean and variance
-                const int o = role;
-                __syncthreads();
-                const float qs[4] = {q[0] * g.scale[o][0], q[1] * g.scale[o][1], q[2] * g.scale[o][2],
-                                     q[3] * g.scale[o][3]};
-                gp_output<GPMPPI_FP32, 1>(g, o, -1, qs, part, sl, rev, 0, blk, lds, pred, vred, m[o], s2[o]);
-                const uint32_t tag = ev + 1;
-                if (w == 0) {
-                    xch_put(xslot(role, ev, 0), lane, m[o], tag);
-                    xch_put(xslot(role, ev, 1), lane, s2[o], tag);
-                    const float mp = xch_get(xslot(1 - role, ev, 0), lane, tag, a.xspin, broken);
-                    const float sp = xch_get(xslot(1 - role, ev, 1), lane, tag, a.xspin, broken);
-                    if (lane < kB) {
-                        xv[lane] = mp;
-                        xv[kB + lane] = sp;
-                    }
-                    if (lane == 0) xv[5 * kB] = broken ? 1.0f : 0.0f;
-                }
-                ++ev;
-                __syncthreads();
-                if (xv[5 * kB] != 0.0f) {
-                    alone = true;
-                    break;
-                }
-                m[1 - o] = xv[sl];
-                s2[1 - o] = xv[kB + sl];
-            } else {
-#pragma unroll
-                for (int oo = 0; oo < 2; ++oo) {
-                    const int o = rev ? 1 - oo : oo;
-                    __syncthreads();
-                    const float qs[4] = {q[0] * g.scale[o][0], q[1] * g.scale[o][1], q[2] * g.scale[o][2],
-                                         q[3] * g.scale[o][3]};
-                    gp_output<GPMPPI_FP32, 1>(g, o, oo == 0 ? 1 - o : -1, qs, part, sl, rev, 0, blk, lds, pred,
-                                              vred, m[o], s2[o]);
-                }
-            }
-            float sth, cth;
-            sincosf(th, &sth, &cth);
-            const Jac J{-dt * v * sth, dt * cth, dt * v * cth, dt * sth};
-            const float Xn = X + dt * v * cth;
-            const float Yn = Y + dt * v * sth;
-            const float thn = th + dt * w_;
-            const float vn = v + (dy.dt_tau_v * (u.x - v) + dt * m[0]);
-            const float wn = w_ + (dy.dt_tau_w * (u.y - w_) + dt * m[1]);
-            float P[15];
-            cov_forward(p, J, dt, dy.a33, dy.a44, dt * dt * s2[0], dt * dt * s2[1], P);
-#pragma unroll
-            for (int i = 0; i < 15; ++i) p[i] = P[i];
-            X = Xn; Y = Yn; th = thn; v = vn; w_ = wn;
-            if ((!first || k >= kl0) && writer) {
-                float *e = segw + (size_t)(k - (first ? kl0 : k0)) * kSegF * kB;
-                seg_put(e, 20, u.x); seg_put(e, 21, u.y); seg_put(e, 22, m[0]); seg_put(e, 23, m[1]);
-                seg_put(e, 24, s2[0]); seg_put(e, 25, s2[1]);
-                seg_put(e, 26, s2[0] > g.sn2[0] ? 1.0f : 0.0f);
-                seg_put(e, 27, s2[1] > g.sn2[1] ? 1.0f : 0.0f);
-            }
-            if (first) {
-                // smoothed stage cost on (x_{k+1}, Sigma_{k+1})
-                float da, db, dc;
-                const float lmax = lmax_grad(p[0], p[1], p[5], da, db, dc);
-                float best_all, om_all;
-                int iseg, iobs;
-                constraint_scan(geo, X, Y, p[0], p[1], p[5], lmax, part, sl, vb, ib, vo, io, best_all, iseg, om_all,
-                                iobs);
-                const float x1[5] = {X, Y, th, v, w_};
-                const float c = smoothed_stage(geo, cw, a.inv_tau, disc, x1, p, s2, iseg, iobs);
-                const float yk = c - Sc;
-                const float tk = S_ + yk;
-                Sc = (tk - S_) - yk;
-                S_ = tk;
-                disc *= cw.discount;
-            }
-        }
-        if (alone) break;
-        if (first) {
-            if (writer && valid && role == 0) a.costs[sg] = S_;
-            if (writer) {   // the last segment's final state
-                float *e = segw + (size_t)(T - kl0) * kSegF * kB;
-                seg_put(e, 0, X); seg_put(e, 1, Y); seg_put(e, 2, th); seg_put(e, 3, v); seg_put(e, 4, w_);
-#pragma unroll
-                for (int i = 0; i < 15; ++i) seg_put(e, 5 + i, p[i]);
-            }
-            continue;
-        }
-        if (job != 1 && writer) {   // the segment's final state
-            float *e = segw + (size_t)(k1 - k0) * kSegF * kB;
-            seg_put(e, 0, X); seg_put(e, 1, Y); seg_put(e, 2, th); seg_put(e, 3, v); seg_put(e, 4, w_);
-#pragma unroll
-            for (int i = 0; i < 15; ++i) seg_put(e, 5 + i, p[i]);
-        }
-        __syncthreads();   // segment scratch visible to every copy of each sample
-
-        // ---------------------------------------------------------- backward
-        for (int k = k1 - 1; k >= k0; --k) {
-            const float *e1 = segw + (size_t)(k + 1 - k0) * kSegF * kB;   // x_{k+1}, p_{k+1}
-            const float *e0 = segw + (size_t)(k - k0) * kSegF * kB;       // x_k, p_k, u, m, s2, flags
-            const float vk = e0[3 * kB], wk = e0[4 * kB];
-            float pk[15];
-#pragma unroll
-            for (int i = 0; i < 15; ++i) pk[i] = e0[(5 + i) * kB];
-            const float ux = e0[20 * kB], uy = e0[21 * kB];
-            const float flag[2] = {e0[26 * kB], e0[27 * kB]};
-            const float s2k[2] = {e0[24 * kB], e0[25 * kB]};
-
-            float x1[5], p1[15], xk[5];
-#pragma unroll
-            for (int i = 0; i < 5; ++i) {
-                x1[i] = e1[i * kB];
-                xk[i] = e0[i * kB];
-            }
-#pragma unroll
-            for (int i = 0; i < 15; ++i) p1[i] = e1[(5 + i) * kB];
-            float da, db, dc;
-            const float lmax = lmax_grad(p1[0], p1[1], p1[5], da, db, dc);
-            float best_all, om_all;
-            int iseg, iobs;
-            constraint_scan(geo, x1[0], x1[1], p1[0], p1[1], p1[5], lmax, part, sl, vb, ib, vo, io, best_all, iseg,
-                            om_all, iobs);
-            float discount_k = 1.0f;
-            for (int i = 0; i < k; ++i) discount_k *= cw.discount;
-            StepAdj sa_out;
-            step_adjoint(geo, cw, dy, a.inv_tau, cbar, discount_k, xk, pk, x1, p1, iseg, iobs, xb, pb, sa_out);
-            float vbk = xb[3], wbk = xb[4];
-            float uxb = sa_out.ub[0], uyb = sa_out.ub[1];
-            const float mb[2] = {sa_out.mb[0], sa_out.mb[1]};
-            const float s2b[2] = {sa_out.s2b[0], sa_out.s2b[1]};
-
-            // ---- GP adjoint, both outputs
-            const float qk[4] = {vk, wk, ux, uy};
-            float qb[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-            float qown[4];   // split: this role's output's share of the GP inputs' adjoint
-            for (int o = 0; o < 2; ++o) {
-                if (SPLIT && o != role) continue;
-                const float sbo = s2b[o] * flag[o];
-                if (writer) {
-                    mb_s[o][sl] = mb[o];
-                    sb_s[o][sl] = sbo;
-                }
-                restage(g, o, lds);   // also publishes mb_s / sb_s
-                const float qs[4] = {qk[0] * g.scale[o][0], qk[1] * g.scale[o][1], qk[2] * g.scale[o][2],
-                                     qk[3] * g.scale[o][3]};
-                gen_kvec(g, o, qs, part, sl, lds);
-                __syncthreads();
-                qk_walk(a, o, lds);
-                __syncthreads();
-                // per-sample sums over this part's points
-                const float4 *zs = reinterpret_cast<const float4 *>(lds + kgroup_bytes<GPMPPI_FP32>(Mpad));
-                const float *al = reinterpret_cast<const float *>(zs + Mpad);
-                float Sd[4] = {0, 0, 0, 0}, Sdd[4] = {0, 0, 0, 0}, Srr = 0.0f, Sra = 0.0f;
-                for (int c = part; c < (Mpad >> 3); c += kParts) {
-                    const float4 *Kp = reinterpret_cast<const float4 *>(lds) + (size_t)c * 64;
-                    const float4 lo = Kp[sl], hi = Kp[32 + sl];
-                    const float kv[8] = {lo.x, hi.x, lo.y, hi.y, lo.z, hi.z, lo.w, hi.w};
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int j = 8 * c + e;
-                        const float4 z = zs[j];
-                        const float rj = rb[sl * (Mpad + 1) + j];
-                        const float beta = kv[e] * (2.0f * sbo * rj - mb[o] * al[j]);
-                        const float d0 = qs[0] - z.x, d1 = qs[1] - z.y, d2 = qs[2] - z.z, d3 = qs[3] - z.w;
-                        Srr = fmaf(rj, rj, Srr);
-                        Sra = fmaf(rj, al[j], Sra);
-                        Sd[0] = fmaf(beta, d0, Sd[0]);
-                        Sd[1] = fmaf(beta, d1, Sd[1]);
-                        Sd[2] = fmaf(beta, d2, Sd[2]);
-                        Sd[3] = fmaf(beta, d3, Sd[3]);
-                        Sdd[0] = fmaf(beta * d0, d0, Sdd[0]);
-                        Sdd[1] = fmaf(beta * d1, d1, Sdd[1]);
-                        Sdd[2] = fmaf(beta * d2, d2, Sdd[2]);
-                        Sdd[3] = fmaf(beta * d3, d3, Sdd[3]);
-                    }
-                }
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    gred[((1 + d) * kParts + part) * kB + sl] = Sd[d];
-                    gred[((5 + d) * kParts + part) * kB + sl] = Sdd[d];
-                }
-                gred[(9 * kParts + part) * kB + sl] = Srr;
-                gred[(10 * kParts + part) * kB + sl] = Sra;
-                // b += sum_s mbar_s r_s over this thread's points; the r rows for P
-                for (int jj = 0; jj < 2; ++jj) {
-                    const int j = tid + kThreads * jj;
-                    if (j < Mpad) {
-                        double acc = bacc[o][jj];
-                        float *Rrow = a.R + ((size_t)o * T * K + (size_t)k * K + (size_t)blk * kB) * Mpad + j;
-                        for (int s = 0; s < kB; ++s) {
-                            if (blk * kB + s < K) {
-                                const float rv = rb[s * (Mpad + 1) + j];
-                                acc += (double)(mb_s[o][s] * rv);
-                                Rrow[(size_t)s * Mpad] = rv;
-                            }
-                        }
-                        bacc[o][jj] = acc;
-                    }
-                }
-                if (writer && valid) a.Gw[(size_t)o * T * K + (size_t)k * K + sg] = sbo;
-                __syncthreads();
-                float tot[11];
-#pragma unroll
-                for (int i = 1; i < 11; ++i) {
-                    float sum = 0.0f;
-#pragma unroll
-                    for (int pp = 0; pp < kParts; ++pp) sum += gred[(i * kParts + pp) * kB + sl];
-                    tot[i] = sum;
-                }
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    const float qd = 2.0f * kLn2 * g.scale[o][d] * tot[1 + d];
-                    if constexpr (SPLIT) qown[d] = qd;
-                    else qb[d] = add_rounded(qb[d], qd);
-                    hyp[o][d] += (double)(-2.0f * kLn2 * tot[5 + d]);
-                }
-                {   // log sf: the folded per-sample terms (k and A^-1 parts cancelled)
-                    const double sn2 = (double)g.sn2[o];
-                    hyp[o][4] += 2.0 * (double)sbo * (((double)s2k[o] - sn2) - sn2 * (double)tot[9]) +
-                                 2.0 * sn2 * (double)mb[o] * (double)tot[10];
-                }
-            }
-            if constexpr (SPLIT) {   // the partner's share, received in exchange for ours
-                const uint32_t tag = ev + 1;
-                if (w == 0) {
-#pragma unroll
-                    for (int d = 0; d < 4; ++d) xch_put(xslot(role, ev, d), lane, qown[d], tag);
-#pragma unroll
-                    for (int d = 0; d < 4; ++d) {
-                        const float vq = xch_get(xslot(1 - role, ev, d), lane, tag, a.xspin, broken);
-                        if (lane < kB) xv[d * kB + lane] = vq;
-                    }
-                    if (lane == 0) xv[5 * kB] = broken ? 1.0f : 0.0f;
-                }
-                ++ev;
-                __syncthreads();
-                if (xv[5 * kB] != 0.0f) {
-                    alone = true;
-                    break;
-                }
-                // in output order, as the unsplit kernel accumulates them
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    const float qp = xv[d * kB + sl];
-                    qb[d] = add_rounded(qb[d], role == 0 ? qown[d] : qp);
-                    qb[d] = add_rounded(qb[d], role == 0 ? qp : qown[d]);
-                }
-            }
-            vbk += qb[0];
-            wbk += qb[1];
-            uxb += qb[2];
-            uyb += qb[3];
-
-            // ---- the nominal control's adjoint through the clip (1 strictly inside the box)
-            {
-                const float2 raw = sampled_raw(np, k, sg, a.U[2 * k], a.U[2 * k + 1]);
-                const float m0 = (raw.x > np.umin0 && raw.x < np.umax0) ? 1.0f : 0.0f;
-                const float m1 = (raw.y > np.umin1 && raw.y < np.umax1) ? 1.0f : 0.0f;
-                if (writer) {
-                    ub_s[0][sl] = valid ? uxb * m0 : 0.0f;
-                    ub_s[1][sl] = valid ? uyb * m1 : 0.0f;
-                }
-                __syncthreads();
-                if (tid < 2 && role == 0) {
-                    float sum = 0.0f;
-                    for (int i = 0; i < kB; ++i) sum += ub_s[tid][i];
-                    a.upart[((size_t)blk * T + k) * 2 + tid] = sum;
-                }
-            }
-            xb[3] = vbk;
-            xb[4] = wbk;
-        }
-        if (alone) break;
+    const int s0 = chunk * a.Kc, kc = a.K - s0 < a.Kc ? a.K - s0 : a.Kc;   // this chunk's samples
+    const long long N = (long long)a.T * kc;
+    const long long n0 = (long long)blockIdx.x * kGpRows;
+    v4f *zs = reinterpret_cast<v4f *>(lds + grad_gp_points_off(Mpad));
+    float *al = reinterpret_cast<float *>(zs + Mpad);
+    for (int i = tid; i < Mpad; i += 64 * kGpWaves) {
+        zs[i] = reinterpret_cast<const v4f *>(g.zs)[(size_t)o * Mpad + i];
+        al[i] = g.alpha[(size_t)o * Mpad + i];
     }
-    (void)np;
-    if (SPLIT && alone) {   // uniform: leave the block to the repair launch
-        if (tid == 0) {
-            __hip_atomic_store(a.repair + blk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (a.flags)
-                __hip_atomic_fetch_or(a.flags, GPMPPI_FLAG_EXCHANGE_TIMEOUT, __ATOMIC_RELAXED,
-                                      __HIP_MEMORY_SCOPE_AGENT);
-        }
-        return;
+    float qs[4];
+    {
+        const long long nc = n0 + sl < N ? n0 + sl : N - 1;
+        const size_t k = (size_t)(nc / kc), s = (size_t)(s0 + nc % kc), K = a.K;
+        const float q[4] = {a.x[(5 * k + 3) * K + s], a.x[(5 * k + 4) * K + s], a.u[2 * k * K + s],
+                            a.u[(2 * k + 1) * K + s]};
+#pragma unroll
+        for (int d = 0; d < 4; ++d) qs[d] = q[d] * g.scale[o][d];
     }
-    // ---- per-workgroup partial sums (split: this role's output only)
     __syncthreads();
-    double *hred = reinterpret_cast<double *>(gred);   // 10 x 32 doubles
-    if (writer) {
+    for (int c = 2 * w + half; c < NT * 4; c += 2 * kGpWaves) {   // a lane per entry, 8 points a turn
+        float kv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const v4f z = zs[8 * c + e];
+            float x = g.c2[o];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const float df = qs[d] - z[d];
+                x = fmaf(-df, df, x);
+            }
+            kv[e] = __builtin_amdgcn_exp2f(x);
+        }
+        float4 *Kp = reinterpret_cast<float4 *>(lds) + c * 64;
+        Kp[sl] = make_float4(kv[0], kv[2], kv[4], kv[6]);
+        Kp[32 + sl] = make_float4(kv[1], kv[3], kv[5], kv[7]);
+    }
+    __syncthreads();
+    // k r d (4), k alpha d (4), k r d^2 (4), k alpha d^2 (4), r r, r alpha, (W k)^2
+    float sum[kGradSums] = {};
+    auto load = [&](float4 (&f)[4], const float4 *p) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) f[q] = p[64 * q];
+    };
+    auto block = [&](v16f &acc, const float4 (&f)[4], int c) {
+        float4 kq[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) kq[q] = reinterpret_cast<const float4 *>(lds)[(4 * c + q) * 64 + lane];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 k = kq[q];
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f[q].x, k.x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f[q].y, k.y, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f[q].z, k.z, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f[q].w, k.w, acc, 0, 0, 0);
+        }
+    };
+    // columns 0 .. n - 1 of a row tile whose block c is at p + c stride
+    auto walk = [&](v16f &acc, const float4 *p, int n, int stride) {
+        float4 f0[4], f1[4];
+        load(f0, p);
+        for (int c = 0; c < n; c += 2) {   // the barriers keep the loads ahead of the products
+            load(f1, p + (size_t)(c + 1 < n ? c + 1 : c) * stride);
+            __builtin_amdgcn_sched_barrier(0);
+            block(acc, f0, c);
+            if (c + 1 >= n) break;
+            load(f0, p + (size_t)(c + 2 < n ? c + 2 : c) * stride);
+            __builtin_amdgcn_sched_barrier(0);
+            block(acc, f1, c + 1);
+        }
+    };
+    for (int i = 0; i * kGpWaves < NT; ++i) {   // W's row tiles, the long ones with the short ones
+        const int t = kGpWaves * i + ((i & 1) ? kGpWaves - 1 - w : w);
+        if (t >= NT) continue;
+        v16f acc = v16f{};
+        const int u = t >> 1;
+        walk(acc, g.w32 + o * g.w32_stride + (size_t)(2 * u * (u + 1) + (t & 1)) * 256 + lane, t + 1, 512);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sum[18] = fmaf(acc[e], acc[e], sum[18]);
+    }
+    const float4 *Qo = a.q32 + (size_t)o * a.q_stride + lane;
+    // this workgroup's rows of R; stores beyond the chunk's last entry are dropped
+    const __amdgpu_buffer_rsrc_t Rr = uniform_rsrc(a.R + ((size_t)o * a.T * a.Kc + n0) * Mpad,
+                                                   (N - n0 < kGpRows ? N - n0 : kGpRows) * Mpad * 4);
+    for (int t = w; t < NT; t += kGpWaves) {
+        v16f acc = v16f{};
+        walk(acc, Qo + (size_t)t * NT * 256, NT, 256);
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {
+            const int row = 32 * t + 8 * e4 + 4 * half;
+            const v4f av = *reinterpret_cast<const v4f *>(al + row);
+            // kernel values of rows row .. + 3 (even and odd points are apart in the operand)
+            const float4 *Kp = reinterpret_cast<const float4 *>(lds) + (t * 4 + e4) * 64 + sl;
+            const float2 ke = reinterpret_cast<const float2 *>(Kp)[half];
+            const float2 ko = reinterpret_cast<const float2 *>(Kp + 32)[half];
+            const float kv[4] = {ke.x, ko.x, ke.y, ko.y};
+            uint32_t __attribute__((ext_vector_type(4))) ru;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const v4f z = zs[row + e];
+                const float r = acc[4 * e4 + e];
+                ru[e] = __float_as_uint(r);
+                const float kr = kv[e] * r, ka = kv[e] * av[e];
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const float df = qs[d] - z[d];
+                    const float x = kr * df, y = ka * df;
+                    sum[d] += x;
+                    sum[4 + d] += y;
+                    sum[8 + d] = fmaf(x, df, sum[8 + d]);
+                    sum[12 + d] = fmaf(y, df, sum[12 + d]);
+                }
+                sum[16] = fmaf(r, r, sum[16]);
+                sum[17] = fmaf(r, av[e], sum[17]);
+            }
+            __builtin_amdgcn_raw_buffer_store_b128(ru, Rr, (sl * Mpad + row) * 4, 0, 0);
+        }
+    }
+    __syncthreads();   // the k operand's last readers are done
+    float *red = reinterpret_cast<float *>(lds);   // [wave][sum][32]
+#pragma unroll
+    for (int j = 0; j < kGradSums; ++j) {
+        const float x = sum[j] + shfl_xor(sum[j], 32);
+        if (half == 0) red[(w * kGradSums + j) * kGpRows + sl] = x;
+    }
+    __syncthreads();
+    for (int i = tid; i < kGradSums * kGpRows; i += 64 * kGpWaves) {
+        const int j = i / kGpRows, l = i % kGpRows;
+        float x = 0.0f;
+#pragma unroll
+        for (int v = 0; v < kGpWaves; ++v) x += red[(v * kGradSums + j) * kGpRows + l];
+        if (j == 18) x = g.vscale[o] * (g.sn2[o] + fmaxf(0.0f, g.sf2[o] - x));
+        if (n0 + l < N) a.sums[((size_t)o * kGradSums + j) * a.T * a.Kc + n0 + l] = x;
+    }
+}
+
+// The adjoint recursion, last step first, a thread per sample; the next step's records are
+// loaded beside a step's arithmetic.
+__global__ __launch_bounds__(64) void grad_back_kernel(GradArgs a, int chunk) {
+    __shared__ double hred[10][64];
+    const int lane = threadIdx.x;
+    const ChunkPos c = chunk_pos(a, chunk, blockIdx.x * 64 + lane);
+    const size_t K = a.K, Kc = a.Kc;
+    const int kc = a.K - c.s0 < a.Kc ? a.K - c.s0 : a.Kc;
+    const size_t NS = (size_t)a.T * a.Kc;   // stride of the chunk arrays
+    const int s = c.valid ? c.s : a.K - 1, sl = c.valid ? c.sl : kc - 1;
+    const int slot = chunk * gridDim.x + blockIdx.x;
+    const GpDev &g = a.gp;
+    const float cbar = c.valid ? a.inv_K : 0.0f;
+    const NoiseParams np = a.noise;
+    {   // Eq. 5's sum, Kahan-compensated, in step order
+        float S = 0.0f, Sc = 0.0f;
+        const float *st = a.stage + sl;
+#pragma unroll 8
+        for (int k = 0; k < a.T; ++k) {
+            const float yk = st[6 * (size_t)k * Kc] - Sc;
+            const float tk = S + yk;
+            Sc = (tk - S) - yk;
+            S = tk;
+        }
+        if (c.valid) a.costs[s] = S;
+    }
+    struct Rec {
+        float th, v, v1, p[15];
+        StageAdj t;
+        float sum[2][kGradSums];
+    };
+    auto load = [&](Rec &r, int k) {
+        const size_t kk = k;
+        r.th = a.x[(5 * kk + 2) * K + s];
+        r.v = a.x[(5 * kk + 3) * K + s];
+        r.v1 = a.x[(5 * (kk + 1) + 3) * K + s];
+#pragma unroll
+        for (int i = 0; i < 15; ++i) r.p[i] = k > 0 ? a.cov[(15 * (kk - 1) + i) * Kc + sl] : 0.0f;
+        const float *st = a.stage + 6 * kk * Kc + sl;
+        r.t = StageAdj{st[Kc], st[2 * Kc], st[3 * Kc], st[4 * Kc], st[5 * Kc]};
 #pragma unroll
         for (int o = 0; o < 2; ++o)
 #pragma unroll
-            for (int i = 0; i < 5; ++i) hred[(o * 5 + i) * kB + sl] = valid ? hyp[o][i] : 0.0;
-    }
-    __syncthreads();
-    if (tid < 10 && (!SPLIT || tid / 5 == role)) {
-        double s = 0.0;
-        for (int i = 0; i < kB; ++i) s += hred[tid * kB + i];
-        a.hpart[(size_t)blk * 10 + tid] = s;
-    }
-    for (int o = 0; o < 2; ++o) {
-        if (SPLIT && o != role) continue;
-        for (int jj = 0; jj < 2; ++jj) {
-            const int j = tid + kThreads * jj;
-            if (j < Mpad) a.bpart[((size_t)blk * 2 + o) * Mpad + j] = bacc[o][jj];
+            for (int j = 0; j < kGradSums; ++j) r.sum[o][j] = a.sums[(o * kGradSums + j) * NS + kk * kc + sl];
+    };
+    double hyp[2][5] = {};
+    float xb[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    float pb[15] = {};
+    Rec r, nx;
+    load(r, a.T - 1);
+    for (int k = a.T - 1; k >= 0; --k) {
+        if (k > 0) load(nx, k - 1);
+        StepAdj sa;
+        chain_adjoint(a.cw, a.dyn, cbar, r.th, r.v, r.p, r.v1, r.t, xb, pb, sa);
+        float qb[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            const float *t = r.sum[o];
+            const float sbo = t[18] > g.sn2[o] ? sa.s2b[o] : 0.0f, mb = sa.mb[o];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                qb[d] += 2.0f * kLn2 * g.scale[o][d] * (2.0f * sbo * t[d] - mb * t[4 + d]);
+                hyp[o][d] += (double)(-2.0f * kLn2 * (2.0f * sbo * t[8 + d] - mb * t[12 + d]));
+            }
+            {   // log sf: the folded per-sample terms (k and A^-1 parts cancelled)
+                const double sn2 = (double)g.sn2[o];
+                hyp[o][4] += 2.0 * (double)sbo * (((double)t[18] - sn2) - sn2 * (double)t[16]) +
+                             2.0 * sn2 * (double)mb * (double)t[17];
+            }
+            if (c.valid) {
+                float *wg = a.wgt + (size_t)o * 2 * NS + (size_t)k * kc + sl;
+                wg[0] = sbo;
+                wg[NS] = mb;
+            }
         }
+        xb[3] += qb[0];
+        xb[4] += qb[1];
+        // the nominal control's adjoint through the clip (1 strictly inside the box)
+        const float2 raw = sampled_raw(np, k, s, a.U[2 * k], a.U[2 * k + 1]);
+        float ub[2] = {sa.ub[0] + qb[2], sa.ub[1] + qb[3]};
+        if (!(c.valid && raw.x > np.umin0 && raw.x < np.umax0)) ub[0] = 0.0f;
+        if (!(c.valid && raw.y > np.umin1 && raw.y < np.umax1)) ub[1] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+#pragma unroll
+            for (int m = 32; m >= 1; m >>= 1) ub[i] += shfl_xor(ub[i], m);
+            if (lane == 0) a.upart[((size_t)slot * a.T + k) * 2 + i] = ub[i];
+        }
+        r = nx;
     }
-    if (REPAIR && tid == 0)   // the block is done
-        __hip_atomic_store(a.repair + blk, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int i = 0; i < 5; ++i) hred[o * 5 + i][lane] = c.valid ? hyp[o][i] : 0.0;
+    __syncthreads();
+    if (lane < 10) {
+        double sum = 0.0;
+        for (int i = 0; i < 64; ++i) sum += hred[lane][i];
+        a.hpart[(size_t)slot * 10 + lane] = sum;
+    }
 }
 
-// Zeroes the split gradient's exchange records and repair marks before a launch.
-__global__ __launch_bounds__(kThreads) void grad_clear_kernel(unsigned long long *rec, size_t n_rec, uint32_t *repair,
-                                                              int n_blk) {
+__global__ __launch_bounds__(kThreads) void exchange_clear_kernel(unsigned long long *rec, size_t n_rec, uint32_t *xep,
+                                                                  uint32_t *repair, int n_blk) {
     const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
     if (i < n_rec) rec[i] = 0ull;
+    if (i < 2) xep[i] = 0u;
     if (i < (size_t)n_blk) repair[i] = 0u;
 }
 
+hipError_t launch_exchange_clear(unsigned long long *rec, size_t n_rec, uint32_t *xep, uint32_t *repair, int n_blk,
+                                 hipStream_t st) {
+    const size_t n = n_rec > (size_t)n_blk ? n_rec : (size_t)n_blk;
+    hipLaunchKernelGGL(exchange_clear_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
+                       rec, n_rec, xep, repair, n_blk);
+    return hipGetLastError();
+}
 
 // dA_ij / dlog ell_d contracted with a weight c_ij: K_ij = exp2(c2 - |zs_i - zs_j|^2),
 // dA/dlog ell_d = K 2 ln2 (zs_id - zs_jd)^2 (the sn^2 I part does not depend on it).
@@ -670,14 +457,20 @@ __device__ __forceinline__ double wave_sum(double x) {
 
 // P = sum_n g_n r_n r_n^T over rows n in [n0, n1) of one output, for one
 // 128 x 128 block (bi <= bj) of the Mpad x Mpad result, contracted with dA/dlog ell:
-// ppart[((o * npairs + pair) * nsplit + split) * 4 + d].  Wave w owns the
-// 32 x 32 tiles (2 (w >> 1) + {0, 1}, 2 (w & 1) + {0, 1}) of the block.
-__global__ __launch_bounds__(kThreads) void grad_syrk_kernel(const float *R, const float *Gw, long long TK, int Mpad,
-                                                             const float *zs, float c20, float c21, int nsplit,
-                                                             double *ppart) {
+// ppart[((o * nslot + slot) * npairs + pair) * 4 + d], slot = chunk nsplit + split.  Wave w
+// owns the 32 x 32 tiles (2 (w >> 1) + {0, 1}, 2 (w & 1) + {0, 1}) of the block.  The blocks on
+// the diagonal also sum their rows' share of b = sum_n mb_n r_n into bpart[slot][o].
+__global__ __launch_bounds__(kThreads) void grad_syrk_kernel(GradArgs a, int chunk) {
     __shared__ double red[kWaves][4];
-    const int pair = blockIdx.x, split = blockIdx.y, o = blockIdx.z;
-    const int npairs = gridDim.x;
+    // consecutive workgroups go to the eight XCDs in turn: every block pair of the same rows on one
+    // XCD, whose L2 then holds the rows
+    const int npairs = a.npairs, nsplit = a.nsplit, Mpad = a.gp.Mpad;
+    const int group = ((int)blockIdx.x / (8 * npairs)) * 8 + (int)(blockIdx.x & 7), pair = ((int)blockIdx.x >> 3) % npairs;
+    if (group >= 2 * nsplit) return;
+    const int split = group >> 1, o = group & 1;
+    const int slot = chunk * nsplit + split, nslot = a.nchunk * nsplit;
+    const int s0 = chunk * a.Kc, kc = a.K - s0 < a.Kc ? a.K - s0 : a.Kc;
+    const long long TK = (long long)a.T * kc;
     const int nb = (Mpad + 127) / 128;
     int bi = 0, rem = pair;
     while (rem >= nb - bi) {
@@ -690,53 +483,80 @@ __global__ __launch_bounds__(kThreads) void grad_syrk_kernel(const float *R, con
     const int ti0 = 4 * bi + 2 * (w >> 1), tj0 = 4 * bj + 2 * (w & 1);
     const int NT = Mpad >> 5;
     const bool vi[2] = {ti0 < NT, ti0 + 1 < NT}, vj[2] = {tj0 < NT, tj0 + 1 < NT};
-    const long long chunk = (TK + nsplit - 1) / nsplit;
-    const long long n0 = (long long)split * chunk;
-    const long long n1 = n0 + chunk < TK ? n0 + chunk : TK;
-    const float *Ro = R + (size_t)o * TK * Mpad;
-    const float *Go = Gw + (size_t)o * TK;
+    const long long rows = (TK + nsplit - 1) / nsplit;
+    const long long n0 = (long long)split * rows;
+    const long long n1 = n0 + rows < TK ? n0 + rows : TK;
+    const size_t NS = (size_t)a.T * a.Kc;
+    const float *Ro = a.R + o * NS * Mpad;
+    const float *Go = a.wgt + o * 2 * NS;
+    const bool bsum = bi == bj && (w & 1) == 0;
+    double bacc[2] = {0.0, 0.0};
     v16f acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = v16f{};
     const int col = lane & 31, rsel = lane >> 5;
-    // rows in chunks of kD row pairs: every load of a chunk is issued before its first
-    // product, so the loads' latency is paid once per chunk
-    constexpr int kD = 8;
-    for (long long n = n0; n < n1; n += 2 * kD) {
-        float gq[kD], ra[kD][2], rbq[kD][2];
-        bool okq[kD];
+    // rows in chunks of kD row pairs, the next chunk's loads in flight beside a chunk's products;
+    // rows past the end count with weight 0
+    constexpr int kD = 4;
+    struct Rows {
+        float g[kD], m[kD], ra[kD][2], rb[kD][2];
+    };
+    auto load = [&](Rows &r, long long n) {
 #pragma unroll
         for (int q = 0; q < kD; ++q) {
-            const long long row = n + 2 * q + rsel;
-            okq[q] = row < n1;
-            const float *rp = Ro + (size_t)(okq[q] ? row : n0) * Mpad;
-            gq[q] = Go[okq[q] ? row : n0];
+            const long long at = n + 2 * q + rsel;
+            const bool ok = at < n1;
+            const long long row = ok ? at : n0;
+            const float *rp = Ro + (size_t)row * Mpad + col;
+            r.g[q] = ok ? Go[row] : 0.0f;
+            r.m[q] = ok && bsum ? Go[NS + row] : 0.0f;
 #pragma unroll
-            for (int i = 0; i < 2; ++i) ra[q][i] = vi[i] ? rp[32 * (ti0 + i) + col] : 0.0f;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) rbq[q][j] = vj[j] ? rp[32 * (tj0 + j) + col] : 0.0f;
+            for (int i = 0; i < 2; ++i) {
+                r.ra[q][i] = vi[i] ? rp[32 * (ti0 + i)] : 0.0f;
+                r.rb[q][i] = vj[i] ? rp[32 * (tj0 + i)] : 0.0f;
+            }
         }
+    };
+    auto multiply = [&](const Rows &r) {
 #pragma unroll
         for (int q = 0; q < kD; ++q) {
-            const float gv = gq[q];
-            float av[2], bv[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) av[i] = okq[q] ? gv * ra[q][i] : 0.0f;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) bv[j] = okq[q] ? rbq[q][j] : 0.0f;
+            const float av[2] = {r.g[q] * r.ra[q][0], r.g[q] * r.ra[q][1]};
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[j], acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], r.rb[q][j], acc[i][j], 0, 0, 0);
+            if (bsum) {
+                bacc[0] += (double)(r.m[q] * r.ra[q][0]);
+                bacc[1] += (double)(r.m[q] * r.ra[q][1]);
+            }
+        }
+    };
+    if (n0 < n1) {
+        Rows r0, r1;
+        load(r0, n0);
+        for (long long n = n0; n < n1; n += 4 * kD) {
+            load(r1, n + 2 * kD);
+            __builtin_amdgcn_sched_barrier(0);   // the loads stay ahead of the products
+            multiply(r0);
+            load(r0, n + 4 * kD);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(r1);
+        }
+    }
+    if (bsum) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const double v = bacc[i] + __shfl_xor(bacc[i], 32, 64);
+            if (rsel == 0 && vi[i]) a.bpart[((size_t)slot * 2 + o) * Mpad + 32 * (ti0 + i) + col] = v;
         }
     }
     // epilogue: sum_ij P_ij dA_ij/dtheta over the wave's tiles (both triangles of a
     // diagonal block; off-diagonal blocks stand for their mirror image too)
-    const float c2 = o ? c21 : c20;
-    const float4 *z = reinterpret_cast<const float4 *>(zs) + (size_t)o * Mpad;
+    const float c2 = a.gp.c2[o];
+    const float4 *z = reinterpret_cast<const float4 *>(a.gp.zs) + (size_t)o * Mpad;
     const float weight = bi == bj ? 1.0f : 2.0f;
     double cacc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -759,29 +579,28 @@ __global__ __launch_bounds__(kThreads) void grad_syrk_kernel(const float *R, con
     __syncthreads();
     if (threadIdx.x < 4) {
         const double v = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
-        ppart[((size_t)(o * npairs + pair) * nsplit + split) * 4 + threadIdx.x] = v;
+        a.ppart[(((size_t)o * nslot + slot) * npairs + pair) * 4 + threadIdx.x] = v;
     }
 }
 
-// b = sum over workgroups of the partial b, then sum_ij b_i alpha_j dA_ij/dlog ell_d:
-// one thread per row i; bterm[(o * gridDim.x + block) * 4 + d].
-__global__ __launch_bounds__(kThreads) void grad_bterm_kernel(const double *bpart, int nwg, int Mpad, const float *zs,
-                                                              const float *alpha, float c20, float c21,
-                                                              double *bterm) {
+// b = sum of the partial b, then sum_ij b_i alpha_j dA_ij/dlog ell_d: a workgroup per 32 rows
+// i, eight threads a row that take every eighth j; bterm[(o * gridDim.x + block) * 4 + d].
+__global__ __launch_bounds__(kThreads) void grad_bterm_kernel(GradArgs a) {
     __shared__ double red[kWaves][4];
-    const int o = blockIdx.y;
-    const int i = blockIdx.x * kThreads + threadIdx.x;
-    const float c2 = o ? c21 : c20;
-    const float4 *z = reinterpret_cast<const float4 *>(zs) + (size_t)o * Mpad;
-    const float *al = alpha + (size_t)o * Mpad;
+    const int o = blockIdx.y, Mpad = a.gp.Mpad, nslot = a.nchunk * a.nsplit;
+    const int i = blockIdx.x * 32 + (threadIdx.x >> 3), part = threadIdx.x & 7;
+    const float c2 = a.gp.c2[o];
+    const float4 *z = reinterpret_cast<const float4 *>(a.gp.zs) + (size_t)o * Mpad;
+    const float *al = a.gp.alpha + (size_t)o * Mpad;
+    double b = 0.0;
+    for (int s = part; s < nslot; s += 8) b += a.bpart[((size_t)s * 2 + o) * Mpad + i];
+#pragma unroll
+    for (int m = 1; m < 8; m <<= 1) b += __shfl_xor(b, m, 64);
+    const float4 zi = z[i];
+    const float bf = (float)b;
     double cacc[4] = {0.0, 0.0, 0.0, 0.0};
-    if (i < Mpad) {
-        double b = 0.0;
-        for (int wg = 0; wg < nwg; ++wg) b += bpart[((size_t)wg * 2 + o) * Mpad + i];
-        const float4 zi = z[i];
-        const float bf = (float)b;
-        for (int j = 0; j < Mpad; ++j) dA_contract(bf * al[j], zi, z[j], c2, cacc);
-    }
+#pragma unroll 4
+    for (int j = part; j < Mpad; j += 8) dA_contract(bf * al[j], zi, z[j], c2, cacc);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
@@ -791,100 +610,71 @@ __global__ __launch_bounds__(kThreads) void grad_bterm_kernel(const double *bpar
     __syncthreads();
     if (threadIdx.x < 4) {
         const double v = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
-        bterm[((size_t)o * gridDim.x + blockIdx.x) * 4 + threadIdx.x] = v;
+        a.bterm[((size_t)o * gridDim.x + blockIdx.x) * 4 + threadIdx.x] = v;
     }
 }
 
-// Fixed-order final sums: J = mean smoothed cost, dU[k][c], and the
-// hyperparameter gradient: log ell_d = direct (through k) + (P - b alpha^T) : dA/dlog ell_d;
-// log sf = its folded per-sample terms.
-__global__ __launch_bounds__(kThreads) void grad_final_kernel(const float *costs, int K, int T, int nwg,
-                                                              const float *upart, const double *hpart,
-                                                              const double *ppart, int nppart, const double *bterm,
-                                                              int nbterm, float *J, float *dU, float *dlog_ell,
-                                                              float *dlog_sf) {
-    __shared__ float red[kThreads];
+// Fixed-order final sums, a workgroup each: J = mean smoothed cost and the hyperparameter
+// gradient (block 0), dU[k][c] (the others).  log ell_d = direct (through k) +
+// (P - b alpha^T) : dA/dlog ell_d; log sf = its folded per-sample terms.
+__global__ __launch_bounds__(kThreads) void grad_final_kernel(GradArgs a, int nslot_back) {
+    __shared__ double red[kThreads];
     const int tid = threadIdx.x;
-    float s = 0.0f;
-    for (int i = tid; i < K; i += kThreads) s += costs[i];
-    red[tid] = s;
-    __syncthreads();
-    for (int h = kThreads / 2; h > 0; h >>= 1) {
-        if (tid < h) red[tid] += red[tid + h];
-        __syncthreads();
-    }
-    if (tid == 0) J[0] = red[0] / (float)K;
-    for (int kc = tid; kc < 2 * T; kc += kThreads) {
+    // sum over i < n of p[i stride], in a fixed order
+    auto total = [&](auto p, size_t n, size_t stride) {
         double v = 0.0;
-        for (int wg = 0; wg < nwg; ++wg) v += upart[(size_t)wg * 2 * T + kc];
-        dU[kc] = (float)v;
-    }
-    if (tid < 10) {
-        const int o = tid / 5, t = tid % 5;
-        double direct = 0.0, mat = 0.0, bt = 0.0;
-        for (int wg = 0; wg < nwg; ++wg) direct += hpart[(size_t)wg * 10 + tid];
-        if (t < 4) {
-            for (int i = 0; i < nppart; ++i) mat += ppart[((size_t)o * nppart + i) * 4 + t];
-            for (int i = 0; i < nbterm; ++i) bt += bterm[((size_t)o * nbterm + i) * 4 + t];
+        for (size_t i = tid; i < n; i += kThreads) v += (double)p[i * stride];
+        __syncthreads();
+        red[tid] = v;
+        __syncthreads();
+        for (int h = kThreads / 2; h > 0; h >>= 1) {
+            if (tid < h) red[tid] += red[tid + h];
+            __syncthreads();
         }
-        const float g = (float)(direct + mat - bt);
-        if (t < 4) dlog_ell[o * 4 + t] = g;
-        else dlog_sf[o] = g;
+        return red[0];
+    };
+    const int b = blockIdx.x;
+    if (b < 2 * a.T) {
+        const double v = total(a.upart + b, nslot_back, (size_t)2 * a.T);
+        if (tid == 0) a.dU[b] = (float)v;
+        return;
     }
+    const int i = b - 2 * a.T;
+    if (i == 10) {
+        const double v = total(a.costs, a.K, 1);
+        if (tid == 0) a.J[0] = (float)(v / (double)a.K);
+        return;
+    }
+    const int o = i / 5, t = i % 5;
+    const double direct = total(a.hpart + i, nslot_back, 10);
+    if (t == 4) {
+        if (tid == 0) a.dlog_sf[o] = (float)direct;
+        return;
+    }
+    const size_t np = (size_t)a.nchunk * a.nsplit * a.npairs;
+    const double mat = total(a.ppart + (size_t)o * np * 4 + t, np, 4);
+    const double bt = total(a.bterm + (size_t)o * a.nbterm * 4 + t, a.nbterm, 4);
+    if (tid == 0) a.dlog_ell[o * 4 + t] = (float)(direct + mat - bt);
 }
 
-size_t grad_lds(int Mpad) { return grad_lds_bytes(Mpad); }
-
-int grad_split_capacity(int Mpad) {
-    const size_t lds = grad_lds_bytes(Mpad);
-    int dev = 0, ncu = 0, per_cu = 0;
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(grad_kernel<true>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(grad_kernel<true>),
-                                                     kThreads, lds) != hipSuccess)
-        return 0;
-    return per_cu * ncu;
-}
-
-hipError_t launch_grad(const GradArgs &args, const GradLaunch &l, hipStream_t st) {
-    const size_t lds = grad_lds_bytes(args.gp.Mpad);
-    GradArgs a = args;
-    hipError_t e;
-    if (a.split) {
-        if (!a.xrec || !a.repair || 2 * l.nwg > grad_split_capacity(a.gp.Mpad)) return hipErrorInvalidValue;
-        const size_t n_rec = (size_t)l.nwg * kGradXchPerBlock;
-        const size_t n = n_rec > (size_t)l.nwg ? n_rec : (size_t)l.nwg;
-        hipLaunchKernelGGL(grad_clear_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
-                           a.xrec, n_rec, a.repair, l.nwg);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = hipFuncSetAttribute(reinterpret_cast<const void *>(grad_kernel<true>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess)
-            return e;
-        hipLaunchKernelGGL(grad_kernel<true>, dim3(2 * l.nwg), dim3(kThreads), lds, st, a);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        // the repair launch: the unsplit kernel for the blocks whose exchange gave up
-        if ((e = hipFuncSetAttribute(reinterpret_cast<const void *>(grad_kernel<false, true>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess)
-            return e;
-        hipLaunchKernelGGL((grad_kernel<false, true>), dim3(l.nwg), dim3(kThreads), lds, st, a);
-    } else {
-        if ((e = hipFuncSetAttribute(reinterpret_cast<const void *>(grad_kernel<false>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess)
-            return e;
-        hipLaunchKernelGGL(grad_kernel<false>, dim3(l.nwg), dim3(kThreads), lds, st, a);
+hipError_t launch_grad(const GradArgs &a, hipStream_t st) {
+    const int nblk = (a.Kc + 63) / 64;
+    const int lds = grad_gp_lds(a.gp.Mpad);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(grad_gp_kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    for (int c = 0; c < a.nchunk; ++c) {
+        const int kc = a.K - c * a.Kc < a.Kc ? a.K - c * a.Kc : a.Kc;
+        const long long N = (long long)a.T * kc;
+        hipLaunchKernelGGL(grad_cov_kernel, dim3(nblk), dim3(64), 0, st, a, c);
+        hipLaunchKernelGGL(grad_stage_kernel, dim3((kc + 255) / 256, a.T), dim3(256), 0, st, a, c);
+        hipLaunchKernelGGL(grad_gp_kernel, dim3((unsigned)((N + kGpRows - 1) / kGpRows), 2), dim3(64 * kGpWaves), lds, st, a, c);
+        hipLaunchKernelGGL(grad_back_kernel, dim3(nblk), dim3(64), 0, st, a, c);
+        hipLaunchKernelGGL(grad_syrk_kernel, dim3((2 * a.nsplit + 7) / 8 * 8 * a.npairs), dim3(kThreads), 0, st, a,
+                           c);
     }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    const long long TK = (long long)a.T * a.K;
-    hipLaunchKernelGGL(grad_syrk_kernel, dim3(l.npairs, l.nsplit, 2), dim3(kThreads), 0, st, a.R, a.Gw, TK, a.gp.Mpad,
-                       a.gp.zs, a.gp.c2[0], a.gp.c2[1], l.nsplit, l.ppart);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(grad_bterm_kernel, dim3(l.nbterm, 2), dim3(kThreads), 0, st, a.bpart, l.nwg, a.gp.Mpad,
-                       a.gp.zs, a.gp.alpha, a.gp.c2[0], a.gp.c2[1], l.bterm);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(grad_final_kernel, dim3(1), dim3(kThreads), 0, st, a.costs, a.K, a.T, l.nwg, a.upart, a.hpart,
-                       l.ppart, l.npairs * l.nsplit, l.bterm, l.nbterm, l.J, l.dU, l.dlog_ell, l.dlog_sf);
+    hipLaunchKernelGGL(grad_bterm_kernel, dim3(a.nbterm, 2), dim3(kThreads), 0, st, a);
+    hipLaunchKernelGGL(grad_final_kernel, dim3(2 * a.T + 11), dim3(kThreads), 0, st, a, a.nchunk * nblk);
     return hipGetLastError();
 }
 

@@ -195,50 +195,40 @@ hipError_t combine_alpha(const double *alpha_terr, int n_terr, int Mpad, Terrain
                          float *alpha32, float *alphas, hipStream_t st);
 hipError_t launch_terrain_means(const float *q, int n, const GpDev &g, const double *alpha_terr, int n_terr,
                                 float *out, hipStream_t st);
-// Differentiation form (the adjoint rollout and its reductions).
+// Differentiation form (see grad.hip).  Samples are taken in chunks of Kc; entry (k, s) of a
+// chunk has index n = k Kc + (s - s0), and the chunk arrays below hold N = T Kc of them.
 struct GradArgs {
     GpDev gp;
     Geometry geo;
     CostWeights cw;
     Dyn dyn;
     NoiseParams noise;
-    int K, T, C, nck;
+    int K, T, Kc, nchunk;
     float inv_tau, inv_K;
     const float4 *q32;       // dense packed Q per output
     long long q_stride;      // float4 per output
-    const float *x0;         // [5]
     const float *U;          // [T][2]
+    const float *x, *u, *s2; // the rollout's trace: states [T+1][5][K], controls [T][2][K], variances [T][2][K]
     float *costs;            // [K] smoothed costs
-    float *ckpt;             // [nck][20][K]
-    float *seg;              // [nwg][C + 1][28][32] per-workgroup segment scratch
-    float *R;                // [2][T K][Mpad]
-    float *Gw;               // [2][T K]
-    double *bpart;           // [nwg][2][Mpad]
-    double *hpart;           // [nwg][10]
-    float *upart;            // [nwg][T][2]
-    // output split (two workgroups per 32 samples, one per GP output): ckpt holds [2 roles]
-    // and seg [nwg][2 roles] copies; xrec [nwg][kGradXchPerBlock] exchange records, zeroed
-    // with repair [nwg] before each split launch; repair marks blocks for the repair launch
-    int split;
-    unsigned long long *xrec;
-    uint32_t *repair;
-    int xspin;               // polls per exchange wait before it gives up; < 0: give up at once
-    uint32_t *flags;         // context status word (GPMPPI_FLAG_EXCHANGE_TIMEOUT)
-};
-
-struct GradLaunch {
-    int nwg;                 // grad_kernel workgroups = ceil(K / 32)
+    float *cov;              // chunk: [T][15][Kc] Sigma_{k+1}
+    float *stage;            // chunk: [T][6][Kc] stage cost and its adjoint
+    float *sums;             // chunk: [2][kGradSums][N]
+    float *R;                // chunk: [2][N][Mpad] r = A^-1 k
+    float *wgt;              // chunk: [2][2][N] adjoints of s2 and m per output
+    double *bpart;           // [nchunk nsplit][2][Mpad]
+    double *hpart;           // [nchunk nblk][10], nblk = ceil(Kc / 64)
+    float *upart;            // [nchunk nblk][T][2]
     int npairs, nsplit;      // grad_syrk_kernel grid: 128-blocks (bi <= bj) x row splits
     int nbterm;              // grad_bterm_kernel blocks per output
     double *ppart, *bterm;   // partial contractions
     float *J, *dU, *dlog_ell, *dlog_sf;   // outputs
 };
-// Dynamic LDS of grad_kernel at this Mpad (must be <= 160 KB minus its static LDS).
-size_t grad_lds(int Mpad);
-constexpr int kGradXchPerBlock = 2 * 4 * 4 * kSamplesPerBlock;   // split exchange records per block
-// Workgroups of the split gradient kernel resident at once (a split launch needs 2 nwg).
-int grad_split_capacity(int Mpad);
-hipError_t launch_grad(const GradArgs &a, const GradLaunch &l, hipStream_t st);
+constexpr int kGradSums = 19;   // per output, step and sample (see grad_gp_kernel)
+// The gradient's part behind the rollout that wrote its trace.
+hipError_t launch_grad(const GradArgs &a, hipStream_t st);
+// Zeroes a split rollout's exchange records [n_rec], epoch words [2] and repair marks [n_blk].
+hipError_t launch_exchange_clear(unsigned long long *rec, size_t n_rec, uint32_t *xep, uint32_t *repair, int n_blk,
+                                 hipStream_t st);
 
 // Q = A^-1 = W^T W of output o packed dense (FP32 operand order).
 hipError_t pack_q(const GpBuildBuffers &b, int M, int Mpad, int o, float4 *q32, hipStream_t st);

@@ -120,7 +120,7 @@ gpmppi_status set_error(gpmppi_status st, const char *msg) { return fail(st, "%s
 }  // namespace gpmppi
 
 constexpr int kSweepLayout = 2;   // CoreShape::layout of blocks in the sweep layout
-constexpr int kGradMaxMpad = 512;   // the adjoint's LDS plan holds k and r for 32 samples
+constexpr int kGradMaxMpad = 512;   // the gradient's LDS plan holds k for 64 (step, sample) entries
 
 // Scratch memory of the allocation-free entry point (gpmppi_grad_noalloc): one
 // array per GPU the library runs on, held until the process ends and shared by
@@ -1233,67 +1233,134 @@ namespace {
 
 // Pieces of the gradient's workspace (256-byte aligned offsets) for one call shape.
 struct GradLayout {
-    GradLaunch l{};
-    int C = 1, nck = 1;
-    int split = 0;   // two workgroups per 32 samples, one per GP output (when they fit the device at once)
-    size_t o_ck = 0, o_seg = 0, o_R = 0, o_G = 0, o_b = 0, o_h = 0, o_u = 0, o_p = 0, o_bt = 0, o_c = 0;
-    size_t o_x = 0, o_rp = 0;
+    int Kc = 0, nchunk = 1;   // samples per chunk
+    int npairs = 0, nsplit = 0, nbterm = 0;
+    size_t o_x = 0, o_u = 0, o_s2 = 0, o_c = 0, o_cov = 0, o_st = 0, o_sum = 0, o_R = 0, o_w = 0, o_b = 0, o_h = 0,
+           o_up = 0, o_p = 0, o_bt = 0, o_rec = 0, o_ep = 0, o_rp = 0;
+    size_t n_rec = 0;         // the split rollout's exchange records (0: unsplit)
     size_t bytes = 0;
 };
 
-// Validates a gradient call on the host and lays out its workspace.
+// Most bytes a gradient call may take: what the entry points promise about a workspace of
+// 8 T K M_pad bytes and a record of every checkpoint segment.  Calls beyond the scratch array
+// by this count are refused.
+size_t grad_limit(const gpmppi_ctx *c, int C) {
+    const int K = c->params.K, T = c->params.T, Mpad = c->Mpad;
+    const long long TK = (long long)T * K;
+    const int nwg = (K + 31) / 32, nck = (T + C - 1) / C, nb = (Mpad + 127) / 128, npairs = nb * (nb + 1) / 2;
+    const long long nsplit = std::max(1LL, std::min<long long>({64LL, (512 + 2 * npairs - 1) / (2 * npairs), (TK + 1) / 2}));
+    const int nbterm = (Mpad + kThreads - 1) / kThreads;
+    size_t off = 0;
+    for (size_t n : {(size_t)2 * nck * 20 * K, (size_t)nwg * 2 * (C + 1) * 28 * 32, (size_t)2 * (size_t)TK * Mpad, (size_t)2 * (size_t)TK,
+                     (size_t)nwg * 2 * Mpad * 2, (size_t)nwg * 10 * 2, (size_t)nwg * T * 2,
+                     (size_t)2 * npairs * (size_t)nsplit * 4 * 2, (size_t)2 * nbterm * 4 * 2, (size_t)K,
+                     (size_t)nwg * 1024 * 2, (size_t)nwg})
+        off += (n * sizeof(float) + 255) / 256 * 256;
+    return off;
+}
+
+// The layout with chunks of Kc samples.
+GradLayout grad_layout(const gpmppi_ctx *c, int Kc) {
+    const int K = c->params.K, T = c->params.T, Mpad = c->Mpad;
+    GradLayout g;
+    g.Kc = Kc;
+    g.nchunk = (K + Kc - 1) / Kc;
+    const int nb = (Mpad + 127) / 128;
+    g.npairs = nb * (nb + 1) / 2;
+    const size_t TK = (size_t)T * K, N = (size_t)T * Kc;
+    // at most two workgroups of the product per compute unit (one more would wait for a whole turn),
+    // the same number of row groups on every XCD
+    g.nsplit = (int)std::max(1LL, std::min<long long>({64LL, 512 / g.npairs / 8 * 4, ((long long)N + 1) / 2}));
+    g.nbterm = Mpad / 32;
+    const size_t nblk = (size_t)g.nchunk * ((Kc + 63) / 64), nslot = (size_t)g.nchunk * g.nsplit;
+    auto take = [&](size_t nfloat) {
+        const size_t at = g.bytes;
+        g.bytes += (nfloat * sizeof(float) + 255) / 256 * 256;
+        return at;
+    };
+    g.o_x = take((size_t)5 * (T + 1) * K);
+    g.o_u = take(2 * TK);
+    g.o_s2 = take(2 * TK);
+    g.o_c = take((size_t)K);
+    g.o_cov = take(15 * N);
+    g.o_st = take(6 * N);
+    g.o_sum = take(2 * kGradSums * N);
+    g.o_R = take(2 * N * Mpad);
+    g.o_w = take(4 * N);
+    g.o_b = take(nslot * 2 * Mpad * 2);
+    g.o_h = take(nblk * 10 * 2);
+    g.o_up = take(nblk * T * 2);
+    g.o_p = take(2 * nslot * g.npairs * 4 * 2);
+    g.o_bt = take((size_t)2 * g.nbterm * 4 * 2);
+    // The rollout's output split where the streamed walk over W bounds a step and the doubled
+    // grid fits (see set_grad_split); a caller that makes every exchange wait give up gets the exchange
+    // at every size.
+    if (c->grad_split && (Mpad > 256 || c->xspin < 0) && K <= rollout_split_capacity(GPMPPI_FP32, Mpad, 8)) {
+        const size_t nb32 = (size_t)((K + 31) / 32);
+        g.n_rec = nb32 * kXchRecPerBlock;
+        g.o_rec = take(2 * g.n_rec);
+        g.o_ep = take(2);
+        g.o_rp = take(nb32);
+    }
+    return g;
+}
+
+// The fewest chunks that fit `limit` bytes.
+GradLayout grad_layout_within(const gpmppi_ctx *c, size_t limit) {
+    const int K = c->params.K;
+    GradLayout g = grad_layout(c, K);
+    for (int n = 2; g.bytes > limit && g.Kc > 1; ++n) {
+        const int Kc = (K + n - 1) / n;
+        if (Kc < g.Kc) g = grad_layout(c, Kc);
+    }
+    return g;
+}
+
+// Validates a gradient call on the host and lays out its workspace: one chunk, unless r would fit
+// the scratch array and the rest does not (so that both entry points, and every checkpoint_every,
+// take the same chunks).  limit: the most the call may need.
 gpmppi_status grad_check(const gpmppi_ctx *c, const float *x0_d, const float *U_d, double tau, int32_t checkpoint_every,
                          const float *J_d, const float *dU_d, const float *dlog_ell_d, const float *dlog_sf_d,
-                         GradLayout &g) {
+                         GradLayout &g, size_t &limit) {
     if (!c || !x0_d || !U_d || !J_d || !dU_d || !dlog_ell_d || !dlog_sf_d) return fail(GPMPPI_E_INVALID, "NULL argument");
     if (!is_fin(tau) || !(tau > 0.0)) return fail(GPMPPI_E_INVALID, "tau must be finite and > 0");
-    const int K = c->params.K, T = c->params.T, Mpad = c->Mpad;
-    if (checkpoint_every < 1 || checkpoint_every > T)
+    if (checkpoint_every < 1 || checkpoint_every > c->params.T)
         return fail(GPMPPI_E_INVALID, "checkpoint_every must lie in [1, T] (got %d)", checkpoint_every);
     if (!c->q32)
         return fail(GPMPPI_E_UNSUPPORTED, "the differentiation form supports M <= %d (padded M is %d)", kGradMaxMpad,
-                    Mpad);
+                    c->Mpad);
     if (c->n_terr > 0) return fail(GPMPPI_E_UNSUPPORTED, "the differentiation form has no terrain ensemble");
     if (c->params.tighten != 0 || c->params.w_goal != 0.0 || c->params.w_term != 0.0)
         return fail(GPMPPI_E_UNSUPPORTED, "the differentiation form has no goal terms or Step-2 tightening");
-    g.C = checkpoint_every;
-    GradLaunch &l = g.l;
-    l.nwg = (K + 31) / 32;
-    g.nck = (T + g.C - 1) / g.C;
-    const int nb = (Mpad + 127) / 128;
-    l.npairs = nb * (nb + 1) / 2;
-    const long long TK = (long long)T * K;
-    l.nsplit = (int)std::max(1LL, std::min<long long>({64LL, (512 + 2 * l.npairs - 1) / (2 * l.npairs), (TK + 1) / 2}));
-    l.nbterm = (Mpad + kThreads - 1) / kThreads;
-    size_t off = 0;
-    auto take = [&](size_t nfloat) {
-        const size_t at = off;
-        off += (nfloat * sizeof(float) + 255) / 256 * 256;
-        return at;
-    };
-    g.split = c->grad_split && 2 * l.nwg <= grad_split_capacity(Mpad) ? 1 : 0;
-    g.o_ck = take((size_t)2 * g.nck * 20 * K);                  // one copy per role
-    g.o_seg = take((size_t)l.nwg * 2 * (g.C + 1) * 28 * 32);    // per block and role
-    g.o_R = take((size_t)2 * TK * Mpad);
-    g.o_G = take((size_t)2 * TK);
-    g.o_b = take((size_t)l.nwg * 2 * Mpad * 2);
-    g.o_h = take((size_t)l.nwg * 10 * 2);
-    g.o_u = take((size_t)l.nwg * T * 2);
-    g.o_p = take((size_t)2 * l.npairs * l.nsplit * 4 * 2);
-    g.o_bt = take((size_t)2 * l.nbterm * 4 * 2);
-    g.o_c = take((size_t)K);
-    g.o_x = take((size_t)l.nwg * kGradXchPerBlock * 2);         // 64-bit exchange records
-    g.o_rp = take((size_t)l.nwg);
-    g.bytes = off;
+    limit = grad_limit(c, checkpoint_every);
+    const size_t r_bytes = (size_t)8 * c->params.T * c->params.K * c->Mpad;
+    g = r_bytes <= kScratchBytes ? grad_layout_within(c, kScratchBytes) : grad_layout(c, c->params.K);
     return GPMPPI_OK;
 }
 
-// Enqueues the adjoint rollout and its reductions with the workspace at ws (device memory of at
-// least g.bytes; no part of it needs to start at zero).
+// Enqueues the rollout, the adjoint recursion and the reductions with the workspace at ws (device
+// memory of at least g.bytes; no part of it needs to start at zero).
 gpmppi_status grad_enqueue(const gpmppi_ctx *c, const GradLayout &g, char *ws, const float *x0_d, const float *U_d,
                            uint64_t seed, double tau, float *J_d, float *dU_d, float *dlog_ell_d, float *dlog_sf_d,
                            float *costs_d, hipStream_t stream) {
-    GradLaunch l = g.l;
+    auto f32 = [&](size_t at) { return reinterpret_cast<float *>(ws + at); };
+    gpmppi_trace tr{};
+    tr.x_d = f32(g.o_x);
+    tr.u_d = f32(g.o_u);
+    tr.gp_var_d = f32(g.o_s2);
+    RolloutArgs ra = rollout_args(c, x0_d, U_d, seed, f32(g.o_c), &tr, nullptr);
+    ra.geo.path_kind = 0;   // its costs are not used: no track, no obstacles
+    ra.geo.P = 0;
+    ra.geo.n_obs = 0;
+    ra.rotate = 1;
+    if (g.n_rec) {
+        ra.xrec = reinterpret_cast<unsigned long long *>(ws + g.o_rec);
+        ra.xep = reinterpret_cast<uint32_t *>(ws + g.o_ep);
+        ra.repair = reinterpret_cast<uint32_t *>(ws + g.o_rp);
+        HIP_TRY(launch_exchange_clear(ra.xrec, g.n_rec, ra.xep, ra.repair, (c->params.K + 31) / 32, stream));
+    }
+    HIP_TRY(launch_rollout(ra, GPMPPI_FP32, g.n_rec ? 1 : rollout_groups(GPMPPI_FP32, c->Mpad), 8, g.n_rec ? 1 : 0,
+                           stream));
     GradArgs a{};
     a.gp = c->gp;
     a.geo = c->geo;
@@ -1304,34 +1371,35 @@ gpmppi_status grad_enqueue(const gpmppi_ctx *c, const GradLayout &g, char *ws, c
     a.noise.key1 = (uint32_t)(seed >> 32);
     a.K = c->params.K;
     a.T = c->params.T;
-    a.C = g.C;
-    a.nck = g.nck;
+    a.Kc = g.Kc;
+    a.nchunk = g.nchunk;
     a.inv_tau = (float)(1.0 / tau);
     a.inv_K = 1.0f / (float)a.K;
     a.q32 = c->q32;
     a.q_stride = c->q_stride;
-    a.x0 = x0_d;
     a.U = U_d;
-    a.costs = costs_d ? costs_d : reinterpret_cast<float *>(ws + g.o_c);
-    a.ckpt = reinterpret_cast<float *>(ws + g.o_ck);
-    a.seg = reinterpret_cast<float *>(ws + g.o_seg);
-    a.R = reinterpret_cast<float *>(ws + g.o_R);
-    a.Gw = reinterpret_cast<float *>(ws + g.o_G);
+    a.x = tr.x_d;
+    a.u = tr.u_d;
+    a.s2 = tr.gp_var_d;
+    a.costs = costs_d ? costs_d : f32(g.o_c);
+    a.cov = f32(g.o_cov);
+    a.stage = f32(g.o_st);
+    a.sums = f32(g.o_sum);
+    a.R = f32(g.o_R);
+    a.wgt = f32(g.o_w);
     a.bpart = reinterpret_cast<double *>(ws + g.o_b);
     a.hpart = reinterpret_cast<double *>(ws + g.o_h);
-    a.upart = reinterpret_cast<float *>(ws + g.o_u);
-    l.ppart = reinterpret_cast<double *>(ws + g.o_p);
-    l.bterm = reinterpret_cast<double *>(ws + g.o_bt);
-    a.split = g.split;
-    a.xrec = reinterpret_cast<unsigned long long *>(ws + g.o_x);
-    a.repair = reinterpret_cast<uint32_t *>(ws + g.o_rp);
-    a.xspin = c->xspin;
-    a.flags = c->flags;
-    l.J = J_d;
-    l.dU = dU_d;
-    l.dlog_ell = dlog_ell_d;
-    l.dlog_sf = dlog_sf_d;
-    HIP_TRY(launch_grad(a, l, stream));
+    a.upart = f32(g.o_up);
+    a.npairs = g.npairs;
+    a.nsplit = g.nsplit;
+    a.nbterm = g.nbterm;
+    a.ppart = reinterpret_cast<double *>(ws + g.o_p);
+    a.bterm = reinterpret_cast<double *>(ws + g.o_bt);
+    a.J = J_d;
+    a.dU = dU_d;
+    a.dlog_ell = dlog_ell_d;
+    a.dlog_sf = dlog_sf_d;
+    HIP_TRY(launch_grad(a, stream));
     return GPMPPI_OK;
 }
 
@@ -1344,13 +1412,20 @@ gpmppi_status gpmppi_grad(gpmppi_ctx *c, const float *x0_d, const float *U_d, ui
                           float *costs_d, void *stream) {
     g_last_error.clear();
     GradLayout g;
-    gpmppi_status st = grad_check(c, x0_d, U_d, tau, checkpoint_every, J_d, dU_d, dlog_ell_d, dlog_sf_d, g);
+    size_t limit = 0;
+    gpmppi_status st = grad_check(c, x0_d, U_d, tau, checkpoint_every, J_d, dU_d, dlog_ell_d, dlog_sf_d, g, limit);
     if (st != GPMPPI_OK) return st;
     if (g.bytes > c->grad_ws_bytes) {
         if (c->grad_ws) (void)hipFree(c->grad_ws);
         c->grad_ws = nullptr;
         c->grad_ws_bytes = 0;
-        if (hipMalloc(&c->grad_ws, g.bytes) != hipSuccess) {
+        hipError_t e = hipMalloc(&c->grad_ws, g.bytes);
+        if (e != hipSuccess && g.bytes > limit) {   // more chunks
+            (void)hipGetLastError();
+            g = grad_layout_within(c, limit);
+            e = hipMalloc(&c->grad_ws, g.bytes);
+        }
+        if (e != hipSuccess) {
             c->grad_ws = nullptr;
             return fail(GPMPPI_E_NOMEM, "hipMalloc of the %zu-byte gradient workspace failed", g.bytes);
         }
@@ -1373,13 +1448,14 @@ gpmppi_status gpmppi_grad_noalloc(gpmppi_ctx *c, const float *x0_d, const float 
                                   float *dlog_sf_d, float *costs_d, void *stream) {
     g_last_error.clear();
     GradLayout g;
-    gpmppi_status st = grad_check(c, x0_d, U_d, tau, checkpoint_every, J_d, dU_d, dlog_ell_d, dlog_sf_d, g);
+    size_t limit = 0;
+    gpmppi_status st = grad_check(c, x0_d, U_d, tau, checkpoint_every, J_d, dU_d, dlog_ell_d, dlog_sf_d, g, limit);
     if (st != GPMPPI_OK) return st;
-    if (g.bytes > kScratchBytes)
+    if (limit > kScratchBytes || g.bytes > kScratchBytes)
         return fail(GPMPPI_E_NOMEM,
                     "the allocation-free gradient needs %zu bytes of scratch, more than its %zu-byte maximum "
                     "(about 8 T K M_pad bytes are needed; use gpmppi_grad)",
-                    g.bytes, kScratchBytes);
+                    std::max(limit, g.bytes), kScratchBytes);
     if (!c->scratch) return fail(GPMPPI_E_HIP, "the scratch array of this context's device has no address");
     return grad_enqueue(c, g, static_cast<char *>(c->scratch), x0_d, U_d, seed, tau, J_d, dU_d, dlog_ell_d,
                         dlog_sf_d, costs_d, (hipStream_t)stream);
