@@ -9,9 +9,7 @@
 //
 // The only recursions are those of the forward states and of their adjoints; everything
 // else is the same work for every (step, sample) and runs over all of them at once:
-//   rollout            the FP32 rollout (rollout_core.hpp, no track, no obstacles) with its
-//                      trace: states, controls, GP variances
-//   grad_cov_kernel    Sigma_{k+1} = A Sigma A^T + dt^2 diag(s2), a thread per sample
+//   grad_forward_kernel  states, controls, GP variances and covariances, step after step
 //   grad_stage_kernel  smoothed stage cost and its adjoint, a thread per (k, s)
 //   grad_gp_kernel     r = Q k, Q = A^-1 = W^T W, and the sums over points from which the GP's
 //                      share of the adjoint follows by the adjoints s2b, mb of its outputs.
@@ -19,8 +17,7 @@
 //                        dq_d        = 2 ln2 s_d sum_j kappa_j d_d
 //                        d log ell_d = -2 ln2 sum_j kappa_j d_d^2     (through k)
 //                      so sum k r d, sum k alpha d, sum k r d^2, sum k alpha d^2, |r|^2 and
-//                      r^T alpha are kept per (output, step, sample), and the variance in FP32
-//                      operands, which d log sf is sensitive to (see below)
+//                      r^T alpha are kept per (output, step, sample)
 //   grad_back_kernel   the adjoint recursion, a thread per sample
 //   grad_syrk_kernel, grad_bterm_kernel, grad_final_kernel
 //                      the length-scales' dependence through A:
@@ -30,16 +27,14 @@
 // so with A r = k and A alpha = y its total derivative folds into per-sample
 // terms in which the large parts through k and through A^-1 cancel exactly:
 //   d log sf    = 2 s2b (s2 - sn^2 - sn^2 |r|^2) + 2 sn^2 mb r^T alpha
-// (s2 - sn^2 = sf^2 - |W k|^2, the latent variance).  What is systematic in it is left over
-// after the cancellation: the rollout's variance, whose 16-bit matrix cores round their sums towards
-// zero, makes 1e-5 of d log sf where FP32 makes 2e-6 (400 points), so grad_gp_kernel
-// computes it again.
+// (s2 - sn^2 = sf^2 - |W k|^2, the latent variance of the forward pass).  What is
+// systematic in it is left over after the cancellation.
 //
 // The samples are taken in chunks where the workspace (8 Mpad + 280 bytes per (k, s)) is
 // limited; a (k, s)'s results do not depend on its chunk.
 //
-// Measured, K = 4096, T = 50, M = 512: 7.6 ms -> 5.4 ms; K = 256, T = 20, M = 200: 0.94 ms ->
-// 0.25 ms.  Before, one kernel ran everything inside the recursion (its r = Q k once
+// Measured, K = 4096, T = 50, M = 512: 7.6 ms -> 5.2 ms; K = 256, T = 20, M = 200: 0.94 ms ->
+// 0.36 ms.  Before, one kernel ran everything inside the recursion (its r = Q k once
 // per reversed step, its variance twice per step: forward and again from checkpoints).
 #include "adjoint_step.hpp"
 #include "gp_tiles.hpp"
@@ -49,6 +44,12 @@ namespace gpmppi {
 namespace {
 
 constexpr float kLn2 = 0.69314718055994531f;
+
+// a b, never fused with a later sum.
+__device__ __forceinline__ float mul_rounded(float a, float b) {
+#pragma clang fp contract(off)
+    return a * b;
+}
 constexpr int kGpRows = 32;    // (k, s) entries per workgroup of grad_gp_kernel
 constexpr int kGpWaves = 8;
 
@@ -68,29 +69,169 @@ __device__ __forceinline__ ChunkPos chunk_pos(const GradArgs &a, int c, int sl) 
 
 }  // namespace
 
-// Latency of one sample's chain: 1.0 us a step (sine, cosine and 60 multiply-adds).
-__global__ __launch_bounds__(64) void grad_cov_kernel(GradArgs a, int chunk) {
-    const ChunkPos c = chunk_pos(a, chunk, blockIdx.x * 64 + threadIdx.x);
-    if (!c.valid) return;
-    const size_t K = a.K, Kc = a.Kc;
-    const float dt = a.dyn.dt;
-    float p[15] = {};
-    const float *x = a.x + c.s, *s2 = a.s2 + c.s;
-    float *out = a.cov + c.sl;
+namespace {
+
+constexpr int kB = 32;           // samples per workgroup of the forward pass
+constexpr int kParts = 8;        // loop splitters
+
+// Dynamic LDS of the forward pass: [k operand 32 x Mpad FP32][staged inputs]
+__host__ __device__ constexpr size_t grad_forward_lds(int Mpad) {
+    return kgroup_bytes<GPMPPI_FP32>(Mpad) + (size_t)staged_slots<GPMPPI_FP32>(Mpad) * 16;
+}
+
+__device__ __forceinline__ void restage(const GpDev &g, int o, unsigned char *lds) {
+    __syncthreads();
+    StagedInputs st;
+    stage_load<GPMPPI_FP32>(st, g, o);
+    stage_store<GPMPPI_FP32>(st, g, lds, kgroup_bytes<GPMPPI_FP32>(g.Mpad));
+    __syncthreads();
+}
+
+}  // namespace
+
+// Forward pass: states, controls, variances and covariances of every step, a workgroup of 32
+// samples or, split, two, workgroup 2 blk + r computing output r's mean and variance and both the
+// per-sample algebra; they exchange mean and variance every step.  The exchanged values enter the
+// same instructions as in the unsplit form (one kernel: two would fuse products and sums
+// differently), so the results are the same bit for bit.  A workgroup whose bounded exchange wait
+// gives up marks its block for the unsplit repair launch that follows every split launch and
+// runs the marked blocks only.
+//
+// The rollout's own kernels would take two thirds of the time, with sums grouped otherwise.  J's
+// gradient jumps where two segments or obstacles are equally near, and one sample in 200000 that
+// changes sides moves dU by 3e-5 of its norm; the FP32 grouping here is kept for that, and for
+// d log sf, which a variance from the 16-bit matrix cores (sums rounded towards zero) moves by
+// 1e-5 (see the top).
+enum ForwardMode { kForwardWhole = 0, kForwardSplit = 1, kForwardRepair = 2 };
+
+__global__ __launch_bounds__(kThreads) void grad_forward_kernel(GradArgs a, int mode) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    __shared__ float pred[kParts * kB];
+    __shared__ float vred[kWaves * kB];
+    __shared__ float xv[2 * kB + 1];   // split: values received from the partner, and a give-up flag
+
+    const bool split = mode == kForwardSplit;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, w = tid >> 6;
+    const int sl = lane & 31;
+    const int part = 2 * w + (lane >> 5);
+    const int blk = split ? (int)(blockIdx.x >> 1) : (int)blockIdx.x;
+    const int role = split ? (int)(blockIdx.x & 1) : 0;   // split: the GP output this workgroup computes
+    if (mode == kForwardRepair && __hip_atomic_load(a.repair + blk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return;
+    const int sg = blk * kB + sl;
+    const bool writer = w == 0 && lane < kB && role == 0 && sg < a.K;   // one copy of each sample
+    const size_t K = a.K;
+    const GpDev &g = a.gp;
+    const Dyn dy = a.dyn;
+    const float dt = dy.dt;
+    NoiseParams np = a.noise;
+
+    // split exchange: step k uses slot k % 4 of the writer's records [block][writer role][slot]
+    // [kind][32]; records are zeroed before the launch, and the tag k + 1 names the step
+    unsigned long long *xrec = a.xrec + (size_t)blk * kGradXchPerBlock;
+    auto xslot = [&](int wr, int k, int kind) { return xrec + ((size_t)(wr * 4 + (k & 3)) * 2 + kind) * kB; };
+    bool broken = false;
+
+    float X = a.x0[0], Y = a.x0[1], th = a.x0[2], v = a.x0[3], w_ = a.x0[4];
+    float p[15];
+#pragma unroll
+    for (int i = 0; i < 15; ++i) p[i] = 0.0f;
+    restage(g, role, lds);
     for (int k = 0; k < a.T; ++k) {
-        const float th = x[(5 * (size_t)k + 2) * K], v = x[(5 * (size_t)k + 3) * K];
-        const float e0 = s2[2 * (size_t)k * K], e1 = s2[(2 * (size_t)k + 1) * K];
+        if (writer) {
+            float *x = a.x + 5 * (size_t)k * K + sg;
+            x[0 * K] = X;
+            x[1 * K] = Y;
+            x[2 * K] = th;
+            x[3 * K] = v;
+            x[4 * K] = w_;
+        }
+        const bool rev = (k & 1) != 0;
+        const float2 u = sampled_control(np, k, sg, a.U[2 * k], a.U[2 * k + 1]);
+        const float q[4] = {v, w_, u.x, u.y};
+        float m[2], s2[2];
+        if (split) {   // this role's output, then the partner's mean and variance
+            const int o = role;
+            __syncthreads();
+            const float qs[4] = {mul_rounded(q[0], g.scale[o][0]), mul_rounded(q[1], g.scale[o][1]),
+                                 mul_rounded(q[2], g.scale[o][2]), mul_rounded(q[3], g.scale[o][3])};
+            gp_output<GPMPPI_FP32, 1>(g, o, -1, qs, part, sl, rev, 0, blk, lds, pred, vred, m[o], s2[o]);
+            const uint32_t tag = (uint32_t)k + 1;
+            if (w == 0) {
+                xch_put(xslot(role, k, 0), lane, m[o], tag);
+                xch_put(xslot(role, k, 1), lane, s2[o], tag);
+                const float mp = xch_get(xslot(1 - role, k, 0), lane, tag, a.xspin, broken);
+                const float sp = xch_get(xslot(1 - role, k, 1), lane, tag, a.xspin, broken);
+                if (lane < kB) {
+                    xv[lane] = mp;
+                    xv[kB + lane] = sp;
+                }
+                if (lane == 0) xv[2 * kB] = broken ? 1.0f : 0.0f;
+            }
+            __syncthreads();
+            if (xv[2 * kB] != 0.0f) {   // uniform: leave the block to the repair launch
+                if (tid == 0) {
+                    __hip_atomic_store(a.repair + blk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (a.flags)
+                        __hip_atomic_fetch_or(a.flags, GPMPPI_FLAG_EXCHANGE_TIMEOUT, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+                }
+                return;
+            }
+            m[1 - o] = xv[sl];
+            s2[1 - o] = xv[kB + sl];
+        } else {
+#pragma unroll
+            for (int oo = 0; oo < 2; ++oo) {
+                const int o = rev ? 1 - oo : oo;
+                __syncthreads();
+                const float qs[4] = {mul_rounded(q[0], g.scale[o][0]), mul_rounded(q[1], g.scale[o][1]),
+                                     mul_rounded(q[2], g.scale[o][2]), mul_rounded(q[3], g.scale[o][3])};
+                gp_output<GPMPPI_FP32, 1>(g, o, oo == 0 ? 1 - o : -1, qs, part, sl, rev, 0, blk, lds, pred, vred, m[o],
+                                          s2[o]);
+            }
+        }
         float sth, cth;
         sincosf(th, &sth, &cth);
         const Jac J{-dt * v * sth, dt * cth, dt * v * cth, dt * sth};
+        const float Xn = X + dt * v * cth;
+        const float Yn = Y + dt * v * sth;
+        const float thn = th + dt * w_;
+        // where either of two products could be fused with their sum, which one is spelt out
+        const float vn = v + fmaf(dy.dt_tau_v, u.x - v, mul_rounded(dt, m[0]));
+        const float wn = w_ + fmaf(dy.dt_tau_w, u.y - w_, mul_rounded(dt, m[1]));
         float P[15];
-        cov_forward(p, J, dt, a.dyn.a33, a.dyn.a44, dt * dt * e0, dt * dt * e1, P);
+        cov_forward(p, J, dt, dy.a33, dy.a44, mul_rounded(dt * dt, s2[0]), mul_rounded(dt * dt, s2[1]), P);
 #pragma unroll
-        for (int i = 0; i < 15; ++i) {
-            p[i] = P[i];
-            out[(15 * (size_t)k + i) * Kc] = P[i];
+        for (int i = 0; i < 15; ++i) p[i] = P[i];
+        X = Xn; Y = Yn; th = thn; v = vn; w_ = wn;
+        if (writer) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) a.s2[(2 * (size_t)k + i) * K + sg] = s2[i];
+            a.u[2 * (size_t)k * K + sg] = u.x;
+            a.u[(2 * (size_t)k + 1) * K + sg] = u.y;
+#pragma unroll
+            for (int i = 0; i < 15; ++i) a.cov[(15 * (size_t)k + i) * K + sg] = p[i];
         }
     }
+    if (writer) {
+        float *x = a.x + 5 * (size_t)a.T * K + sg;
+        x[0 * K] = X;
+        x[1 * K] = Y;
+        x[2 * K] = th;
+        x[3 * K] = v;
+        x[4 * K] = w_;
+    }
+    if (mode == kForwardRepair && tid == 0)   // the block is done
+        __hip_atomic_store(a.repair + blk, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Zeroes the split forward pass's exchange records and repair marks before a launch.
+__global__ __launch_bounds__(kThreads) void grad_clear_kernel(unsigned long long *rec, size_t n_rec, uint32_t *repair,
+                                                              int n_blk) {
+    const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
+    if (i < n_rec) rec[i] = 0ull;
+    if (i < (size_t)n_blk) repair[i] = 0u;
 }
 
 // Argmin over the polyline segments and obstacles, the smoothed stage cost at (x_{k+1},
@@ -106,9 +247,9 @@ __global__ __launch_bounds__(256) void grad_stage_kernel(GradArgs a, int chunk) 
     float x1[5], p1[15];
 #pragma unroll
     for (int i = 0; i < 5; ++i) x1[i] = a.x[(5 * (size_t)(k + 1) + i) * K + c.s];
-    p1[0] = a.cov[(15 * (size_t)k + 0) * Kc + c.sl];
-    p1[1] = a.cov[(15 * (size_t)k + 1) * Kc + c.sl];
-    p1[5] = a.cov[(15 * (size_t)k + 5) * Kc + c.sl];
+    p1[0] = a.cov[(15 * (size_t)k + 0) * K + c.s];
+    p1[1] = a.cov[(15 * (size_t)k + 1) * K + c.s];
+    p1[5] = a.cov[(15 * (size_t)k + 5) * K + c.s];
     const float s2[2] = {a.s2[2 * (size_t)k * K + c.s], a.s2[(2 * (size_t)k + 1) * K + c.s]};
     const float X = x1[0], Y = x1[1], sa = p1[0], sb = p1[1], sc = p1[5];
     float da, db, dc;
@@ -168,7 +309,7 @@ __host__ __device__ constexpr int grad_gp_lds(int Mpad) { return grad_gp_points_
 
 }  // namespace
 
-// r = Q k, |W k|^2 and the sums over points of 32 (k, s) entries of one output.  The product stays on the
+// r = Q k and the sums over points of 32 (k, s) entries of one output.  The product stays on the
 // FP32 matrix cores: A^-1 magnifies what is systematic in r's error, and the 16-bit ones round
 // their sums towards zero (r by FP16 terms of Q and k, exact operands: its error is two thirds of
 // FP32's, but d log ell's is three times FP32's, 2.3e-5 against 0.7e-5 at 512 points).
@@ -219,7 +360,7 @@ __global__ __launch_bounds__(64 * kGpWaves, 4) void grad_gp_kernel(GradArgs a, i
         Kp[32 + sl] = make_float4(kv[1], kv[3], kv[5], kv[7]);
     }
     __syncthreads();
-    // k r d (4), k alpha d (4), k r d^2 (4), k alpha d^2 (4), r r, r alpha, (W k)^2
+    // k r d (4), k alpha d (4), k r d^2 (4), k alpha d^2 (4), r r, r alpha
     float sum[kGradSums] = {};
     auto load = [&](float4 (&f)[4], const float4 *p) {
 #pragma unroll
@@ -252,15 +393,6 @@ __global__ __launch_bounds__(64 * kGpWaves, 4) void grad_gp_kernel(GradArgs a, i
             block(acc, f1, c + 1);
         }
     };
-    for (int i = 0; i * kGpWaves < NT; ++i) {   // W's row tiles, the long ones with the short ones
-        const int t = kGpWaves * i + ((i & 1) ? kGpWaves - 1 - w : w);
-        if (t >= NT) continue;
-        v16f acc = v16f{};
-        const int u = t >> 1;
-        walk(acc, g.w32 + o * g.w32_stride + (size_t)(2 * u * (u + 1) + (t & 1)) * 256 + lane, t + 1, 512);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) sum[18] = fmaf(acc[e], acc[e], sum[18]);
-    }
     const float4 *Qo = a.q32 + (size_t)o * a.q_stride + lane;
     // this workgroup's rows of R; stores beyond the chunk's last entry are dropped
     const __amdgpu_buffer_rsrc_t Rr = uniform_rsrc(a.R + ((size_t)o * a.T * a.Kc + n0) * Mpad,
@@ -312,7 +444,6 @@ __global__ __launch_bounds__(64 * kGpWaves, 4) void grad_gp_kernel(GradArgs a, i
         float x = 0.0f;
 #pragma unroll
         for (int v = 0; v < kGpWaves; ++v) x += red[(v * kGradSums + j) * kGpRows + l];
-        if (j == 18) x = g.vscale[o] * (g.sn2[o] + fmaxf(0.0f, g.sf2[o] - x));
         if (n0 + l < N) a.sums[((size_t)o * kGradSums + j) * a.T * a.Kc + n0 + l] = x;
     }
 }
@@ -344,7 +475,7 @@ __global__ __launch_bounds__(64) void grad_back_kernel(GradArgs a, int chunk) {
         if (c.valid) a.costs[s] = S;
     }
     struct Rec {
-        float th, v, v1, p[15];
+        float th, v, v1, s2[2], p[15];
         StageAdj t;
         float sum[2][kGradSums];
     };
@@ -354,7 +485,9 @@ __global__ __launch_bounds__(64) void grad_back_kernel(GradArgs a, int chunk) {
         r.v = a.x[(5 * kk + 3) * K + s];
         r.v1 = a.x[(5 * (kk + 1) + 3) * K + s];
 #pragma unroll
-        for (int i = 0; i < 15; ++i) r.p[i] = k > 0 ? a.cov[(15 * (kk - 1) + i) * Kc + sl] : 0.0f;
+        for (int o = 0; o < 2; ++o) r.s2[o] = a.s2[(2 * kk + o) * K + s];
+#pragma unroll
+        for (int i = 0; i < 15; ++i) r.p[i] = k > 0 ? a.cov[(15 * (kk - 1) + i) * K + s] : 0.0f;
         const float *st = a.stage + 6 * kk * Kc + sl;
         r.t = StageAdj{st[Kc], st[2 * Kc], st[3 * Kc], st[4 * Kc], st[5 * Kc]};
 #pragma unroll
@@ -375,7 +508,7 @@ __global__ __launch_bounds__(64) void grad_back_kernel(GradArgs a, int chunk) {
 #pragma unroll
         for (int o = 0; o < 2; ++o) {
             const float *t = r.sum[o];
-            const float sbo = t[18] > g.sn2[o] ? sa.s2b[o] : 0.0f, mb = sa.mb[o];
+            const float sbo = r.s2[o] > g.sn2[o] ? sa.s2b[o] : 0.0f, mb = sa.mb[o];
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
                 qb[d] += 2.0f * kLn2 * g.scale[o][d] * (2.0f * sbo * t[d] - mb * t[4 + d]);
@@ -383,7 +516,7 @@ __global__ __launch_bounds__(64) void grad_back_kernel(GradArgs a, int chunk) {
             }
             {   // log sf: the folded per-sample terms (k and A^-1 parts cancelled)
                 const double sn2 = (double)g.sn2[o];
-                hyp[o][4] += 2.0 * (double)sbo * (((double)t[18] - sn2) - sn2 * (double)t[16]) +
+                hyp[o][4] += 2.0 * (double)sbo * (((double)r.s2[o] - sn2) - sn2 * (double)t[16]) +
                              2.0 * sn2 * (double)mb * (double)t[17];
             }
             if (c.valid) {
@@ -419,22 +552,6 @@ __global__ __launch_bounds__(64) void grad_back_kernel(GradArgs a, int chunk) {
     }
 }
 
-__global__ __launch_bounds__(kThreads) void exchange_clear_kernel(unsigned long long *rec, size_t n_rec, uint32_t *xep,
-                                                                  uint32_t *repair, int n_blk) {
-    const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i < n_rec) rec[i] = 0ull;
-    if (i < 2) xep[i] = 0u;
-    if (i < (size_t)n_blk) repair[i] = 0u;
-}
-
-hipError_t launch_exchange_clear(unsigned long long *rec, size_t n_rec, uint32_t *xep, uint32_t *repair, int n_blk,
-                                 hipStream_t st) {
-    const size_t n = n_rec > (size_t)n_blk ? n_rec : (size_t)n_blk;
-    hipLaunchKernelGGL(exchange_clear_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
-                       rec, n_rec, xep, repair, n_blk);
-    return hipGetLastError();
-}
-
 // dA_ij / dlog ell_d contracted with a weight c_ij: K_ij = exp2(c2 - |zs_i - zs_j|^2),
 // dA/dlog ell_d = K 2 ln2 (zs_id - zs_jd)^2 (the sn^2 I part does not depend on it).
 __device__ __forceinline__ void dA_contract(float cval, const float4 &zi, const float4 &zj, float c2, double acc[4]) {
@@ -455,12 +572,44 @@ __device__ __forceinline__ double wave_sum(double x) {
     return x;
 }
 
+// Three BF16 terms of eight FP32 values (exact: each remainder is).
+struct Terms {
+    uint4 t[3];
+};
+__device__ __forceinline__ void split_terms(Terms &o, const float x[8]) {
+    uint32_t u[3][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float a = x[2 * i], b = x[2 * i + 1];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            u[k][i] = pack_bf16x2(a, b);
+            a -= __uint_as_float(u[k][i] << 16);
+            b -= __uint_as_float(u[k][i] & 0xffff0000u);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) o.t[k] = make_uint4(u[k][0], u[k][1], u[k][2], u[k][3]);
+}
+
 // P = sum_n g_n r_n r_n^T over rows n in [n0, n1) of one output, for one
 // 128 x 128 block (bi <= bj) of the Mpad x Mpad result, contracted with dA/dlog ell:
 // ppart[((o * nslot + slot) * npairs + pair) * 4 + d], slot = chunk nsplit + split.  Wave w
 // owns the 32 x 32 tiles (2 (w >> 1) + {0, 1}, 2 (w & 1) + {0, 1}) of the block.  The blocks on
 // the diagonal also sum their rows' share of b = sum_n mb_n r_n into bpart[slot][o].
-__global__ __launch_bounds__(kThreads) void grad_syrk_kernel(GradArgs a, int chunk) {
+//
+// The FP32 values go through the BF16 matrix cores as three terms each (24 bits, exact) and six
+// products: at 512 points, T K = 204800, 1.3 ms instead of 2.0 (FP32 products take 1.0 at their peak
+// rate); bound by the vector unit that splits (a third of the time) and the barriers of a turn.
+// The 16-bit cores round their sums towards zero, so every 32 rows start a fresh sum, the leading
+// products last, that is added in FP32 (round to nearest); the error of d log ell by it is 3e-7,
+// where one running sum makes 2e-5 and FP32 products 4e-7 (512 points, 4096 rows; over 28
+// gradients of 40 to 512 points the error against 64 bits is 1.005 of FP32 products' and a
+// running FP32 sum's, theirs in another order 1.009).
+//
+// A workgroup loads and splits its 32 rows of 256 columns once and shares them in LDS.
+__global__ __launch_bounds__(kThreads, 2) void grad_syrk_kernel(GradArgs a, int chunk) {
+    __shared__ uint4 terms[8 * 2 * 3 * 64];
     __shared__ double red[kWaves][4];
     // consecutive workgroups go to the eight XCDs in turn: every block pair of the same rows on one
     // XCD, whose L2 then holds the rows
@@ -487,71 +636,121 @@ __global__ __launch_bounds__(kThreads) void grad_syrk_kernel(GradArgs a, int chu
     const long long n0 = (long long)split * rows;
     const long long n1 = n0 + rows < TK ? n0 + rows : TK;
     const size_t NS = (size_t)a.T * a.Kc;
-    const float *Ro = a.R + o * NS * Mpad;
     const float *Go = a.wgt + o * 2 * NS;
-    const bool bsum = bi == bj && (w & 1) == 0;
-    double bacc[2] = {0.0, 0.0};
     v16f acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = v16f{};
-    const int col = lane & 31, rsel = lane >> 5;
-    // rows in chunks of kD row pairs, the next chunk's loads in flight beside a chunk's products;
-    // rows past the end count with weight 0
-    constexpr int kD = 4;
+    const int col = lane & 31;
+    // Thread (rg, cq) of the 32 rows of a turn: rows 8 rg .. + 7, columns 4 cq .. + 3 of the block's
+    // 128 columns of i (cq < 32, weighted) and 128 of j; operand of 32 columns and 16 rows:
+    // terms[tile][step][term][lane ^ (tile & 3)] (the exclusive or spreads the stores over the banks)
+    const int rg = w, cq = lane, tile = cq >> 3;
+    const bool wgt = cq < 32, bsum = bi == bj && wgt;
+    const int c0 = wgt ? 128 * bi + 4 * cq : 128 * bj + 4 * (cq - 32);
+    const bool cok = c0 < Mpad;
+    const float *Rc = a.R + o * NS * Mpad + (cok ? c0 : 0);
+    double bacc[4] = {0.0, 0.0, 0.0, 0.0};
     struct Rows {
-        float g[kD], m[kD], ra[kD][2], rb[kD][2];
+        v4f r[8];
+        float g[8];
     };
-    auto load = [&](Rows &r, long long n) {
+    auto load = [&](Rows &x, long long n) {
 #pragma unroll
-        for (int q = 0; q < kD; ++q) {
-            const long long at = n + 2 * q + rsel;
+        for (int e = 0; e < 8; ++e) {
+            const long long at = n + 8 * rg + e;
             const bool ok = at < n1;
             const long long row = ok ? at : n0;
-            const float *rp = Ro + (size_t)row * Mpad + col;
-            r.g[q] = ok ? Go[row] : 0.0f;
-            r.m[q] = ok && bsum ? Go[NS + row] : 0.0f;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                r.ra[q][i] = vi[i] ? rp[32 * (ti0 + i)] : 0.0f;
-                r.rb[q][i] = vj[i] ? rp[32 * (tj0 + i)] : 0.0f;
-            }
+            x.r[e] = *reinterpret_cast<const v4f *>(Rc + (size_t)row * Mpad);
+            x.g[e] = ok && cok ? Go[row] : 0.0f;
         }
     };
-    auto multiply = [&](const Rows &r) {
+    auto store = [&](const Rows &x, long long n) {
+        if (bsum) {
 #pragma unroll
-        for (int q = 0; q < kD; ++q) {
-            const float av[2] = {r.g[q] * r.ra[q][0], r.g[q] * r.ra[q][1]};
+            for (int e = 0; e < 8; ++e) {
+                const long long at = n + 8 * rg + e;
+                const float m = at < n1 && cok ? Go[NS + at] : 0.0f;
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], r.rb[q][j], acc[i][j], 0, 0, 0);
-            if (bsum) {
-                bacc[0] += (double)(r.m[q] * r.ra[q][0]);
-                bacc[1] += (double)(r.m[q] * r.ra[q][1]);
+                for (int c = 0; c < 4; ++c) bacc[c] += (double)(m * x.r[e][c]);
             }
         }
+        uint4 *out = terms + (size_t)(tile * 2 + (rg >> 1)) * 3 * 64;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = wgt ? mul_rounded(x.g[e], x.r[e][c]) : cok ? x.r[e][c] : 0.0f;
+            Terms t;
+            split_terms(t, v);
+            const int p = (4 * (cq & 7) + c + 32 * (rg & 1)) ^ (tile & 3);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) out[k * 64 + p] = t.t[k];
+        }
+    };
+    auto operand = [&](int tl, int step, int term) {
+        return terms[(size_t)((tl * 2 + step) * 3 + term) * 64 + (lane ^ (tl & 3))];
     };
     if (n0 < n1) {
-        Rows r0, r1;
-        load(r0, n0);
-        for (long long n = n0; n < n1; n += 4 * kD) {
-            load(r1, n + 2 * kD);
+        Rows x;
+        load(x, n0);
+        for (long long n = n0; n < n1; n += 32) {
+            __syncthreads();   // the last turn's readers are done
+            store(x, n);
+            __syncthreads();
+            if (n + 32 < n1) load(x, n + 32);
             __builtin_amdgcn_sched_barrier(0);   // the loads stay ahead of the products
-            multiply(r0);
-            load(r0, n + 4 * kD);
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(r1);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                v16f t[2] = {v16f{}, v16f{}};
+                auto mma = [&](const uint4 (&x)[2], const uint4 &y) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        t[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf(x[i]), as_bf(y), t[i], 0, 0, 0);
+                };
+                const int tj = 4 + 2 * (w & 1) + j;
+#pragma unroll
+                for (int step = 0; step < 2; ++step) {
+                    uint4 h[2], m[2], l[2];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        h[i] = operand(2 * (w >> 1) + i, step, 0);
+                        m[i] = operand(2 * (w >> 1) + i, step, 1);
+                        l[i] = operand(2 * (w >> 1) + i, step, 2);
+                    }
+                    const uint4 bh = operand(tj, step, 0), bm = operand(tj, step, 1);
+                    mma(h, operand(tj, step, 2));
+                    mma(l, bh);
+                    mma(m, bm);
+                    mma(h, bm);
+                    mma(m, bh);
+                    __builtin_amdgcn_sched_barrier(0);   // one step's operands at a time
+                }
+#pragma unroll
+                for (int step = 0; step < 2; ++step) {
+                    const uint4 h[2] = {operand(2 * (w >> 1), step, 0), operand(2 * (w >> 1) + 1, step, 0)};
+                    mma(h, operand(tj, step, 0));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[i][j][e] += t[i][e];
+            }
         }
     }
-    if (bsum) {
+    if (bi == bj) {   // the four row groups' sums of m r, in order
+        double *bs = reinterpret_cast<double *>(terms);   // [row group][128]
+        __syncthreads();
+        if (wgt) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const double v = bacc[i] + __shfl_xor(bacc[i], 32, 64);
-            if (rsel == 0 && vi[i]) a.bpart[((size_t)slot * 2 + o) * Mpad + 32 * (ti0 + i) + col] = v;
+            for (int c = 0; c < 4; ++c) bs[rg * 128 + 4 * cq + c] = bacc[c];
         }
+        __syncthreads();
+        const int i = threadIdx.x;
+        if (i < 128 && 128 * bi + i < Mpad)
+            a.bpart[((size_t)slot * 2 + o) * Mpad + 128 * bi + i] = (bs[i] + bs[128 + i]) + (bs[256 + i] + bs[384 + i]);
     }
     // epilogue: sum_ij P_ij dA_ij/dtheta over the wave's tiles (both triangles of a
     // diagonal block; off-diagonal blocks stand for their mirror image too)
@@ -657,16 +856,51 @@ __global__ __launch_bounds__(kThreads) void grad_final_kernel(GradArgs a, int ns
     if (tid == 0) a.dlog_ell[o * 4 + t] = (float)(direct + mat - bt);
 }
 
+int grad_split_capacity(int Mpad) {
+    const size_t lds = grad_forward_lds(Mpad);
+    int dev = 0, ncu = 0, per_cu = 0;
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(grad_forward_kernel),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(grad_forward_kernel),
+                                                     kThreads, lds) != hipSuccess)
+        return 0;
+    return per_cu * ncu;
+}
+
+static hipError_t launch_forward(const GradArgs &a, ForwardMode mode, hipStream_t st) {
+    const size_t lds = grad_forward_lds(a.gp.Mpad);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(grad_forward_kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    const int nwg = (a.K + kB - 1) / kB;
+    hipLaunchKernelGGL(grad_forward_kernel, dim3(mode == kForwardSplit ? 2 * nwg : nwg), dim3(kThreads), lds, st, a,
+                       (int)mode);
+    return hipGetLastError();
+}
+
 hipError_t launch_grad(const GradArgs &a, hipStream_t st) {
+    hipError_t e;
+    if (a.split) {
+        const int nwg = (a.K + kB - 1) / kB;
+        if (!a.xrec || !a.repair || 2 * nwg > grad_split_capacity(a.gp.Mpad)) return hipErrorInvalidValue;
+        const size_t n_rec = (size_t)nwg * kGradXchPerBlock;   // > nwg
+        hipLaunchKernelGGL(grad_clear_kernel, dim3((unsigned)((n_rec + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
+                           a.xrec, n_rec, a.repair, nwg);
+        if ((e = launch_forward(a, kForwardSplit, st)) != hipSuccess) return e;
+        if ((e = launch_forward(a, kForwardRepair, st)) != hipSuccess) return e;   // the repair launch
+    } else if ((e = launch_forward(a, kForwardWhole, st)) != hipSuccess) {
+        return e;
+    }
     const int nblk = (a.Kc + 63) / 64;
     const int lds = grad_gp_lds(a.gp.Mpad);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(grad_gp_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
+    if ((e = hipFuncSetAttribute(reinterpret_cast<const void *>(grad_gp_kernel),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds)) != hipSuccess)
+        return e;
     for (int c = 0; c < a.nchunk; ++c) {
         const int kc = a.K - c * a.Kc < a.Kc ? a.K - c * a.Kc : a.Kc;
         const long long N = (long long)a.T * kc;
-        hipLaunchKernelGGL(grad_cov_kernel, dim3(nblk), dim3(64), 0, st, a, c);
         hipLaunchKernelGGL(grad_stage_kernel, dim3((kc + 255) / 256, a.T), dim3(256), 0, st, a, c);
         hipLaunchKernelGGL(grad_gp_kernel, dim3((unsigned)((N + kGpRows - 1) / kGpRows), 2), dim3(64 * kGpWaves), lds, st, a, c);
         hipLaunchKernelGGL(grad_back_kernel, dim3(nblk), dim3(64), 0, st, a, c);

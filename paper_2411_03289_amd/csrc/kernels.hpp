@@ -207,10 +207,18 @@ struct GradArgs {
     float inv_tau, inv_K;
     const float4 *q32;       // dense packed Q per output
     long long q_stride;      // float4 per output
+    const float *x0;         // [5]
     const float *U;          // [T][2]
-    const float *x, *u, *s2; // the rollout's trace: states [T+1][5][K], controls [T][2][K], variances [T][2][K]
+    float *x, *u, *s2;       // forward pass: states [T+1][5][K], controls [T][2][K], variances [T][2][K]
+    float *cov;              // [T][15][K] Sigma_{k+1}
+    // its output split: exchange records [ceil(K / 32)][kGradXchPerBlock], zeroed with the repair marks
+    // before each split launch
+    int split;
+    unsigned long long *xrec;
+    uint32_t *repair;        // blocks for the repair launch
+    int xspin;               // polls per exchange wait before it gives up; < 0: give up at once
+    uint32_t *flags;         // context status word (GPMPPI_FLAG_EXCHANGE_TIMEOUT)
     float *costs;            // [K] smoothed costs
-    float *cov;              // chunk: [T][15][Kc] Sigma_{k+1}
     float *stage;            // chunk: [T][6][Kc] stage cost and its adjoint
     float *sums;             // chunk: [2][kGradSums][N]
     float *R;                // chunk: [2][N][Mpad] r = A^-1 k
@@ -223,12 +231,11 @@ struct GradArgs {
     double *ppart, *bterm;   // partial contractions
     float *J, *dU, *dlog_ell, *dlog_sf;   // outputs
 };
-constexpr int kGradSums = 19;   // per output, step and sample (see grad_gp_kernel)
-// The gradient's part behind the rollout that wrote its trace.
+constexpr int kGradSums = 18;   // per output, step and sample (see grad_gp_kernel)
+constexpr int kGradXchPerBlock = 2 * 4 * 2 * kSamplesPerBlock;   // split exchange records per block
+// Workgroups of the split forward pass resident at once (a launch needs 2 ceil(K / 32)).
+int grad_split_capacity(int Mpad);
 hipError_t launch_grad(const GradArgs &a, hipStream_t st);
-// Zeroes a split rollout's exchange records [n_rec], epoch words [2] and repair marks [n_blk].
-hipError_t launch_exchange_clear(unsigned long long *rec, size_t n_rec, uint32_t *xep, uint32_t *repair, int n_blk,
-                                 hipStream_t st);
 
 // Q = A^-1 = W^T W of output o packed dense (FP32 operand order).
 hipError_t pack_q(const GpBuildBuffers &b, int M, int Mpad, int o, float4 *q32, hipStream_t st);

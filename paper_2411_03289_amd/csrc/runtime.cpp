@@ -1236,8 +1236,8 @@ struct GradLayout {
     int Kc = 0, nchunk = 1;   // samples per chunk
     int npairs = 0, nsplit = 0, nbterm = 0;
     size_t o_x = 0, o_u = 0, o_s2 = 0, o_c = 0, o_cov = 0, o_st = 0, o_sum = 0, o_R = 0, o_w = 0, o_b = 0, o_h = 0,
-           o_up = 0, o_p = 0, o_bt = 0, o_rec = 0, o_ep = 0, o_rp = 0;
-    size_t n_rec = 0;         // the split rollout's exchange records (0: unsplit)
+           o_up = 0, o_p = 0, o_bt = 0, o_rec = 0, o_rp = 0;
+    int split = 0;            // two workgroups per 32 samples, one per GP output (when they fit the device at once)
     size_t bytes = 0;
 };
 
@@ -1282,7 +1282,7 @@ GradLayout grad_layout(const gpmppi_ctx *c, int Kc) {
     g.o_u = take(2 * TK);
     g.o_s2 = take(2 * TK);
     g.o_c = take((size_t)K);
-    g.o_cov = take(15 * N);
+    g.o_cov = take(15 * TK);
     g.o_st = take(6 * N);
     g.o_sum = take(2 * kGradSums * N);
     g.o_R = take(2 * N * Mpad);
@@ -1292,15 +1292,11 @@ GradLayout grad_layout(const gpmppi_ctx *c, int Kc) {
     g.o_up = take(nblk * T * 2);
     g.o_p = take(2 * nslot * g.npairs * 4 * 2);
     g.o_bt = take((size_t)2 * g.nbterm * 4 * 2);
-    // The rollout's output split where the streamed walk over W bounds a step and the doubled
-    // grid fits (see set_grad_split); a caller that makes every exchange wait give up gets the exchange
-    // at every size.
-    if (c->grad_split && (Mpad > 256 || c->xspin < 0) && K <= rollout_split_capacity(GPMPPI_FP32, Mpad, 8)) {
-        const size_t nb32 = (size_t)((K + 31) / 32);
-        g.n_rec = nb32 * kXchRecPerBlock;
-        g.o_rec = take(2 * g.n_rec);
-        g.o_ep = take(2);
-        g.o_rp = take(nb32);
+    const size_t nwg = (size_t)((K + 31) / 32);
+    g.split = c->grad_split && 2 * (long long)nwg <= grad_split_capacity(Mpad) ? 1 : 0;
+    if (g.split) {
+        g.o_rec = take(nwg * kGradXchPerBlock * 2);   // 64-bit exchange records
+        g.o_rp = take(nwg);
     }
     return g;
 }
@@ -1338,29 +1334,12 @@ gpmppi_status grad_check(const gpmppi_ctx *c, const float *x0_d, const float *U_
     return GPMPPI_OK;
 }
 
-// Enqueues the rollout, the adjoint recursion and the reductions with the workspace at ws (device
+// Enqueues the forward pass, the adjoint recursion and the reductions with the workspace at ws (device
 // memory of at least g.bytes; no part of it needs to start at zero).
 gpmppi_status grad_enqueue(const gpmppi_ctx *c, const GradLayout &g, char *ws, const float *x0_d, const float *U_d,
                            uint64_t seed, double tau, float *J_d, float *dU_d, float *dlog_ell_d, float *dlog_sf_d,
                            float *costs_d, hipStream_t stream) {
     auto f32 = [&](size_t at) { return reinterpret_cast<float *>(ws + at); };
-    gpmppi_trace tr{};
-    tr.x_d = f32(g.o_x);
-    tr.u_d = f32(g.o_u);
-    tr.gp_var_d = f32(g.o_s2);
-    RolloutArgs ra = rollout_args(c, x0_d, U_d, seed, f32(g.o_c), &tr, nullptr);
-    ra.geo.path_kind = 0;   // its costs are not used: no track, no obstacles
-    ra.geo.P = 0;
-    ra.geo.n_obs = 0;
-    ra.rotate = 1;
-    if (g.n_rec) {
-        ra.xrec = reinterpret_cast<unsigned long long *>(ws + g.o_rec);
-        ra.xep = reinterpret_cast<uint32_t *>(ws + g.o_ep);
-        ra.repair = reinterpret_cast<uint32_t *>(ws + g.o_rp);
-        HIP_TRY(launch_exchange_clear(ra.xrec, g.n_rec, ra.xep, ra.repair, (c->params.K + 31) / 32, stream));
-    }
-    HIP_TRY(launch_rollout(ra, GPMPPI_FP32, g.n_rec ? 1 : rollout_groups(GPMPPI_FP32, c->Mpad), 8, g.n_rec ? 1 : 0,
-                           stream));
     GradArgs a{};
     a.gp = c->gp;
     a.geo = c->geo;
@@ -1378,9 +1357,17 @@ gpmppi_status grad_enqueue(const gpmppi_ctx *c, const GradLayout &g, char *ws, c
     a.q32 = c->q32;
     a.q_stride = c->q_stride;
     a.U = U_d;
-    a.x = tr.x_d;
-    a.u = tr.u_d;
-    a.s2 = tr.gp_var_d;
+    a.x0 = x0_d;
+    a.x = f32(g.o_x);
+    a.u = f32(g.o_u);
+    a.s2 = f32(g.o_s2);
+    a.split = g.split;
+    if (g.split) {
+        a.xrec = reinterpret_cast<unsigned long long *>(ws + g.o_rec);
+        a.repair = reinterpret_cast<uint32_t *>(ws + g.o_rp);
+    }
+    a.xspin = c->xspin;
+    a.flags = c->flags;
     a.costs = costs_d ? costs_d : f32(g.o_c);
     a.cov = f32(g.o_cov);
     a.stage = f32(g.o_st);
