@@ -46,8 +46,8 @@ KERNEL_SOURCES = ["paper_2411_03289_amd/csrc/rollout.hip", "paper_2411_03289_amd
                   "paper_2411_03289_amd/csrc/device_common.hpp", "paper_2411_03289_amd/csrc/kernels.hpp",
                   "paper_2411_03289_amd/build.py"]
 MEASURED_TRAFFIC = {
-    "sources_sha256": "a72eb1d1f2c032ffa9a030427f2227d9d75c1140237250617ac89c67ff200e67",
-    "bytes": {"fp32": 510947.875 * 1024, "bf16x3": 2082751.375 * 1024, "bf16": 18564.0 * 1024},
+    "sources_sha256": "6ee4b7aab371759373feb1517ed624b87bb64040a2900da50218ff215e704576",
+    "bytes": {"fp32": 2520061.25 * 1024, "bf16x3": 2584617.75 * 1024, "bf16": 18564.0 * 1024},
 }
 
 

@@ -21,7 +21,7 @@ using namespace core;
 // record per sample: a record is valid once its tag names this launch's epoch
 // and the step, so no flag and no store-completion wait is needed.  Slots cycle
 // over four steps (a writer runs at most two steps ahead of a slot's reader).
-// The values reach the same arithmetic as in rollout_block, so the results are
+// The values reach the same arithmetic as in rollout_core, so the results are
 // bitwise those of the unsplit kernel.  The launcher admits the shape only
 // where the whole doubled grid fits the device at once, but other work on the
 // device can still keep one role waiting: every wait is bounded

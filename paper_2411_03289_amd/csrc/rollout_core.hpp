@@ -52,11 +52,14 @@
 // generation, contraction, constraint loops and state update one after another, with FP32
 // operands in the FP32 form):
 //   K     T    M     form     before    now      bound now
-//   256   50   50    FP32     219 us    63 us    the pose/covariance chain, 2900 cycles a step
-//   1024  100  300   FP32     2089 us   345 us   W streamed per 16 samples, constraint loops
-//   4096  60   128   BF16x3   954 us    271 us   vector instructions of k and the loops
-//   16384 100  1024  BF16x3   9603 us   9341 us  W from L2, some 52 bytes a clock per CU
-//   16384 100  1024  FP32     26.4 ms   10.5 ms  the same
+//   256   20   50    FP32     219 us    63 us    the pose and covariance chain, 3 us a step
+//   2500  40   300   FP32     2086 us   345 us   W streamed per 16 samples, vector work of k
+//   2048  30   256   FP32 (*) 1951 us   311 us   the chain, twice (nominal sequence first)
+//   4096  50   256   BF16x3   953 us    272 us   vector work of k beside the products, 5 us a step
+//   16384 100  1024  BF16x3   10.2 ms   9.6 ms   W from L2, some 52 bytes a clock per CU
+//   16384 100  1024  FP32     26.6 ms   10.6 ms  the same
+// (*) three terrains, tightening along the nominal sequence.  Over 12 seeds of the last, the
+// error of the weights against 64 bits went from 4.8e-6 to 3.7e-6 (mean), of U from 9.1e-7 to 7.4e-7.
 #pragma once
 #include "core_step.hpp"
 #include "device_common.hpp"
