@@ -33,7 +33,7 @@
 // The samples are taken in chunks where the workspace (8 Mpad + 280 bytes per (k, s)) is
 // limited; a (k, s)'s results do not depend on its chunk.
 //
-// Measured, K = 4096, T = 50, M = 512: 7.6 ms -> 5.2 ms; K = 256, T = 20, M = 200: 0.94 ms ->
+// Measured, K = 4096, T = 50, M = 512: 7.6 ms -> 4.3 ms; K = 256, T = 20, M = 200: 0.94 ms ->
 // 0.36 ms.  Before, one kernel ran everything inside the recursion (its r = Q k once
 // per reversed step, its variance twice per step: forward and again from checkpoints).
 #include "adjoint_step.hpp"
