@@ -118,7 +118,7 @@ struct CoreShape {
     int G, layout;
 };
 CoreShape core_shape(int precision, int Mpad, int K, int groups, int cus);
-CoreShape batch_shape(int Mpad, bool big);
+CoreShape batch_shape(int precision, int Mpad, bool big);
 int core_lds(int precision, int Mpad, CoreShape s);   // dynamic LDS of a workgroup
 // The BF16 form's kernels (rollout_bf16.hip): G sample groups of 32 and NW waves per workgroup.
 size_t rollout_bf16_lds(int G, int Mpad);

@@ -120,7 +120,7 @@ __device__ __forceinline__ void rollout_block_split(const RolloutArgs &a, int bl
         return gp_mean_of(mp, B, sl);
     };
     WFrag<PREC> none[1];   // every block of W streams from L2 each step
-    UnitCursor first;
+    UnitCursor<true> first;
     resident_load<PREC, 0>(none, wt, first, ul);
     auto contract = [&]() {
         walk_units<PREC, G, 0, true>(wt, none, first, lane, ul, lds, role, NT, rs, vp - role * NT * B);
@@ -287,7 +287,7 @@ typedef const RolloutArgs __attribute__((address_space(4))) ConstRolloutArgs;
 // (problem, sample block) items from a shared counter until the list (sorted
 // longest first) is exhausted.  Results do not depend on which workgroup
 // runs an item.  *counter must be 0 at launch.  Problems whose whole layout fits run
-// 32-sample blocks of it; GS > 0: the others run blocks of 16 GS samples of the sweep
+// 32-sample blocks of it; GS > 0: the others run blocks of 16 GS samples of the serial or sweep
 // layout.
 template <int PREC, int GS>
 __global__ __launch_bounds__(64 * kCoreWaves) void rollout_batch_kernel(ConstRolloutArgs *probs, const int2 *items,
@@ -307,7 +307,11 @@ __global__ __launch_bounds__(64 * kCoreWaves) void rollout_batch_kernel(ConstRol
         if (a.gp.NT <= kResidentTiles) {
             rollout_core<PREC, 2, kWholeResident>(a, b, lds);
         } else {
-            if constexpr (GS > 0) rollout_core<PREC, GS, kSweep>(a, b, lds);
+            if constexpr (GS == 2) rollout_core<PREC, 2, kSerial>(a, b, lds);
+            if constexpr (GS == 4) {
+                if (a.gp.NT <= serial_tiles<PREC>()) rollout_core<PREC, 4, kSerial>(a, b, lds);
+                else rollout_core<PREC, 4, kSweep>(a, b, lds);
+            }
         }
     }
 }
@@ -371,6 +375,13 @@ static hipError_t set_lds(F *fn, size_t bytes) {
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
+// The block of more row tiles than the whole layouts hold.
+template <int PREC>
+static CoreShape long_shape(int NT, bool big) {
+    if (!big) return CoreShape{2, kSerial};
+    return CoreShape{4, NT <= serial_tiles<PREC>() ? kSerial : kSweep};
+}
+
 // The block of one problem: the smallest that still gives every compute unit at most one
 // workgroup, as the horizon is a serial chain and a block's step gets longer with its
 // samples; 64 samples where the blocks outnumber the compute units anyway.  big: 64-sample
@@ -378,11 +389,11 @@ static hipError_t set_lds(F *fn, size_t bytes) {
 template <int PREC>
 static CoreShape core_shape_t(int NT, int K, bool big, int cus) {
     const int whole = NT <= kResidentTiles ? kWholeResident : kWholeStream;
-    const bool w1 = core_plan<PREC, 1, false>(NT).bytes <= kCoreLdsMax;
+    const bool w1 = core_plan<PREC, 1, kWholeStream>(NT).bytes <= kCoreLdsMax;
     const long long n16 = (K + 15) / 16;
     if (w1 && n16 <= cus) return CoreShape{1, whole};
     if (whole == kWholeResident) return CoreShape{2, whole};
-    return CoreShape{big && n16 > 2LL * cus ? 4 : 2, kSweep};
+    return long_shape<PREC>(NT, big && n16 > 2LL * cus);
 }
 
 CoreShape core_shape(int precision, int Mpad, int K, int groups, int cus) {
@@ -391,17 +402,19 @@ CoreShape core_shape(int precision, int Mpad, int K, int groups, int cus) {
                                     : core_shape_t<GPMPPI_BF16X3>(Mpad / 32, K, big, cus);
 }
 
-// A batched problem's block (see rollout_batch_kernel); big: the batch's sweep blocks hold
-// 64 samples.
-CoreShape batch_shape(int Mpad, bool big) {
+// A batched problem's block (see rollout_batch_kernel); big: the batch's blocks of more than
+// kResidentTiles row tiles hold 64 samples.
+CoreShape batch_shape(int precision, int Mpad, bool big) {
     if (Mpad / 32 <= kResidentTiles) return CoreShape{2, kWholeResident};
-    return CoreShape{big ? 4 : 2, kSweep};
+    return precision == GPMPPI_FP32 ? long_shape<GPMPPI_FP32>(Mpad / 32, big) : long_shape<GPMPPI_BF16X3>(Mpad / 32, big);
 }
 
 template <int PREC>
 static int core_lds_t(int NT, CoreShape s) {
-    if (s.layout == kSweep) return s.G == 4 ? core_plan<PREC, 4, true>(NT).bytes : core_plan<PREC, 2, true>(NT).bytes;
-    return s.G == 1 ? core_plan<PREC, 1, false>(NT).bytes : core_plan<PREC, 2, false>(NT).bytes;
+    if (s.layout == kSweep) return core_plan<PREC, 4, kSweep>(NT).bytes;
+    if (s.layout == kSerial)
+        return s.G == 4 ? core_plan<PREC, 4, kSerial>(NT).bytes : core_plan<PREC, 2, kSerial>(NT).bytes;
+    return s.G == 1 ? core_plan<PREC, 1, kWholeStream>(NT).bytes : core_plan<PREC, 2, kWholeResident>(NT).bytes;
 }
 
 int core_lds(int precision, int Mpad, CoreShape s) {
@@ -413,7 +426,7 @@ static hipError_t launch_core(const RolloutArgs &args, hipStream_t st) {
     RolloutArgs a = args;
     int lds = core_lds_t<PREC>(a.gp.NT, CoreShape{G, LAYOUT});
     const long long world = 20LL * a.geo.P + 16LL * a.geo.n_obs;
-    a.world_lds = G == 1 && LAYOUT != kSweep && lds + world <= kCoreLdsMax;
+    a.world_lds = G == 1 && lds + world <= kCoreLdsMax;
     if (a.world_lds) lds += (int)world;
     if (lds > kCoreLdsMax) return hipErrorInvalidValue;
     hipError_t e = set_lds(rollout_kernel<PREC, G, LAYOUT>, lds);
@@ -425,7 +438,9 @@ static hipError_t launch_core(const RolloutArgs &args, hipStream_t st) {
 
 template <int PREC>
 static hipError_t launch_core_p(const RolloutArgs &a, CoreShape s, hipStream_t st) {
-    if (s.layout == kSweep) return s.G == 4 ? launch_core<PREC, 4, kSweep>(a, st) : launch_core<PREC, 2, kSweep>(a, st);
+    if (s.layout == kSweep) return launch_core<PREC, 4, kSweep>(a, st);
+    if (s.layout == kSerial)
+        return s.G == 4 ? launch_core<PREC, 4, kSerial>(a, st) : launch_core<PREC, 2, kSerial>(a, st);
     if (s.layout == kWholeStream) return launch_core<PREC, 1, kWholeStream>(a, st);
     return s.G == 1 ? launch_core<PREC, 1, kWholeResident>(a, st) : launch_core<PREC, 2, kWholeResident>(a, st);
 }
@@ -462,7 +477,7 @@ static hipError_t launch_rollout_split_t(const RolloutArgs &a, hipStream_t st) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // the repair launch: the unsplit kernel recomputes the blocks whose exchange gave up
-    return launch_core_p<PREC>(a, CoreShape{2, a.gp.NT <= kResidentTiles ? kWholeResident : kSweep}, st);
+    return launch_core_p<PREC>(a, CoreShape{2, a.gp.NT <= kResidentTiles ? kWholeResident : kSerial}, st);
 }
 
 template <int PREC>

@@ -21,12 +21,23 @@
 //   whole  one phase per step: both outputs' k in LDS at once, double-buffered; the
 //          row tiles of W of both outputs are dealt to the waves longest first.  Up to
 //          256 points all of W stays in registers over the horizon (nine 32x32 blocks a
-//          wave), so a step reads nothing from memory; up to 448 points five blocks do
-//          and the rest come through a four-deep ring
+//          wave), so a step reads nothing from memory; up to 448 points (BF16x3 form 576)
+//          five blocks do and the rest come through a four-deep ring
+//   serial two phases per step, one per output: all of its k into LDS, a barrier, its row
+//          tiles dealt to the waves, W through the four-deep ring.  Nothing of the vector
+//          work is hidden, but W streams without a pause: 41K of the 34K cycles a wave's share
+//          of 1024 points takes at the 64 bytes a clock of a compute unit's L1.  32 samples up
+//          to 1024 points, 64 where their k fits LDS (448 points, BF16x3 form 512).  Odd steps
+//          take the outputs in the opposite order: one output's W stays in the XCD's 4 MB of
+//          L2 from step to step, both (4.3 MB at 1024 points) would not
 //   sweep  chunks of eight column tiles of one output; every wave keeps the
 //          accumulators of all its row tiles over the chunks, so LDS holds two chunks
 //          only and a block may own 64 samples at M_pad = 1024 (W is streamed once
 //          per 64 samples instead of once per 32)
+// A step of the serial layout against one of 32-sample blocks in chunks of the sweep's kind (two
+// blocks of W in flight per wave and a barrier every sixteen): K = 512, M = 1024 47 us against 68
+// (BF16x3; 48 against 71 FP32), K = 2048, M = 700 25 against 38.  64 samples, K = 9000, M = 500:
+// 30 against 35 (BF16x3).
 //
 // Sums are grouped the same way in every layout, block size and wave count, so
 // results do not depend on them (bit for bit):
@@ -95,6 +106,20 @@ template <int PREC>
 struct WFrag {
     uint4 h[2];
     uint4 l[2];
+    __device__ __forceinline__ void pin() {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            pin_word(h[s]);
+            pin_word(l[s]);
+        }
+    }
+    static __device__ __forceinline__ void pin_word(uint4 &x) {
+        typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+        v4u t;
+        __builtin_memcpy(&t, &x, 16);
+        __asm__ __volatile__("" : "+v"(t));
+        __builtin_memcpy(&x, &t, 16);
+    }
 };
 
 __device__ __forceinline__ int wfrag_voff(int lane) {
@@ -144,15 +169,27 @@ __device__ __forceinline__ void kterm_load(KTerm<PREC> &k, const unsigned char *
     k.l = K[64];
 }
 
-// acc[s] += W block . k tile of one group.
-template <int PREC>
-__device__ __forceinline__ void group_mma(v4f &a0, v4f &a1, const WFrag<PREC> &f, const KTerm<PREC> &k) {
-    a0 = mma16<PREC>(f.h[0], k.h, a0);
-    a1 = mma16<PREC>(f.h[1], k.h, a1);
-    a0 = mma16<PREC>(f.h[0], k.l, a0);
-    a1 = mma16<PREC>(f.h[1], k.l, a1);
-    a0 = mma16<PREC>(f.l[0], k.h, a0);
-    a1 = mma16<PREC>(f.l[1], k.h, a1);
+// acc[s][g0 ..] += W block . k tile of N groups.  A product's sum waits for the one before it: term by
+// term, the two halves of every group lie between two products of one sum.
+template <int PREC, int N, int G>
+__device__ __forceinline__ void groups_mma(v4f (&acc)[2][G], int g0, const WFrag<PREC> &f, const KTerm<PREC> *k) {
+#pragma unroll
+    for (int term = 0; term < 3; ++term)
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+                acc[s][g0 + i] = mma16<PREC>(term == 2 ? f.l[s] : f.h[s], term == 1 ? k[i].l : k[i].h, acc[s][g0 + i]);
+}
+
+// Sum of a wave's four quarters, halves first (every quarter gets it), by exchanges between
+// registers: through LDS each of the two steps would wait some hundred cycles.
+__device__ __forceinline__ float quarter_sum(float x) {
+    const uint32_t a = __float_as_uint(x);
+    const auto h = __builtin_amdgcn_permlane32_swap(a, a, false, false);
+    const uint32_t b = __float_as_uint(__uint_as_float(h[0]) + __uint_as_float(h[1]));
+    const auto q = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+    return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
 
 // Sum of squares over a finished row tile's 32 rows, per sample (every quarter-wave
@@ -170,10 +207,7 @@ __device__ __forceinline__ float tile_sq(const v4f &a0, const v4f &a1, const v4f
         }
         q[s] = fmaf(a[3], a[3], fmaf(a[2], a[2], fmaf(a[1], a[1], a[0] * a[0])));
     }
-    float t = q[0] + q[1];
-    t += shfl_xor(t, 32);
-    t += shfl_xor(t, 16);
-    return t;
+    return quarter_sum(q[0] + q[1]);
 }
 
 // The eight class sums, added pairwise.
@@ -322,13 +356,6 @@ __device__ __forceinline__ void gen_octet(const GenIn<PREC> &t, const GenQ<PREC>
     store_octet<PREC>(kt, lane, kv);
 }
 
-// Sum of a class's four octet chains (every quarter-wave gets it).
-__device__ __forceinline__ float octet_sum(float ms) {
-    ms += shfl_xor(ms, 32);
-    ms += shfl_xor(ms, 16);
-    return ms;
-}
-
 // The query scaled by the lengthscales.  Contraction is off: fused into the differences
 // of kval32, the product would not be rounded, depending on the code in between.
 __device__ __forceinline__ void scaled_query(const GpCore &g, int o, const float q[4], float qs[4]) {
@@ -337,25 +364,29 @@ __device__ __forceinline__ void scaled_query(const GpCore &g, int o, const float
     for (int d = 0; d < 4; ++d) qs[d] = q[d] * g.scale[o][d];
 }
 
-// One tile for the G groups: group i's query comes from the lanes of its samples (lane l
-// holds sample l % (16 G), scaled query qs).  inputs(in) gives the tile's inputs, for each
-// group anew: where they come from LDS, reading them again is cheaper than keeping
-// forty registers for them.
-template <int PREC, int G, class Inputs>
-__device__ __forceinline__ void gen_tile16(const Inputs &inputs, const float qs[4], unsigned char *kt, int lane,
-                                           float (&ms)[G]) {
+// The queries of the G groups: group i's from the lanes of its samples (lane l holds sample
+// l % (16 G), scaled query qs).
+template <int PREC, int G>
+__device__ __forceinline__ void gen_queries(GenQ<PREC> (&gq)[G], const float qs[4], int lane) {
     float qg[G][4];   // gathered together: one LDS round trip
 #pragma unroll
     for (int i = 0; i < G; ++i)
 #pragma unroll
         for (int d = 0; d < 4; ++d) qg[i][d] = G == 1 ? qs[d] : __shfl(qs[d], 16 * i + (lane & 15), 64);
 #pragma unroll
+    for (int i = 0; i < G; ++i) gen_query<PREC>(gq[i], qg[i], lane);
+}
+
+// One tile for the G groups.  inputs(in) gives the tile's inputs, for each group anew: where they
+// come from LDS, reading them again is cheaper than keeping forty registers for them.
+template <int PREC, int G, class Inputs>
+__device__ __forceinline__ void gen_tile16(const Inputs &inputs, const GenQ<PREC> (&gq)[G], unsigned char *kt, int lane,
+                                           float (&ms)[G]) {
+#pragma unroll
     for (int i = 0; i < G; ++i) {
         GenIn<PREC> in;
         inputs(in);
-        GenQ<PREC> gq;
-        gen_query<PREC>(gq, qg[i], lane);
-        gen_octet<PREC>(in, gq, kt + i * kTerms * 1024, lane, ms[i]);
+        gen_octet<PREC>(in, gq[i], kt + i * kTerms * 1024, lane, ms[i]);
     }
 }
 
@@ -366,19 +397,29 @@ template <int PREC, int G, int NW, class Load>
 __device__ __forceinline__ void gen_output(const GpCore &g, int o, const float q[4], int wv, int lane, unsigned char *kb,
                                            float *mr, GenIn<PREC> &in, const Load &load) {
     constexpr int B = 16 * G, S = kTerms;
+    constexpr bool kAhead = PREC != GPMPPI_FP32;   // the next tile's inputs (sixteen registers) load beside this one
     float qs[4];
     scaled_query(g, o, q, qs);
+    GenQ<PREC> gq[G];
+    gen_queries<PREC, G>(gq, qs, lane);
+    GenIn<PREC> next = in;
     for (int cl = wv; cl < kClasses; cl += NW) {
         float ms[G];
 #pragma unroll
         for (int i = 0; i < G; ++i) ms[i] = 0.0f;
         for (int jt = cl; jt < g.NT; jt += kClasses) {
-            if (jt != wv) load(in, jt);
-            gen_tile16<PREC, G>([&](GenIn<PREC> &t) { t = in; }, qs, kb + jt * (G * S * 1024), lane, ms);
+            if constexpr (kAhead) {
+                in = next;
+                const int jn = jt + kClasses < g.NT ? jt + kClasses : cl + NW;
+                if (jn < g.NT) load(next, jn);
+            } else if (jt != wv) {
+                load(in, jt);
+            }
+            gen_tile16<PREC, G>([&](GenIn<PREC> &t) { t = in; }, gq, kb + jt * (G * S * 1024), lane, ms);
         }
 #pragma unroll
         for (int i = 0; i < G; ++i) {
-            const float t = octet_sum(ms[i]);
+            const float t = quarter_sum(ms[i]);
             if (lane < 16) mr[cl * B + 16 * i + lane] = t;
         }
     }
@@ -444,28 +485,30 @@ struct CorePlan {
     int ns;                                    // steps per half of the noise table
 };
 
-// The sweep layout of 64-sample blocks keeps one copy of each small array instead of two
-// by step parity (it has at least four phases per step to separate writers and readers).
-template <int G, bool SWEEP>
-__host__ __device__ constexpr int core_parities() { return SWEEP && G == 4 ? 1 : 2; }
+enum CoreLayout { kWholeResident = 0, kWholeStream = 1, kSweep = 2, kSerial = 3 };
 
-template <int PREC, int G, bool SWEEP>
+// The whole layouts keep two copies of each small array by step parity; in the others the phases of
+// a step separate writers and readers.
+constexpr int core_parities(int layout) { return layout == kSweep || layout == kSerial ? 1 : 2; }
+
+template <int PREC, int G, int LAYOUT>
 __host__ __device__ constexpr CorePlan core_plan(int NT) {
-    constexpr int B = 16 * G, NW = kCoreWaves, PP = core_parities<G, SWEEP>();
+    constexpr bool SWEEP = LAYOUT == kSweep, SERIAL = LAYOUT == kSerial;
+    constexpr int B = 16 * G, NW = kCoreWaves, PP = core_parities(LAYOUT);
     CorePlan p{};
     p.ns = G == 1 ? 16 : G == 2 ? 8 : 2;
-    p.kbuf = (SWEEP ? kSweepTiles : 2 * NT) * G * kTerms * 1024;
-    int off = 2 * p.kbuf;
+    p.kbuf = (SWEEP ? kSweepTiles : SERIAL ? NT : 2 * NT) * G * kTerms * 1024;
+    int off = (SERIAL ? 1 : 2) * p.kbuf;
     auto take = [&](int bytes) {
         const int at = off;
         off += (bytes + 15) / 16 * 16;
         return at;
     };
     p.rs = take(PREC == GPMPPI_FP32 && !SWEEP ? 2 * NT * 32 * 4 : 0);
-    // FP32 form: points and alpha, of both outputs (whole) or of two chunks (sweep)
-    p.z = take(PREC == GPMPPI_FP32 ? 2 * (SWEEP ? kSweepTiles : NT) * 32 * 20 : 0);
+    // FP32 form: points and alpha, of both outputs (whole) or of two chunks (sweep); serial: from memory
+    p.z = take(PREC == GPMPPI_FP32 && !SERIAL ? 2 * (SWEEP ? kSweepTiles : NT) * 32 * 20 : 0);
     p.mp = take(PP * 2 * kClasses * B * 4);
-    p.vp = take(PP * 2 * (SWEEP ? kClasses : NT) * B * 4);
+    p.vp = take((SERIAL ? 3 : PP * 2) * (SWEEP ? kClasses : NT) * B * 4);
     p.un = take(2 * p.ns * B * 8);
     p.geo = take(PP * 6 * B * 4);
     p.ps = take(16 * B * 4);
@@ -477,55 +520,61 @@ __host__ __device__ constexpr CorePlan core_plan(int NT) {
 
 constexpr int kCoreLdsMax = 160 * 1024;
 constexpr int kBatchLdsMax = kCoreLdsMax - 64;   // the batch kernel keeps its item in LDS too
-static_assert(core_plan<GPMPPI_FP32, 4, true>(32).bytes <= kBatchLdsMax, "64-sample blocks fit at M_pad = 1024");
+static_assert(core_plan<GPMPPI_FP32, 4, kSweep>(32).bytes <= kBatchLdsMax, "64-sample blocks fit at M_pad = 1024");
+// Row tiles up to which the serial layout of 64-sample blocks fits LDS (FP32 form 14, BF16x3 form 16).
+template <int PREC>
+__host__ __device__ constexpr int serial_tiles() {
+    int nt = 32;
+    while (core_plan<PREC, 4, kSerial>(nt).bytes > kBatchLdsMax) --nt;
+    return nt;
+}
+static_assert(core_plan<GPMPPI_FP32, 2, kSerial>(32).bytes <= kBatchLdsMax, "32-sample blocks fit at M_pad = 1024");
 
 // ---------------------------------------------------------------- contraction
 // Whole layout.  Units (output o, row tile t) of both outputs, t descending, are dealt
 // to the waves in snake order (a tile's work is t + 1 blocks, so the waves' totals
-// are within a block or two of each other); 8 bits per unit: t | o << 7.
+// are within a block or two of each other); 8 bits per unit: t | o << 7.  At most eight units
+// a wave (32 row tiles of one output over four waves, or of both over eight): one word, as a
+// choice of words would lie in scratch memory, whose read waits for every W block in flight.
 struct UnitList {
-    uint64_t w0, w1;   // up to sixteen units
+    uint64_t units;
     int n, blocks;
-    __device__ __forceinline__ int at(int i) const { return (int)(((i & 8) ? w1 : w0) >> (8 * (i & 7))) & 0xFF; }
+    __device__ __forceinline__ int at(int i) const { return (int)(units >> (8 * i)) & 0xFF; }
 };
 
 // NO outputs (2, or 1: output o1 only) over NW waves.
 template <int NW>
 __device__ __forceinline__ UnitList unit_list(int w, int NT, int NO, int o1, int rot) {
-    UnitList l{0, 0, 0, 0};
+    UnitList l{0, 0, 0};
     const int total = NO * NT;
     for (int r = 0; r * NW < total; ++r) {
         const int i = r * NW + ((r & 1) ? NW - 1 - w : w);
         if (i >= total) continue;
         const int t = NT - 1 - (NO == 2 ? i >> 1 : i), o = NO == 2 ? i & 1 : o1;
-        const uint64_t e = (uint64_t)(t | (o << 7));
-        if (l.n < 8) l.w0 |= e << (8 * l.n);
-        else l.w1 |= e << (8 * (l.n - 8));
+        l.units |= (uint64_t)(t | (o << 7)) << (8 * l.n);
         ++l.n;
         l.blocks += t + 1;
     }
     if (rot && l.n > 1) {   // start at a block-dependent unit
         const int s = rot % l.n;
-        UnitList q{0, 0, l.n, l.blocks};
-        for (int i = 0; i < l.n; ++i) {
-            const uint64_t e = (uint64_t)l.at((i + s) % l.n);
-            if (i < 8) q.w0 |= e << (8 * i);
-            else q.w1 |= e << (8 * (i - 8));
-        }
-        l = q;
+        uint64_t u = 0;
+        for (int i = 0; i < l.n; ++i) u |= (uint64_t)l.at((i + s) % l.n) << (8 * i);
+        l.units = u;
     }
-    auto uni = [](uint64_t x) {   // scalar registers for the cursors
-        return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)x) |
-               (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32;
-    };
-    return UnitList{uni(l.w0), uni(l.w1), __builtin_amdgcn_readfirstlane(l.n),
-                    __builtin_amdgcn_readfirstlane(l.blocks)};
+    // scalar registers for the cursors
+    const uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)l.units) |
+                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(l.units >> 32)) << 32;
+    return UnitList{u, __builtin_amdgcn_readfirstlane(l.n), __builtin_amdgcn_readfirstlane(l.blocks)};
 }
 
+// SCALAR: in scalar registers, whose branches cost less where the loop over the blocks is long;
+// the unrolled steps of the resident layout are 2 % faster without them.
+template <bool SCALAR>
 struct UnitCursor {
     int n, c, t, o, base;
     __device__ __forceinline__ void unit(const UnitList &l) {
-        const int e = n < l.n ? l.at(n) : 0;   // past the end: row tile 0 (a valid block)
+        int e = n < l.n ? l.at(n) : 0;   // past the end: row tile 0 (a valid block)
+        if constexpr (!SCALAR) __asm__ __volatile__("" : "+v"(e));
         t = e & 0x7F;
         o = e >> 7;
         const int u = t >> 1;
@@ -568,35 +617,36 @@ __device__ __forceinline__ void unit_finish(v4f (&acc)[2][G], int o, int t, int 
 // the whole horizon (res, loaded by resident_load); STREAM: the others run through a
 // register ring four blocks deep every step.  kb: tile (o, c) at ((o - o0) NT + c)
 // tile_bytes; sums of squares to vp[(o NT + t) B].
-template <int PREC, int RB>
-__device__ __forceinline__ void resident_load(WFrag<PREC> (&res)[RB ? RB : 1], const WTerms<PREC> &wt, UnitCursor &c,
-                                              const UnitList &ul) {
+template <int PREC, int RB, bool SCALAR>
+__device__ __forceinline__ void resident_load(WFrag<PREC> (&res)[RB ? RB : 1], const WTerms<PREC> &wt,
+                                              UnitCursor<SCALAR> &c, const UnitList &ul) {
     c.start(ul);
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
         wfrag_load<PREC>(res[i], wt, c.o, c.block());
         c.next(ul);
     }
+    // arrived here: or every step's first use would wait, and for the loads behind it
+#pragma unroll
+    for (int i = 0; i < RB; ++i) res[i].pin();
 }
 
 template <int PREC, int G, int RB, bool STREAM>
 __device__ __forceinline__ void walk_units(const WTerms<PREC> &wt, const WFrag<PREC> (&res)[RB ? RB : 1],
-                                           const UnitCursor &first, int lane, const UnitList &ul,
+                                           const UnitCursor<STREAM> &first, int lane, const UnitList &ul,
                                            const unsigned char *kb, int o0, int NT, const float *rs, float *vp) {
     constexpr int TB = G * kTerms * 1024;
     const int nb = ul.blocks;
     if (nb == 0) return;
     WFrag<PREC> ring[STREAM ? 4 : 1];
-    UnitCursor pc = first, mc;
+    UnitCursor<STREAM> pc = first, mc;
     auto fetch = [&](int r) {
         wfrag_load<PREC>(ring[r], wt, pc.o, pc.block());
         pc.next(ul);
     };
-    if constexpr (STREAM) {
-        if (nb > RB) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) fetch(r);
-        }
+    if constexpr (STREAM) {   // not only where blocks are left: on a way without these loads the waits below would
+#pragma unroll                // be for whatever the registers were loaded with last
+        for (int r = 0; r < 4; ++r) fetch(r);
     }
     v4f acc[2][G];
 #pragma unroll
@@ -606,7 +656,7 @@ __device__ __forceinline__ void walk_units(const WTerms<PREC> &wt, const WFrag<P
     mc.start(ul);
     KTerm<PREC> kc[G], kn[G];
     // k of the cursor's block (past the end the cursor stands on a valid tile)
-    auto kload = [&](KTerm<PREC> (&k)[G], const UnitCursor &c) {
+    auto kload = [&](KTerm<PREC> (&k)[G], const UnitCursor<STREAM> &c) {
         const unsigned char *kt = kb + ((c.n < ul.n ? c.o - o0 : 0) * NT + c.c) * TB;
 #pragma unroll
         for (int g = 0; g < G; ++g) kterm_load<PREC>(k[g], kt + g * kTerms * 1024, lane);
@@ -615,8 +665,8 @@ __device__ __forceinline__ void walk_units(const WTerms<PREC> &wt, const WFrag<P
         const int t = mc.t, o = mc.o;
         const bool end = mc.next(ul);
         kload(kn, mc);
-#pragma unroll
-        for (int g = 0; g < G; ++g) group_mma<PREC>(acc[0][g], acc[1][g], f, kc[g]);
+        if constexpr (STREAM) __builtin_amdgcn_sched_barrier(0);   // not sunk behind the products, to its use
+        groups_mma<PREC, G>(acc, 0, f, kc);
         if (end) unit_finish<PREC, G>(acc, o, t, NT, lane, rs, vp);
 #pragma unroll
         for (int g = 0; g < G; ++g) kc[g] = kn[g];
@@ -626,14 +676,18 @@ __device__ __forceinline__ void walk_units(const WTerms<PREC> &wt, const WFrag<P
     for (int i = 0; i < RB; ++i)
         if (i < nb) block(res[i]);
     if constexpr (STREAM) {
-        for (int base = RB; base < nb; base += 4) {
-#pragma unroll
+        int base = RB;
+        for (; base + 4 <= nb; base += 4) {   // no way out inside a turn: it would come back to the loop's
+#pragma unroll                                // head with other loads last, and the wait there be for all of them
             for (int r = 0; r < 4; ++r) {
-                if (base + r >= nb) break;
                 block(ring[r]);
                 fetch(r);
+                __builtin_amdgcn_sched_barrier(0);   // two blocks' products together would wait for both
             }
         }
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+            if (base + r < nb) block(ring[r]);
     }
 }
 
@@ -739,9 +793,11 @@ struct Sweep {
                     const int c = c0 + q;
                     if (c < ncol) {
 #pragma unroll
-                        for (int g = 0; g < G; ++g) {
-                            group_mma<PREC>(acc[i][0][g], acc[i][1][g], ring[q], k[g]);
-                            kterm_load<PREC>(k[g], kb + (c + 1 < ncol ? (c + 1) * TB : 0) + g * KB, lane);
+                        for (int g = 0; g < G; g += 2) {
+                            groups_mma<PREC, 2>(acc[i], g, ring[q], k + g);
+#pragma unroll
+                            for (int e = g; e < g + 2; ++e)
+                                kterm_load<PREC>(k[e], kb + (c + 1 < ncol ? (c + 1) * TB : 0) + e * KB, lane);
                             __builtin_amdgcn_sched_barrier(0);   // not sunk to its use
                         }
                     }
@@ -785,15 +841,14 @@ constexpr int kResidentTiles = 8;
 template <bool STREAM>
 __host__ __device__ constexpr int resident_blocks() { return STREAM ? 5 : 9; }
 
-enum CoreLayout { kWholeResident = 0, kWholeStream = 1, kSweep = 2 };
-
 // Called by all threads of a workgroup of eight waves with core_plan's LDS.
 template <int PREC, int G, int LAYOUT>
 __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsigned char *lds) {
-    constexpr bool SWEEP = LAYOUT == kSweep, STREAM = LAYOUT == kWholeStream;
+    constexpr bool SWEEP = LAYOUT == kSweep, SERIAL = LAYOUT == kSerial, STREAM = LAYOUT == kWholeStream;
+    constexpr bool WHOLE = !SWEEP && !SERIAL;
     constexpr int B = 16 * G, S = kTerms, TB = G * S * 1024, NW = kCoreWaves;
-    constexpr int PM = core_parities<G, SWEEP>() - 1;   // step parity mask of the small arrays
-    constexpr int RB = SWEEP ? 0 : resident_blocks<STREAM>();
+    constexpr int PM = core_parities(LAYOUT) - 1;   // step parity mask of the small arrays
+    constexpr int RB = WHOLE ? resident_blocks<STREAM>() : 0;
     constexpr bool kPoints = PREC == GPMPPI_FP32;
     constexpr int NS = NW - 2;   // waves that share the constraint loops
     int tid = threadIdx.x, lane = tid & 63, sl = lane % B, sg = blk * B + sl;
@@ -802,7 +857,7 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
     const GpCore &gp = a.gp;
     const Geometry &geo = a.geo;
     const Dyn dy = a.dyn;
-    const CorePlan pl = core_plan<PREC, G, SWEEP>(NT);
+    const CorePlan pl = core_plan<PREC, G, LAYOUT>(NT);
     // The thread index, opaque from here on: called in every phase, so that the many addresses
     // made from it are recomputed there instead of staying live across the whole horizon
     // (they cost some 60 registers).
@@ -814,7 +869,7 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
     };
     float *rs = reinterpret_cast<float *>(lds + pl.rs);
     float *mp = reinterpret_cast<float *>(lds + pl.mp);     // [parity][output][class][B]
-    float *vp = reinterpret_cast<float *>(lds + pl.vp);     // [parity][output][row tile or class][B]
+    float *vp = reinterpret_cast<float *>(lds + pl.vp);     // [parity][output][row tile or class][B]; serial: [3][row tile][B]
     float2 *un = reinterpret_cast<float2 *>(lds + pl.un);   // [half][ns][B] sampled controls
     float *gx = reinterpret_cast<float *>(lds + pl.geo);    // [parity][6][B] position, covariance, lambda_max
     float *ored = reinterpret_cast<float *>(lds + pl.ored); // [parity][2 NS][B]
@@ -844,7 +899,7 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
 
     const WTerms<PREC> wt = wterms<PREC>(gp, lane);
     const int nch = SWEEP ? (NT + kSweepTiles - 1) / kSweepTiles : 1;   // chunks per output
-    const int nph = SWEEP ? 2 * nch : 1;                                // phases per step
+    const int nph = WHOLE ? 1 : 2 * nch;                                // phases per step
 
     // points of the FP32 form.  Whole: both outputs for the whole horizon, z [2][Mpad] then
     // alpha [2][Mpad].  Sweep: two chunks, each z [256] then alpha [256], refilled two phases
@@ -863,7 +918,10 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
     };
 
     noise_fill(0);
-    if constexpr (kPoints && !SWEEP) {
+    if constexpr (kPoints && SERIAL) {
+        for (int i = tid; i < 2 * NT * 32; i += 64 * NW) rs[i] = gp.wrs[i];
+    }
+    if constexpr (kPoints && WHOLE) {
         for (int i = tid; i < 2 * NT * 32; i += 64 * NW) {
             rs[i] = gp.wrs[i];
             zl[i] = reinterpret_cast<const v4f *>(gp.zs)[i];
@@ -907,13 +965,15 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
         a.trace.sxy_d[2 * K + sg] = 0.0f;
     }
 
-    UnitList ul{};
-    UnitCursor ufirst{};
+    UnitList ul{};   // serial: output 0's
+    UnitCursor<STREAM> ufirst{};
     WFrag<PREC> res[RB ? RB : 1];
     Sweep<PREC, G, NW> sw;
     if constexpr (SWEEP) {
         sw.init(w, NT);
         if (w >= NW / 2) sw.prefetch(0, 0, wt);
+    } else if constexpr (SERIAL) {
+        ul = unit_list<NW>(w, NT, 1, 0, 0);
     } else {
         ul = unit_list<NW>(w, NT, 2, 0, 0);
         resident_load<PREC, RB>(res, wt, ufirst, ul);
@@ -925,7 +985,13 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
     auto generate = [&](int ks, int j, unsigned char *kb) {
         float *mrow = mp + (ks & PM) * 2 * kClasses * B;
         const float q[4] = {v, w_, u.x, u.y};
-        if constexpr (SWEEP) {
+        if constexpr (SERIAL) {
+            const int o = j ^ (ks & 1), wv = j ? NW - 1 - w : w;
+            GenIn<PREC> in;
+            if (wv < NT) gen_load<PREC>(in, gp, o, wv, lane);
+            gen_output<PREC, G, NW>(gp, o, q, wv, lane, kb, mrow + o * kClasses * B, in,
+                                    [&](GenIn<PREC> &t, int jt) { gen_load<PREC>(t, gp, o, jt, lane); });
+        } else if constexpr (SWEEP) {
             const int o = j >= nch, ca = (j - o * nch) * kSweepTiles, jt = sweep_tile(j), cl = jt - ca;
             if (ca == 0) {
 #pragma unroll
@@ -935,6 +1001,8 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
                 unsigned char *kt = kb + cl * TB;
                 float qs[4];
                 scaled_query(gp, o, q, qs);
+                GenQ<PREC> gq[G];
+                gen_queries<PREC, G>(gq, qs, lane);
                 if constexpr (kPoints) {
                     const v4f *zc = zl + (j & 1) * (kChunkPts + kChunkPts / 4);
                     gen_tile16<PREC, G>(
@@ -942,18 +1010,18 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
                             gen_load_points(t, zc + 32 * cl, reinterpret_cast<const float *>(zc + kChunkPts) + 32 * cl,
                                             lane);
                         },
-                        qs, kt, lane, msw);
+                        gq, kt, lane, msw);
                 } else {
                     GenIn<PREC> in;
                     gen_load<PREC>(in, gp, o, jt, lane);
-                    gen_tile16<PREC, G>([&](GenIn<PREC> &t) { t = in; }, qs, kt, lane, msw);
+                    gen_tile16<PREC, G>([&](GenIn<PREC> &t) { t = in; }, gq, kt, lane, msw);
                 }
             }
             if (ca + kSweepTiles >= NT) {
                 float *mr = mrow + (o * kClasses + cl) * B;
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
-                    const float t = octet_sum(msw[g]);
+                    const float t = quarter_sum(msw[g]);
                     if (lane < 16) mr[16 * g + lane] = t;
                 }
             }
@@ -975,7 +1043,9 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
                 auto tile = [&](int o, int jt, float (&ms)[G]) {
                     float qs[4];
                     scaled_query(gp, o, q, qs);
-                    gen_tile16<PREC, G>([&](GenIn<PREC> &t) { t = in[o]; }, qs, kb + (o * NT + jt) * TB, lane, ms);
+                    GenQ<PREC> gq[G];
+                    gen_queries<PREC, G>(gq, qs, lane);
+                    gen_tile16<PREC, G>([&](GenIn<PREC> &t) { t = in[o]; }, gq, kb + (o * NT + jt) * TB, lane, ms);
                 };
                 if (t0 < NT) load(0, in[0], t0);
                 if (!kPoints && t1 < NT) load(1, in[1], t1);
@@ -984,7 +1054,7 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
                 if (t1 < NT) tile(1, t1, m1);
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
-                    const float a0 = octet_sum(m0[g]), a1 = octet_sum(m1[g]);
+                    const float a0 = quarter_sum(m0[g]), a1 = quarter_sum(m1[g]);
                     if (lane < 16) {
                         mrow[t0 * B + 16 * g + lane] = a0;
                         mrow[(kClasses + t1) * B + 16 * g + lane] = a1;
@@ -1007,6 +1077,9 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
             }
         }
     };
+    // Serial: the rows of vp of output o in step ks.  The outputs' turns take three places in rotation: a step's
+    // are read beside the next step's first turn.
+    auto serial_rows = [&](int ks, int o) { return vp + (2 * ks + (o ^ (ks & 1))) % 3 * NT * B; };
     // Variance contraction of chunk j of step ks.
     auto contract = [&](int ks, int j, const unsigned char *kb) {
         float *vrow = vp + (ks & PM) * 2 * VR * B;
@@ -1016,15 +1089,22 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
             if (w < NW / 2) sw.prefetch(o, ca / kSweepTiles, wt);   // the others fetched before the barrier
             sw.chunk(o, ca / kSweepTiles, kb, lane, wt);
             if (ca + kSweepTiles >= NT) sw.finish(gp, o, lane, vrow + o * VR * B);
+        } else if constexpr (SERIAL) {
+            const int o = j ^ (ks & 1);
+            const UnitList l{ul.units | (o ? 0x8080808080808080u : 0u), ul.n, ul.blocks};
+            UnitCursor<true> first;
+            first.start(l);
+            walk_units<PREC, G, 0, true>(wt, res, first, lane, l, kb, o, NT, rs, serial_rows(ks, o) - o * NT * B);
         } else {
             walk_units<PREC, G, RB, STREAM>(wt, res, ufirst, lane, ul, kb, 0, NT, rs, vrow);
         }
     };
     // Both outputs' variances of step ks.
     auto variances = [&](int ks, float &sa, float &sb) {
-        const float *r = vp + (ks & PM) * 2 * VR * B;
-        sa = gp_variance<PREC>(gp, 0, row_classes(r, VR, B, sl));
-        sb = gp_variance<PREC>(gp, 1, row_classes(r + VR * B, VR, B, sl));
+        const float *r = vp + (ks & PM) * 2 * VR * B, *r0 = SERIAL ? serial_rows(ks, 0) : r;
+        const float *r1 = SERIAL ? serial_rows(ks, 1) : r + VR * B;
+        sa = gp_variance<PREC>(gp, 0, row_classes(r0, VR, B, sl));
+        sb = gp_variance<PREC>(gp, 1, row_classes(r1, VR, B, sl));
     };
     // Step ks's constraint loops at its final position, by the six waves that carry neither
     // pose nor cost; 16-sample blocks read the geometry from LDS where it fits.
@@ -1035,13 +1115,13 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
         const float *r = gx + ((ks + 1) & PM) * 6 * B + sl;
         float *out = ored + ((ks + 1) & PM) * 2 * NS * B;
         const int wv = w < NW / 2 ? w : w - 1;
-        if (G == 1 && !SWEEP && a.world_lds)
+        if (G == 1 && WHOLE && a.world_lds)
             world_share<NS, B>(geo, wseg, winv, wobs, wv, lane, r[0], r[B], r[2 * B], r[3 * B], r[4 * B], r[5 * B], out,
                                true, true);
         else
             world_share<NS, B>(geo, wv, lane, r[0], r[B], r[2 * B], r[3 * B], r[4 * B], r[5 * B], out, true, true);
     };
-    if (G == 1 && !SWEEP && a.world_lds) {
+    if (G == 1 && WHOLE && a.world_lds) {
         for (int i = tid; i < geo.P; i += 64 * NW) {
             wseg[i] = reinterpret_cast<const v4f *>(geo.seg)[i];
             winv[i] = geo.seg_inv[i];
@@ -1086,8 +1166,10 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
         if (traced && writer()) write_margins(a.trace, K, sg, ks, st);
     };
 
-    generate(0, 0, lds);
-    __syncthreads();
+    if constexpr (!SERIAL) {
+        generate(0, 0, lds);
+        __syncthreads();
+    }
     int buf = 0;
     for (int k = 0; k < T; ++k) {
         for (int j = 0; j < nph; ++j) {
@@ -1096,6 +1178,11 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
             float m0 = 0.0f, m1 = 0.0f;
             const float vk = v, wk = w_;
             const float2 uk = u;
+            if constexpr (SERIAL) {
+                generate(k, j, lds);
+                __syncthreads();
+                refresh_lane();
+            }
             if constexpr (kPoints && SWEEP) points_load(j + 2 < nph ? j + 2 : j + 2 - nph);
             if (last) {   // step k's means are complete: the next query
                 const float *r = mp + (k & PM) * 2 * kClasses * B;
@@ -1110,8 +1197,9 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
             buf ^= 1;
             // half of the waves contract first, so both pipes of a SIMD have work
             const bool gen_first = w < NW / 2;
+            if constexpr (SERIAL) contract(k, j, lds);
 #pragma unroll 1
-            for (int pass = 0; pass < 2; ++pass) {
+            for (int pass = 0; pass < (SERIAL ? 0 : 2); ++pass) {
                 refresh_lane();
                 if ((pass == 0) == gen_first) {
                     if (!(last && k + 1 == T)) generate(last ? k + 1 : k, last ? 0 : j + 1, kn);
@@ -1132,13 +1220,13 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
                         add_gp_variance(ps[15 * B], dy.dt, sb);
                     }
                     if (cost) {
-                        if (!SWEEP && k >= 2) settle(k - 2);
+                        if (WHOLE && k >= 2) settle(k - 2);
                         stage(k - 1, vk, sa, sb);
                         if (traced && writer()) write_variances(a.trace, K, sg, k - 1, sa, sb);
                     }
                 }
             }
-            if (last && SWEEP && cost && k >= 1) settle(k - 1);
+            if (last && !WHOLE && cost && k >= 1) settle(k - 1);
             if (last && pose) {
                 const float *g0 = gx + (k & PM) * 6 * B + sl;
                 float *ps = pstate + sl;
@@ -1190,7 +1278,7 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
         float sa, sb;
         variances(T - 1, sa, sb);
         if (traced && writer()) write_variances(a.trace, K, sg, T - 1, sa, sb);
-        if (!SWEEP && T >= 2) settle(T - 2);
+        if (WHOLE && T >= 2) settle(T - 2);
         stage(T - 1, v, sa, sb);
     }
     __syncthreads();

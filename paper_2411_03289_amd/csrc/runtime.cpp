@@ -119,7 +119,7 @@ namespace gpmppi {
 gpmppi_status set_error(gpmppi_status st, const char *msg) { return fail(st, "%s", msg); }
 }  // namespace gpmppi
 
-constexpr int kSweepLayout = 2;   // CoreShape::layout of blocks in the sweep layout
+constexpr int kSweepLayout = 2;   // CoreShape::layout from which on a batch's blocks have its GS groups
 constexpr int kGradMaxMpad = 512;   // the gradient's LDS plan holds k for 64 (step, sample) entries
 
 // Scratch memory of the allocation-free entry point (gpmppi_grad_noalloc): one
@@ -832,12 +832,21 @@ gpmppi_status batch_enqueue_step(gpmppi_batch *b, hipStream_t st) {
     return GPMPPI_OK;
 }
 
+// Whether blocks of more than kResidentTiles row tiles hold 64 samples: where the shape allows
+// them and blocks of 32 would outnumber the compute units (a block's steps are a serial chain,
+// so fewer and longer blocks only pay where every compute unit has one).
+bool batch_big(const gpmppi_batch *b, int groups) {
+    long long blocks = 0;
+    for (const gpmppi_ctx *c : b->ctx) blocks += (c->params.K + 31) / 32;
+    return groups == b->G_max && blocks > b->cus;
+}
+
 // Most persistent workgroups one compute unit holds at the LDS plan of the batch's largest
 // block (at most 2).
 int batch_lds(const gpmppi_batch *b, int groups) {
     int lds = 0;
     for (const gpmppi_ctx *c : b->ctx)
-        lds = std::max(lds, core_lds(b->precision, c->Mpad, batch_shape(c->Mpad, groups == b->G_max)));
+        lds = std::max(lds, core_lds(b->precision, c->Mpad, batch_shape(b->precision, c->Mpad, batch_big(b, groups))));
     return lds;
 }
 int wg_capacity(const gpmppi_batch *b, int groups) {
@@ -876,11 +885,12 @@ gpmppi_status check_tuning(const gpmppi_tuning *t, int G_max, int wg_max, bool b
 gpmppi_status batch_install(gpmppi_batch *b, const gpmppi_tuning &t) {
     std::vector<std::pair<double, int2>> it;
     int GS = 0;
+    const bool big = batch_big(b, t.groups);
     for (int p = 0; p < b->n; ++p) {
         const int K = b->ctx[p]->params.K;
         const CoreShape s = b->precision == GPMPPI_BF16 ? CoreShape{2 * t.groups, 0}
-                                                        : batch_shape(b->ctx[p]->Mpad, t.groups == b->G_max);
-        if (s.layout == kSweepLayout) GS = s.G;
+                                                        : batch_shape(b->precision, b->ctx[p]->Mpad, big);
+        if (s.layout >= kSweepLayout) GS = s.G;
         const int B = 16 * s.G;
         for (int blk = 0; blk < (K + B - 1) / B; ++blk) it.push_back({b->cost[p] * s.G, make_int2(p, blk)});
     }
