@@ -40,12 +40,16 @@ struct GpDev {
 //  wrs    [2][Mpad] what undoes a row's scale and the k operand's on the product
 //  alphas [2][Mpad] alpha sf^2 / 2^15, for kernel values scaled by 2^15 / sf^2
 //  zop16  zop as 16x16x32 products
-struct GpCore : GpDev {
+struct GpTerms {
     const uint4 *wfh;
     const uint4 *wfl;
     const float *wrs;
     const float *alphas;
     const uint4 *zop16;
+};
+struct GpCore {
+    const GpDev &d;
+    const GpTerms &t;
 };
 
 struct Geometry {
@@ -71,7 +75,7 @@ struct Dyn {
 };
 
 struct RolloutArgs {
-    GpCore gp;
+    GpDev gp;
     Geometry geo;
     CostWeights cw;
     Dyn dyn;
@@ -81,7 +85,6 @@ struct RolloutArgs {
     int K, T;
     int rotate;                     // start each block's walk over W at a block-dependent unit (FP32 and BF16x3
                                     // forms: output-split launches)
-    int world_lds;                  // 16-sample blocks: the track and obstacles fit LDS beside the plan
     const float *x0;                // [5]
     const float *U;                 // [T][2]
     float *costs;                   // [K]
@@ -96,6 +99,9 @@ struct RolloutArgs {
     uint32_t *flags;                // context status word: GPMPPI_FLAG_EXCHANGE_TIMEOUT is set here
     uint32_t *repair;               // [nblk] split launches: blocks whose exchange gave up, recomputed and
                                     // cleared by the repair launch that follows (all 0 between launches)
+    // rollout_core.hpp only: last, as the BF16 form's kernels are up to 5 % slower with other offsets above
+    GpTerms terms;
+    int world_lds;                  // 16-sample blocks: the track and obstacles fit LDS beside the plan
 };
 
 struct UpdateArgs {

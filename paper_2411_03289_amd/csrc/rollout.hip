@@ -62,7 +62,7 @@ __device__ __forceinline__ void rollout_block_split(const RolloutArgs &a, int bl
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int sl = lane % B, sg = blk * B + sl;
     const int K = a.K, NT = a.gp.NT;
-    const GpCore &gp = a.gp;
+    const GpCore gp{a.gp, a.terms};
     const bool writer = role == 0 && sg < K && w == 0 && lane < B;
     const SplitPlan pl = split_plan<PREC, NW>(NT);
     float *rs = reinterpret_cast<float *>(lds + pl.rs) - role * NT * 32;   // rows of this role's output
@@ -107,7 +107,7 @@ __device__ __forceinline__ void rollout_block_split(const RolloutArgs &a, int bl
         a.trace.sxy_d[2 * K + sg] = 0.0f;
     }
     if constexpr (PREC == GPMPPI_FP32)
-        for (int i = tid; i < NT * 32; i += 64 * NW) rs[role * NT * 32 + i] = gp.wrs[role * NT * 32 + i];
+        for (int i = tid; i < NT * 32; i += 64 * NW) rs[role * NT * 32 + i] = gp.t.wrs[role * NT * 32 + i];
     const WTerms<PREC> wt = wterms<PREC>(gp, lane);
     const UnitList ul = unit_list<NW>(w, NT, 1, role, a.rotate ? blk : 0);
     // this role's output at query q: mean (complete after the barrier), then the variance

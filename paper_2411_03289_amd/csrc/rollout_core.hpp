@@ -137,11 +137,11 @@ struct WTerms {
 
 template <int PREC>
 __device__ __forceinline__ WTerms<PREC> wterms(const GpCore &g, int lane) {
-    const long long bytes = g.wb_stride * 32;
+    const long long bytes = g.d.wb_stride * 32;
     WTerms<PREC> t;
-    t.h = uniform_rsrc(PREC == GPMPPI_FP32 ? g.wfh : g.wbh, bytes);
-    t.l = uniform_rsrc(PREC == GPMPPI_FP32 ? g.wfl : g.wbl, bytes);
-    t.out = __builtin_amdgcn_readfirstlane((int)(g.wb_stride * 16));
+    t.h = uniform_rsrc(PREC == GPMPPI_FP32 ? g.t.wfh : g.d.wbh, bytes);
+    t.l = uniform_rsrc(PREC == GPMPPI_FP32 ? g.t.wfl : g.d.wbl, bytes);
+    t.out = __builtin_amdgcn_readfirstlane((int)(g.d.wb_stride * 16));
     t.voff = wfrag_voff(lane);
     return t;
 }
@@ -218,9 +218,9 @@ __device__ __forceinline__ float class_sum(const float s[kClasses]) {
 // Predictive variance of output o from the sum of squares (FP32 form: of W k / sf).
 template <int PREC>
 __device__ __forceinline__ float gp_variance(const GpCore &g, int o, float sq) {
-    const float sf2 = g.sf2[o];
+    const float sf2 = g.d.sf2[o];
     const float lat = PREC == GPMPPI_FP32 ? fmaf(-sf2, sq, sf2) : sf2 - sq;
-    return g.vscale[o] * (g.sn2[o] + fmaxf(0.0f, lat));
+    return g.d.vscale[o] * (g.d.sn2[o] + fmaxf(0.0f, lat));
 }
 
 // ---------------------------------------------------------------- kernel vectors
@@ -290,14 +290,14 @@ __device__ __forceinline__ void gen_load_points(GenIn<GPMPPI_FP32> &t, const v4f
 
 template <int PREC>
 __device__ __forceinline__ void gen_load(GenIn<PREC> &t, const GpCore &g, int o, int jt, int lane) {
-    const size_t p0 = (size_t)o * g.Mpad + 32 * jt;
+    const size_t p0 = (size_t)o * g.d.Mpad + 32 * jt;
     if constexpr (PREC == GPMPPI_FP32) {
-        gen_load_points(t, reinterpret_cast<const v4f *>(g.zs) + p0, g.alphas + p0, lane);
+        gen_load_points(t, reinterpret_cast<const v4f *>(g.d.zs) + p0, g.t.alphas + p0, lane);
     } else {
-        const uint4 *a = g.zop16 + o * g.zop_stride + (size_t)jt * 128 + lane;
+        const uint4 *a = g.t.zop16 + o * g.d.zop_stride + (size_t)jt * 128 + lane;
         t.a[0] = a[0];
         t.a[1] = a[64];
-        const v4f *al = reinterpret_cast<const v4f *>(g.alpha + p0) + 2 * (lane >> 4);
+        const v4f *al = reinterpret_cast<const v4f *>(g.d.alpha + p0) + 2 * (lane >> 4);
         t.al[0] = al[0];
         t.al[1] = al[1];
     }
@@ -361,7 +361,7 @@ __device__ __forceinline__ void gen_octet(const GenIn<PREC> &t, const GenQ<PREC>
 __device__ __forceinline__ void scaled_query(const GpCore &g, int o, const float q[4], float qs[4]) {
 #pragma clang fp contract(off)
 #pragma unroll
-    for (int d = 0; d < 4; ++d) qs[d] = q[d] * g.scale[o][d];
+    for (int d = 0; d < 4; ++d) qs[d] = q[d] * g.d.scale[o][d];
 }
 
 // The queries of the G groups: group i's from the lanes of its samples (lane l holds sample
@@ -407,11 +407,11 @@ __device__ __forceinline__ void gen_output(const GpCore &g, int o, const float q
         float ms[G];
 #pragma unroll
         for (int i = 0; i < G; ++i) ms[i] = 0.0f;
-        for (int jt = cl; jt < g.NT; jt += kClasses) {
+        for (int jt = cl; jt < g.d.NT; jt += kClasses) {
             if constexpr (kAhead) {
                 in = next;
-                const int jn = jt + kClasses < g.NT ? jt + kClasses : cl + NW;
-                if (jn < g.NT) load(next, jn);
+                const int jn = jt + kClasses < g.d.NT ? jt + kClasses : cl + NW;
+                if (jn < g.d.NT) load(next, jn);
             } else if (jt != wv) {
                 load(in, jt);
             }
@@ -820,7 +820,7 @@ struct Sweep {
             if (t >= NT) break;
             v4f r0{}, r1{};
             if constexpr (PREC == GPMPPI_FP32) {
-                const v4f *rp = reinterpret_cast<const v4f *>(g.wrs + (o * NT + t) * 32) + (lane >> 4);
+                const v4f *rp = reinterpret_cast<const v4f *>(g.t.wrs + (o * NT + t) * 32) + (lane >> 4);
                 r0 = rp[0];
                 r1 = rp[4];
             }
@@ -854,7 +854,7 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
     int tid = threadIdx.x, lane = tid & 63, sl = lane % B, sg = blk * B + sl;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int K = a.K, T = a.T, NT = a.gp.NT;
-    const GpCore &gp = a.gp;
+    const GpCore gp{a.gp, a.terms};
     const Geometry &geo = a.geo;
     const Dyn dy = a.dyn;
     const CorePlan pl = core_plan<PREC, G, LAYOUT>(NT);
@@ -910,8 +910,8 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
     auto points_load = [&](int j) {
         const int o = j >= nch, p = (j - o * nch) * kChunkPts + (tid < kChunkPts ? tid : 4 * (tid - kChunkPts));
         if (tid >= kChunkPts + kChunkPts / 4 || p >= 32 * NT) return;
-        znext = tid < kChunkPts ? reinterpret_cast<const v4f *>(gp.zs)[o * 32 * NT + p]
-                                : *reinterpret_cast<const v4f *>(gp.alphas + o * 32 * NT + p);
+        znext = tid < kChunkPts ? reinterpret_cast<const v4f *>(gp.d.zs)[o * 32 * NT + p]
+                                : *reinterpret_cast<const v4f *>(gp.t.alphas + o * 32 * NT + p);
     };
     auto points_store = [&](int j) {
         if (tid < kChunkPts + kChunkPts / 4) zl[(j & 1) * (kChunkPts + kChunkPts / 4) + tid] = znext;
@@ -919,13 +919,13 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
 
     noise_fill(0);
     if constexpr (kPoints && SERIAL) {
-        for (int i = tid; i < 2 * NT * 32; i += 64 * NW) rs[i] = gp.wrs[i];
+        for (int i = tid; i < 2 * NT * 32; i += 64 * NW) rs[i] = gp.t.wrs[i];
     }
     if constexpr (kPoints && WHOLE) {
         for (int i = tid; i < 2 * NT * 32; i += 64 * NW) {
-            rs[i] = gp.wrs[i];
-            zl[i] = reinterpret_cast<const v4f *>(gp.zs)[i];
-            reinterpret_cast<float *>(zl + 2 * NT * 32)[i] = gp.alphas[i];
+            rs[i] = gp.t.wrs[i];
+            zl[i] = reinterpret_cast<const v4f *>(gp.d.zs)[i];
+            reinterpret_cast<float *>(zl + 2 * NT * 32)[i] = gp.t.alphas[i];
         }
     }
     if constexpr (kPoints && SWEEP) {

@@ -196,7 +196,8 @@ struct gpmppi_ctx {
     float *cost_scratch = nullptr;   // [K]
     float *tight = nullptr;          // [T+1][3] nominal Sigma_XY (Step 2 tightening)
     // host copies
-    GpCore gp{};
+    GpDev gp{};
+    GpTerms terms{};
     Geometry geo{};
     CostWeights cw{};
     Dyn dyn{};
@@ -375,6 +376,7 @@ RolloutArgs rollout_args(const gpmppi_ctx *c, const float *x0, const float *U, u
                          const gpmppi_trace *trace, const uint32_t *step_counter) {
     RolloutArgs a{};
     a.gp = c->gp;
+    a.terms = c->terms;
     a.geo = c->geo;
     a.cw = c->cw;
     a.dyn = c->dyn;
@@ -544,11 +546,11 @@ gpmppi_status gpmppi_init(const gpmppi_params *params, const gpmppi_gp gp[2], co
     c->gp.w32 = c->w32;
     c->gp.wbh = c->wbh;
     c->gp.wbl = c->wbl;
-    c->gp.wfh = c->wfh;
-    c->gp.wfl = c->wfl;
-    c->gp.wrs = c->wrs;
-    c->gp.alphas = c->alphas;
-    c->gp.zop16 = c->zop16;
+    c->terms.wfh = c->wfh;
+    c->terms.wfl = c->wfl;
+    c->terms.wrs = c->wrs;
+    c->terms.alphas = c->alphas;
+    c->terms.zop16 = c->zop16;
     c->gp.w32_stride = c->w32_stride;
     c->gp.wb_stride = c->wb_stride;
     c->gp.zop = c->zop;
