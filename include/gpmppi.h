@@ -273,7 +273,8 @@ typedef struct {
                           * group count only, 64 samples, chosen by K and M; the results do not depend on it */
     int32_t rotate;      /* 1: each workgroup starts its walk over W at a block-dependent row tile; 0: at the
                           * first (FP32 and BF16x3 forms: with split = 1 only, the results do not depend on it) */
-    int32_t wg_per_cu;   /* batches: persistent workgroups per compute unit, 1 or 2 (LDS permitting) */
+    int32_t wg_per_cu;   /* batches: persistent workgroups per compute unit, 1 or 2 (2 where the k operand of one
+                          * output leaves room for two); no more are launched than fit */
     int32_t order;       /* batches: 0 = items longest first, 1 = problem order */
     int32_t waves;       /* wave64s per rollout workgroup: 4 or 8 (FP32 and BF16x3 forms without split: always
                           * eight, whichever is given), or 12 for the wave-specialised

@@ -117,6 +117,8 @@ struct UpdateArgs {
     uint32_t *flags;
 };
 
+// LDS of G sample groups' k operand of one output and the staged inputs
+size_t rollout_lds_bytes(int precision, int G, int Mpad);
 // sample groups of 32 the launch shape of a context may name (1 or 2)
 int rollout_groups(int precision, int Mpad);
 // A rollout workgroup's block: 16 G samples in a layout of rollout_core.hpp (CoreLayout).
@@ -127,7 +129,6 @@ CoreShape core_shape(int precision, int Mpad, int K, int groups, int cus);
 CoreShape batch_shape(int precision, int Mpad, bool big);
 int core_lds(int precision, int Mpad, CoreShape s);   // dynamic LDS of a workgroup
 // The BF16 form's kernels (rollout_bf16.hip): G sample groups of 32 and NW waves per workgroup.
-size_t rollout_bf16_lds(int G, int Mpad);
 hipError_t launch_rollout_bf16(const RolloutArgs &a, int G, int NW, int split, hipStream_t st);
 int rollout_split_capacity_bf16(int Mpad, int NW);
 hipError_t launch_rollout_batch_bf16(const RolloutArgs *probs_d, const int2 *items_d, int n_items, uint32_t *counter,

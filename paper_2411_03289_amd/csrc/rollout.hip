@@ -353,18 +353,19 @@ __global__ __launch_bounds__(kThreads) void gp_predict_kernel(GpDev g, const flo
     }
 }
 
+size_t rollout_lds_bytes(int precision, int G, int Mpad) {
+    switch (precision) {
+        case GPMPPI_FP32: return G == 2 ? dyn_lds_bytes<GPMPPI_FP32, 2>(Mpad) : dyn_lds_bytes<GPMPPI_FP32, 1>(Mpad);
+        case GPMPPI_BF16: return G == 2 ? dyn_lds_bytes<GPMPPI_BF16, 2>(Mpad) : dyn_lds_bytes<GPMPPI_BF16, 1>(Mpad);
+        default: return G == 2 ? dyn_lds_bytes<GPMPPI_BF16X3, 2>(Mpad) : dyn_lds_bytes<GPMPPI_BF16X3, 1>(Mpad);
+    }
+}
+
 // Sample groups of 32 the launch shape allows: two when two groups' k operand of one
 // output (and the staged inputs of the prediction kernel) fit the 160 KB LDS of a CDNA4
 // compute unit, else one.
 static int groups_for(int precision, int Mpad) {
-    const size_t budget = 160 * 1024 - 8 * 1024;
-    size_t need2 = 0;
-    switch (precision) {
-        case GPMPPI_FP32: need2 = dyn_lds_bytes<GPMPPI_FP32, 2>(Mpad); break;
-        case GPMPPI_BF16: need2 = dyn_lds_bytes<GPMPPI_BF16, 2>(Mpad); break;
-        default: need2 = dyn_lds_bytes<GPMPPI_BF16X3, 2>(Mpad); break;
-    }
-    return need2 <= budget ? 2 : 1;
+    return rollout_lds_bytes(precision, 2, Mpad) <= 160 * 1024 - 8 * 1024 ? 2 : 1;
 }
 
 int rollout_groups(int precision, int Mpad) { return groups_for(precision, Mpad); }

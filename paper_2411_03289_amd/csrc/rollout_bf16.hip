@@ -526,10 +526,6 @@ static hipError_t launch_rollout_batch_p(const RolloutArgs *probs, const int2 *i
                   : launch_rollout_batch_t<PREC, 1, kWaves>(probs, items, n_items, counter, Mpad_max, grid, st);
 }
 
-size_t rollout_bf16_lds(int G, int Mpad) {
-    return G == 2 ? dyn_lds_bytes<GPMPPI_BF16, 2>(Mpad) : dyn_lds_bytes<GPMPPI_BF16, 1>(Mpad);
-}
-
 hipError_t launch_rollout_batch_bf16(const RolloutArgs *probs_d, const int2 *items_d, int n_items, uint32_t *counter,
                                      int G, int NW, int Mpad_max, int grid, hipStream_t st) {
     if (G < 1 || G > rollout_groups(GPMPPI_BF16, Mpad_max) || grid < 1 || (NW != kWaves && NW != 8))

@@ -843,18 +843,25 @@ bool batch_big(const gpmppi_batch *b, int groups) {
     return groups == b->G_max && blocks > b->cus;
 }
 
-// Most persistent workgroups one compute unit holds at the LDS plan of the batch's largest
-// block (at most 2).
+// LDS of the batch's largest block at this group count (FP32 and BF16x3 forms).
 int batch_lds(const gpmppi_batch *b, int groups) {
     int lds = 0;
     for (const gpmppi_ctx *c : b->ctx)
         lds = std::max(lds, core_lds(b->precision, c->Mpad, batch_shape(b->precision, c->Mpad, batch_big(b, groups))));
     return lds;
 }
+
+// Most persistent workgroups per compute unit a shape may name: as many as the k operand of one
+// output leaves room for, at most 2.
 int wg_capacity(const gpmppi_batch *b, int groups) {
-    if (b->precision == GPMPPI_BF16)
-        return std::max(1, std::min(2, (int)((160 * 1024) / (rollout_bf16_lds(groups, b->Mpad_max) + 4096))));
-    return std::max(1, std::min(2, (160 * 1024) / (batch_lds(b, groups) + 64)));
+    return std::max(1, std::min(2, (int)((160 * 1024) / (rollout_lds_bytes(b->precision, groups, b->Mpad_max) + 4096))));
+}
+
+// How many of them are launched: no more than fit a compute unit at the blocks' own LDS (a
+// workgroup beyond that would only wait for one to end).
+int wg_launched(const gpmppi_batch *b, int groups, int wg_per_cu) {
+    if (b->precision == GPMPPI_BF16) return wg_per_cu;
+    return std::max(1, std::min(wg_per_cu, (160 * 1024) / (batch_lds(b, groups) + 64)));
 }
 
 // Both workgroups of every sample block fit the device at once (output split, one group).
@@ -911,7 +918,7 @@ gpmppi_status batch_install(gpmppi_batch *b, const gpmppi_tuning &t) {
     b->wg_per_cu = t.wg_per_cu;
     b->order = t.order;
     b->waves = t.waves;
-    b->grid = std::max(1, std::min(b->n_items, b->cus * t.wg_per_cu));
+    b->grid = std::max(1, std::min(b->n_items, b->cus * wg_launched(b, t.groups, t.wg_per_cu)));
     return GPMPPI_OK;
 }
 
@@ -1145,7 +1152,7 @@ gpmppi_status gpmppi_batch_tune(gpmppi_batch *b, const float *x0_d, const float 
     const gpmppi_tuning keep{b->G, b->rotate, b->wg_per_cu, b->order, b->waves, 0, 0.0};
     gpmppi_tuning best{0, 0, 0, 0, 8, 0, -1.0};
     for (int G = 1; G <= b->G_max; ++G) {
-        const int wmax = wg_capacity(b, G);
+        const int wmax = wg_launched(b, G, wg_capacity(b, G));
         // FP32 and BF16x3 forms: one wave count, no rotation
         const bool one = b->precision != GPMPPI_BF16;
         for (int rot = 0; rot <= (one ? 0 : 1); ++rot)
