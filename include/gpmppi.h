@@ -230,7 +230,7 @@ gpmppi_status gpmppi_closed_loop(gpmppi_ctx *ctx, float *x_d, float *U_d, uint64
  * the records of every sample and step) is allocated on first use and kept by the context;
  * where that fails, the samples are taken in chunks that need no more than 8 T K Mpad bytes
  * and checkpoints at every checkpoint_every steps would (GPMPPI_E_NOMEM if that fails
- * too).  Enqueued on stream. */
+ * too), in that call and the later ones.  Enqueued on stream. */
 gpmppi_status gpmppi_grad(gpmppi_ctx *ctx, const float *x0_d, const float *U_d, uint64_t seed, double tau,
                           int32_t checkpoint_every, float *J_d, float *dU_d, float *dlog_ell_d, float *dlog_sf_d,
                           float *costs_d, void *stream);

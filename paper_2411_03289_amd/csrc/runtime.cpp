@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "device_common.hpp"
+#include "grad_workspace.hpp"
 #include "kernels.hpp"
 
 using namespace gpmppi;
@@ -178,9 +179,8 @@ struct gpmppi_ctx {
     long long w32_stride = 0, wb_stride = 0, zop_stride = 0;
     float4 *q32 = nullptr;           // dense packed Q = A^-1 per output (differentiation form, Mpad <= 512)
     long long q_stride = 0;          // float4 per output
-    void *grad_ws = nullptr;         // differentiation-form workspace (grown on demand)
+    GradWorkspace grad_ws;           // differentiation-form workspace (grown on demand)
     int grad_split = 1;              // 1: split the gradient's outputs over two workgroups where they fit
-    size_t grad_ws_bytes = 0;
     void *scratch = nullptr;         // this device's allocation-free scratch array (not owned)
     float4 *obs = nullptr;
     float4 *seg = nullptr;
@@ -205,7 +205,7 @@ struct gpmppi_ctx {
     std::vector<void *> owned;
 
     ~gpmppi_ctx() {
-        if (grad_ws) (void)hipFree(grad_ws);
+        if (grad_ws.p) (void)hipFree(grad_ws.p);
         for (void *p : owned) (void)hipFree(p);
     }
 };
@@ -1313,10 +1313,8 @@ GradLayout grad_layout(const gpmppi_ctx *c, int Kc) {
     g.o_bt = take((size_t)2 * g.nbterm * 4 * 2);
     const size_t nwg = (size_t)((K + 31) / 32);
     g.split = c->grad_split && 2 * (long long)nwg <= grad_split_capacity(Mpad) ? 1 : 0;
-    if (g.split) {
-        g.o_rec = take(nwg * kGradXchPerBlock * 2);   // 64-bit exchange records
-        g.o_rp = take(nwg);
-    }
+    g.o_rec = take(nwg * kGradXchPerBlock * 2);   // 64-bit exchange records; not only where split: the chunks
+    g.o_rp = take(nwg);                           // are the same either way
     return g;
 }
 
@@ -1421,23 +1419,17 @@ gpmppi_status gpmppi_grad(gpmppi_ctx *c, const float *x0_d, const float *U_d, ui
     size_t limit = 0;
     gpmppi_status st = grad_check(c, x0_d, U_d, tau, checkpoint_every, J_d, dU_d, dlog_ell_d, dlog_sf_d, g, limit);
     if (st != GPMPPI_OK) return st;
-    if (g.bytes > c->grad_ws_bytes) {
-        if (c->grad_ws) (void)hipFree(c->grad_ws);
-        c->grad_ws = nullptr;
-        c->grad_ws_bytes = 0;
-        hipError_t e = hipMalloc(&c->grad_ws, g.bytes);
-        if (e != hipSuccess && g.bytes > limit) {   // more chunks
+    const bool have = grad_reserve(
+        c->grad_ws, g, limit, [&](size_t most) { return grad_layout_within(c, most); },
+        [](size_t n) -> void * {
+            void *p = nullptr;
+            if (hipMalloc(&p, n) == hipSuccess) return p;
             (void)hipGetLastError();
-            g = grad_layout_within(c, limit);
-            e = hipMalloc(&c->grad_ws, g.bytes);
-        }
-        if (e != hipSuccess) {
-            c->grad_ws = nullptr;
-            return fail(GPMPPI_E_NOMEM, "hipMalloc of the %zu-byte gradient workspace failed", g.bytes);
-        }
-        c->grad_ws_bytes = g.bytes;
-    }
-    return grad_enqueue(c, g, static_cast<char *>(c->grad_ws), x0_d, U_d, seed, tau, J_d, dU_d, dlog_ell_d,
+            return nullptr;
+        },
+        [](void *p) { (void)hipFree(p); });
+    if (!have) return fail(GPMPPI_E_NOMEM, "hipMalloc of the %zu-byte gradient workspace failed", g.bytes);
+    return grad_enqueue(c, g, static_cast<char *>(c->grad_ws.p), x0_d, U_d, seed, tau, J_d, dU_d, dlog_ell_d,
                         dlog_sf_d, costs_d, (hipStream_t)stream);
 }
 
