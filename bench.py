@@ -370,7 +370,8 @@ def main():
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": traffic, "traffic_unit": "bytes per launch",
                      "hbm_frac": (traffic / (r["rollout_kernel_ms"] * 1e-3) / HBM_PEAK_BPS) if traffic else None,
-                     "kernel": "rollout_pipe_kernel" if r["shape"]["waves"] == 12 else "rollout_kernel",
+                     "kernel": ("rollout_pipe_kernel" if r["shape"]["waves"] == 12 else
+                                "rollout_bf16_kernel" if best == "bf16" else "rollout_kernel"),
                      "flops_per_launch": flops_per_launch},
         "forms": results,
         "speedup_vs_fp32": {n: results["fp32"]["ms_per_step"] / results[n]["ms_per_step"]

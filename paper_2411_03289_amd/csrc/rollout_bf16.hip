@@ -38,10 +38,10 @@ namespace gpmppi {
 
 // The rollout of sample block blk (samples blk * B .. blk * B + B - 1) of one
 // problem; called by all threads of a workgroup.
-template <int PREC, int G, int NW = kWaves, int WALK = kWalkAny>
+template <int G, int NW = kWaves, int WALK = kWalkAny>
 __device__ __forceinline__ void rollout_block(const RolloutArgs &a, int blk, unsigned char *lds, float *pred,
                                               float *ored, float *vred) {
-    using S = Shapes<PREC, G, NW>;
+    using S = Shapes<GPMPPI_BF16, G, NW>;
     const int tid = threadIdx.x;
     const int lane = tid & 63, w = tid >> 6;
     const int sl = lane % S::B;                     // sample within the block
@@ -51,7 +51,7 @@ __device__ __forceinline__ void rollout_block(const RolloutArgs &a, int blk, uns
     const bool writer = valid && w == 0 && lane < S::B;
     const int K = a.K;
     const int Mpad = a.gp.Mpad;
-    const size_t zs_off = G * kgroup_bytes<PREC>(Mpad);
+    const size_t zs_off = G * kgroup_bytes<GPMPPI_BF16>(Mpad);
 
     NoiseParams np = a.noise;
     {
@@ -82,13 +82,7 @@ __device__ __forceinline__ void rollout_block(const RolloutArgs &a, int blk, uns
         a.trace.sxy_d[2 * K + sg] = 0.0f;
     }
 
-    if constexpr (mfma_gen<PREC>()) {   // alpha of both outputs, for the whole horizon
-        stage_alpha<NW>(a.gp, lds, zs_off);
-    } else if constexpr (!scalar_inputs<G>()) {   // inputs of output 0 (the first output of step 0)
-        StagedInputs st;
-        stage_load<PREC, NW>(st, a.gp, 0);
-        stage_store<PREC, NW>(st, a.gp, lds, zs_off);
-    }
+    stage_alpha<NW>(a.gp, lds, zs_off);   // alpha of both outputs, for the whole horizon
     for (int k = 0; k < a.T; ++k) {
         // even steps: outputs 0 then 1; odd steps: 1 then 0 (and blocks reversed)
         const bool rev = (k & 1) != 0;
@@ -126,8 +120,8 @@ __device__ __forceinline__ void rollout_block(const RolloutArgs &a, int blk, uns
             __syncthreads();   // staged inputs visible; previous k-operand readers are done
             const float qs[4] = {q[0] * a.gp.scale[o][0], q[1] * a.gp.scale[o][1], q[2] * a.gp.scale[o][2],
                                  q[3] * a.gp.scale[o][3]};
-            m[o] = gp_gen<PREC, G, NW>(a.gp, o, qs, part, sl, lds, pred);
-            s2[o] = gp_walk<PREC, G, NW, WALK>(a.gp, o, oo == 0 ? 1 - o : -1, rev, a.rotate, blk, lds, vred, sl,
+            m[o] = gp_gen<GPMPPI_BF16, G, NW>(a.gp, o, qs, part, sl, lds, pred);
+            s2[o] = gp_walk<GPMPPI_BF16, G, NW, WALK>(a.gp, o, oo == 0 ? 1 - o : -1, rev, a.rotate, blk, lds, vred, sl,
                                                [&](int wv) {
                                                    world_loop<S::lwaves, S::B>(geo, oo, wv, sl, Xs, Ys, sa, sb, sc,
                                                                                lmax, ored);
@@ -181,11 +175,11 @@ __device__ __forceinline__ uint32_t xch_tag(uint32_t epoch, int k) {
 }
 
 // Role `role` of sample block blk (one sample group, G = 1); see above.
-template <int PREC, int NW, int WALK>
+template <int NW, int WALK>
 __device__ __forceinline__ void rollout_block_split(const RolloutArgs &a, int blk, int role, unsigned char *lds,
                                                     float *pred, float *ored, float *vred, float *xv) {
     constexpr int G = 1;
-    using S = Shapes<PREC, G, NW>;
+    using S = Shapes<GPMPPI_BF16, G, NW>;
     static_assert(S::B == 32, "exchange records hold one 32-sample group");
     const int tid = threadIdx.x;
     const int lane = tid & 63, w = tid >> 6;
@@ -194,7 +188,7 @@ __device__ __forceinline__ void rollout_block_split(const RolloutArgs &a, int bl
     const int sg = blk * S::B + sl;
     const int K = a.K;
     const bool writer = role == 0 && sg < K && w == 0 && lane < S::B;
-    const size_t zs_off = kgroup_bytes<PREC>(a.gp.Mpad);
+    const size_t zs_off = kgroup_bytes<GPMPPI_BF16>(a.gp.Mpad);
 
     NoiseParams np = a.noise;
     {
@@ -232,13 +226,7 @@ __device__ __forceinline__ void rollout_block_split(const RolloutArgs &a, int bl
         a.trace.sxy_d[1 * K + sg] = 0.0f;
         a.trace.sxy_d[2 * K + sg] = 0.0f;
     }
-    if constexpr (mfma_gen<PREC>()) {
-        stage_alpha<NW>(a.gp, lds, zs_off);
-    } else {   // the inputs of this role's output, for the whole horizon
-        StagedInputs st;
-        stage_load<PREC, NW>(st, a.gp, role);
-        stage_store<PREC, NW>(st, a.gp, lds, zs_off);
-    }
+    stage_alpha<NW>(a.gp, lds, zs_off);
 
     StageIn prev{};        // role 0: the previous step's cost inputs, completed by that step's s2 of output 1
     float s20_prev = 0.0f;
@@ -254,9 +242,9 @@ __device__ __forceinline__ void rollout_block_split(const RolloutArgs &a, int bl
             advance_pose(dy, v, w_, sth, cth, X, Y, th);
             const float Xs = X, Ys = Y;
             __syncthreads();   // the previous step's k-operand and loop-result readers are done
-            const float m1 = gp_gen<PREC, G, NW>(a.gp, 1, qs, part, sl, lds, pred);
+            const float m1 = gp_gen<GPMPPI_BF16, G, NW>(a.gp, 1, qs, part, sl, lds, pred);
             if (w == 0) xch_put(slot(k, 1), lane, m1, tag);
-            const float s21 = gp_walk<PREC, G, NW, WALK>(a.gp, 1, -1, rev, a.rotate, blk, lds, vred, sl, [&](int wv) {
+            const float s21 = gp_walk<GPMPPI_BF16, G, NW, WALK>(a.gp, 1, -1, rev, a.rotate, blk, lds, vred, sl, [&](int wv) {
                 world_loop<NW, S::B>(geo, 0, wv, sl, Xs, Ys, 0.0f, 0.0f, 0.0f, 0.0f, ored);
                 if (wv == 0) {
                     const float m0 = xch_get(slot(k, 0), lane, tag, spin, broken);
@@ -285,7 +273,7 @@ __device__ __forceinline__ void rollout_block_split(const RolloutArgs &a, int bl
         const StepJac jac = step_jacobian(dy, v, sth, cth);
         advance_pose(dy, v, w_, sth, cth, X, Y, th);
         __syncthreads();
-        const float m0 = gp_gen<PREC, G, NW>(a.gp, 0, qs, part, sl, lds, pred);
+        const float m0 = gp_gen<GPMPPI_BF16, G, NW>(a.gp, 0, qs, part, sl, lds, pred);
         if (w == 0) xch_put(slot(k, 0), lane, m0, tag);
 
         // ---- chance-constraint geometry at (x_{k+1}, Sigma_{k+1}) (Eqs. 13-16): the position
@@ -301,7 +289,7 @@ __device__ __forceinline__ void rollout_block_split(const RolloutArgs &a, int bl
         const float hh = 0.5f * (sa - sc);
         const float lmax = 0.5f * (sa + sc) + sqrtf(hh * hh + sb * sb);
         const float Xs = X, Ys = Y;
-        const float s20 = gp_walk<PREC, G, NW, WALK>(a.gp, 0, -1, rev, a.rotate, blk, lds, vred, sl, [&](int wv) {
+        const float s20 = gp_walk<GPMPPI_BF16, G, NW, WALK>(a.gp, 0, -1, rev, a.rotate, blk, lds, vred, sl, [&](int wv) {
             world_loop<NW, S::B>(geo, 1, wv, sl, Xs, Ys, sa, sb, sc, lmax, ored);
             if (wv == 0) {
                 const float m1 = xch_get(slot(k, 1), lane, tag, spin, broken);
@@ -367,29 +355,29 @@ __device__ __forceinline__ void rollout_block_split(const RolloutArgs &a, int bl
     }
 }
 
-template <int PREC, int NW, int WALK>
-__global__ __launch_bounds__(64 * NW) void rollout_split_kernel(RolloutArgs a) {
-    using S = Shapes<PREC, 1, NW>;
+template <int NW, int WALK>
+__global__ __launch_bounds__(64 * NW) void rollout_bf16_split_kernel(RolloutArgs a) {
+    using S = Shapes<GPMPPI_BF16, 1, NW>;
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ float pred[S::rparts * S::B];
     __shared__ float ored[2 * NW * S::B];   // both loops on every wave (rollout_block_split)
     __shared__ float vred[NW * S::B];
     __shared__ float xv[kXvFail + 1];
     const int role = __builtin_amdgcn_readfirstlane((int)(blockIdx.x & 1));
-    rollout_block_split<PREC, NW, WALK>(a, blockIdx.x >> 1, role, lds, pred, ored, vred, xv);
+    rollout_block_split<NW, WALK>(a, blockIdx.x >> 1, role, lds, pred, ored, vred, xv);
 }
 
 // a.repair == NULL: every block.  Otherwise the repair launch after an output
 // split (G = 1): only the blocks the split launch marked, whose marks it clears.
-template <int PREC, int G, int NW, int WALK>
-__global__ __launch_bounds__(64 * NW) void rollout_kernel(RolloutArgs a) {
-    using S = Shapes<PREC, G, NW>;
+template <int G, int NW, int WALK>
+__global__ __launch_bounds__(64 * NW) void rollout_bf16_kernel(RolloutArgs a) {
+    using S = Shapes<GPMPPI_BF16, G, NW>;
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ float pred[S::rparts * S::B];
     __shared__ float ored[2 * S::lwaves * S::B];
     __shared__ float vred[NW * S::B];
     if (a.repair && __hip_atomic_load(a.repair + blockIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return;
-    rollout_block<PREC, G, NW, WALK>(a, blockIdx.x, lds, pred, ored, vred);
+    rollout_block<G, NW, WALK>(a, blockIdx.x, lds, pred, ored, vred);
     if (a.repair && threadIdx.x == 0)
         __hip_atomic_store(a.repair + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -404,10 +392,10 @@ typedef const RolloutArgs __attribute__((address_space(4))) ConstRolloutArgs;
 // (problem, sample block) items from a shared counter until the list (sorted
 // longest first) is exhausted.  Results do not depend on which workgroup
 // runs an item.  *counter must be 0 at launch.
-template <int PREC, int G, int NW>
-__global__ __launch_bounds__(64 * NW) void rollout_batch_kernel(ConstRolloutArgs *probs, const int2 *items,
+template <int G, int NW>
+__global__ __launch_bounds__(64 * NW) void rollout_bf16_batch_kernel(ConstRolloutArgs *probs, const int2 *items,
                                                                  int n_items, uint32_t *counter) {
-    using S = Shapes<PREC, G, NW>;
+    using S = Shapes<GPMPPI_BF16, G, NW>;
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ float pred[S::rparts * S::B];
     __shared__ float ored[2 * S::lwaves * S::B];
@@ -422,7 +410,7 @@ __global__ __launch_bounds__(64 * NW) void rollout_batch_kernel(ConstRolloutArgs
         const int2 pb = items[it];
         const int p = __builtin_amdgcn_readfirstlane(pb.x);
         const int b = __builtin_amdgcn_readfirstlane(pb.y);
-        rollout_block<PREC, G, NW>(*(const RolloutArgs *)&probs[p], b, lds, pred, ored, vred);
+        rollout_block<G, NW>(*(const RolloutArgs *)&probs[p], b, lds, pred, ored, vred);
     }
 }
 
@@ -433,20 +421,20 @@ static hipError_t set_lds(F *fn, size_t bytes) {
 }
 
 // One problem: the kernel carries only the walk over W that its size takes.
-template <int PREC, int G, int NW, int WALK>
+template <int G, int NW, int WALK>
 static hipError_t launch_rollout_w(const RolloutArgs &a, hipStream_t st) {
-    const size_t lds = dyn_lds_bytes<PREC, G>(a.gp.Mpad);
-    hipError_t e = set_lds(rollout_kernel<PREC, G, NW, WALK>, lds);
+    const size_t lds = dyn_lds_bytes<GPMPPI_BF16, G>(a.gp.Mpad);
+    hipError_t e = set_lds(rollout_bf16_kernel<G, NW, WALK>, lds);
     if (e != hipSuccess) return e;
     const dim3 grid((a.K + 32 * G - 1) / (32 * G));
-    hipLaunchKernelGGL((rollout_kernel<PREC, G, NW, WALK>), grid, dim3(64 * NW), lds, st, a);
+    hipLaunchKernelGGL((rollout_bf16_kernel<G, NW, WALK>), grid, dim3(64 * NW), lds, st, a);
     return hipGetLastError();
 }
 
-template <int PREC, int G, int NW>
+template <int G, int NW>
 static hipError_t launch_rollout_t(const RolloutArgs &a, hipStream_t st) {
-    return walk_by_rows(a.gp.NT, NW) ? launch_rollout_w<PREC, G, NW, kWalkRows>(a, st)
-                                     : launch_rollout_w<PREC, G, NW, kWalkPairs>(a, st);
+    return walk_by_rows(a.gp.NT, NW) ? launch_rollout_w<G, NW, kWalkRows>(a, st)
+                                     : launch_rollout_w<G, NW, kWalkPairs>(a, st);
 }
 
 // Workgroups of fn (64 NW threads, lds bytes of dynamic LDS) resident at once on the device.
@@ -461,86 +449,84 @@ static hipError_t resident_blocks(F *fn, int NW, size_t lds, int &n) {
     return e;
 }
 
-template <int PREC, int NW, int WALK>
+template <int NW, int WALK>
 static hipError_t split_capacity_w(int Mpad, int &n) {
-    const size_t lds = dyn_lds_bytes<PREC, 1>(Mpad);
-    hipError_t e = set_lds(rollout_split_kernel<PREC, NW, WALK>, lds);
+    const size_t lds = dyn_lds_bytes<GPMPPI_BF16, 1>(Mpad);
+    hipError_t e = set_lds(rollout_bf16_split_kernel<NW, WALK>, lds);
     if (e != hipSuccess) return e;
-    return resident_blocks(rollout_split_kernel<PREC, NW, WALK>, NW, lds, n);
+    return resident_blocks(rollout_bf16_split_kernel<NW, WALK>, NW, lds, n);
 }
 
-template <int PREC, int NW>
+template <int NW>
 static int split_capacity_t(int Mpad) {
     int n = 0;
-    const hipError_t e = walk_by_rows(Mpad / 32, NW) ? split_capacity_w<PREC, NW, kWalkRows>(Mpad, n)
-                                                    : split_capacity_w<PREC, NW, kWalkPairs>(Mpad, n);
+    const hipError_t e = walk_by_rows(Mpad / 32, NW) ? split_capacity_w<NW, kWalkRows>(Mpad, n)
+                                                    : split_capacity_w<NW, kWalkPairs>(Mpad, n);
     return e == hipSuccess ? 32 * (n / 2) : 0;
 }
 
-template <int PREC, int NW, int WALK>
+template <int NW, int WALK>
 static hipError_t launch_rollout_split_w(const RolloutArgs &a, hipStream_t st) {
     if (!a.xrec || !a.xep || !a.repair) return hipErrorInvalidValue;
-    const size_t lds = dyn_lds_bytes<PREC, 1>(a.gp.Mpad);
+    const size_t lds = dyn_lds_bytes<GPMPPI_BF16, 1>(a.gp.Mpad);
     int cap = 0;
-    hipError_t e = split_capacity_w<PREC, NW, WALK>(a.gp.Mpad, cap);
+    hipError_t e = split_capacity_w<NW, WALK>(a.gp.Mpad, cap);
     if (e != hipSuccess) return e;
     const int nblk = (a.K + 31) / 32;
     if (2 * nblk > cap) return hipErrorCooperativeLaunchTooLarge;   // both roles of every block resident together
-    hipLaunchKernelGGL((rollout_split_kernel<PREC, NW, WALK>), dim3(2 * nblk), dim3(64 * NW), lds, st, a);
+    hipLaunchKernelGGL((rollout_bf16_split_kernel<NW, WALK>), dim3(2 * nblk), dim3(64 * NW), lds, st, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // the repair launch: the unsplit kernel recomputes the blocks whose exchange gave up
-    return launch_rollout_w<PREC, 1, NW, WALK>(a, st);
+    return launch_rollout_w<1, NW, WALK>(a, st);
 }
 
-template <int PREC, int NW>
+template <int NW>
 static hipError_t launch_rollout_split_t(const RolloutArgs &a, hipStream_t st) {
-    return walk_by_rows(a.gp.NT, NW) ? launch_rollout_split_w<PREC, NW, kWalkRows>(a, st)
-                                     : launch_rollout_split_w<PREC, NW, kWalkPairs>(a, st);
+    return walk_by_rows(a.gp.NT, NW) ? launch_rollout_split_w<NW, kWalkRows>(a, st)
+                                     : launch_rollout_split_w<NW, kWalkPairs>(a, st);
 }
 
-template <int PREC>
 static hipError_t launch_rollout_p(const RolloutArgs &a, int G, int NW, int split, hipStream_t st) {
-    if (split) return NW == 8 ? launch_rollout_split_t<PREC, 8>(a, st) : launch_rollout_split_t<PREC, kWaves>(a, st);
-    if (NW == 8) return G == 2 ? launch_rollout_t<PREC, 2, 8>(a, st) : launch_rollout_t<PREC, 1, 8>(a, st);
-    return G == 2 ? launch_rollout_t<PREC, 2, kWaves>(a, st) : launch_rollout_t<PREC, 1, kWaves>(a, st);
+    if (split) return NW == 8 ? launch_rollout_split_t<8>(a, st) : launch_rollout_split_t<kWaves>(a, st);
+    if (NW == 8) return G == 2 ? launch_rollout_t<2, 8>(a, st) : launch_rollout_t<1, 8>(a, st);
+    return G == 2 ? launch_rollout_t<2, kWaves>(a, st) : launch_rollout_t<1, kWaves>(a, st);
 }
 
-template <int PREC, int G, int NW>
+template <int G, int NW>
 static hipError_t launch_rollout_batch_t(const RolloutArgs *probs, const int2 *items, int n_items, uint32_t *counter,
                                          int Mpad_max, int grid, hipStream_t st) {
-    const size_t lds = dyn_lds_bytes<PREC, G>(Mpad_max);
-    hipError_t e = set_lds(rollout_batch_kernel<PREC, G, NW>, lds);
+    const size_t lds = dyn_lds_bytes<GPMPPI_BF16, G>(Mpad_max);
+    hipError_t e = set_lds(rollout_bf16_batch_kernel<G, NW>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((rollout_batch_kernel<PREC, G, NW>), dim3(grid), dim3(64 * NW), lds, st,
+    hipLaunchKernelGGL((rollout_bf16_batch_kernel<G, NW>), dim3(grid), dim3(64 * NW), lds, st,
                        (ConstRolloutArgs *)probs, items, n_items, counter);
     return hipGetLastError();
 }
 
-template <int PREC>
 static hipError_t launch_rollout_batch_p(const RolloutArgs *probs, const int2 *items, int n_items, uint32_t *counter,
                                          int G, int NW, int Mpad_max, int grid, hipStream_t st) {
     if (NW == 8)
-        return G == 2 ? launch_rollout_batch_t<PREC, 2, 8>(probs, items, n_items, counter, Mpad_max, grid, st)
-                      : launch_rollout_batch_t<PREC, 1, 8>(probs, items, n_items, counter, Mpad_max, grid, st);
-    return G == 2 ? launch_rollout_batch_t<PREC, 2, kWaves>(probs, items, n_items, counter, Mpad_max, grid, st)
-                  : launch_rollout_batch_t<PREC, 1, kWaves>(probs, items, n_items, counter, Mpad_max, grid, st);
+        return G == 2 ? launch_rollout_batch_t<2, 8>(probs, items, n_items, counter, Mpad_max, grid, st)
+                      : launch_rollout_batch_t<1, 8>(probs, items, n_items, counter, Mpad_max, grid, st);
+    return G == 2 ? launch_rollout_batch_t<2, kWaves>(probs, items, n_items, counter, Mpad_max, grid, st)
+                  : launch_rollout_batch_t<1, kWaves>(probs, items, n_items, counter, Mpad_max, grid, st);
 }
 
 hipError_t launch_rollout_batch_bf16(const RolloutArgs *probs_d, const int2 *items_d, int n_items, uint32_t *counter,
                                      int G, int NW, int Mpad_max, int grid, hipStream_t st) {
     if (G < 1 || G > rollout_groups(GPMPPI_BF16, Mpad_max) || grid < 1 || (NW != kWaves && NW != 8))
         return hipErrorInvalidValue;
-    return launch_rollout_batch_p<GPMPPI_BF16>(probs_d, items_d, n_items, counter, G, NW, Mpad_max, grid, st);
+    return launch_rollout_batch_p(probs_d, items_d, n_items, counter, G, NW, Mpad_max, grid, st);
 }
 
 hipError_t launch_rollout_bf16(const RolloutArgs &args, int G, int NW, int split, hipStream_t st) {
     RolloutArgs a = args;
     if (!split) a.repair = nullptr;   // an unsplit launch computes every block
-    return launch_rollout_p<GPMPPI_BF16>(a, G, NW, split, st);
+    return launch_rollout_p(a, G, NW, split, st);
 }
 
 int rollout_split_capacity_bf16(int Mpad, int NW) {
-    return NW == 8 ? split_capacity_t<GPMPPI_BF16, 8>(Mpad) : split_capacity_t<GPMPPI_BF16, kWaves>(Mpad);
+    return NW == 8 ? split_capacity_t<8>(Mpad) : split_capacity_t<kWaves>(Mpad);
 }
 
 }  // namespace gpmppi
