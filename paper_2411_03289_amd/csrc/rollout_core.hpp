@@ -147,9 +147,11 @@ __device__ __forceinline__ WTerms<PREC> wterms(const GpCore &g, int lane) {
 }
 
 // Block blk of output o; the block index is wave-uniform.
+// have: whether there is one; otherwise the address is that behind the last block, where the resource's
+// bounds check returns zeros without a memory access.
 template <int PREC>
-__device__ __forceinline__ void wfrag_load(WFrag<PREC> &f, const WTerms<PREC> &t, int o, int blk) {
-    const int at = __builtin_amdgcn_readfirstlane((o ? t.out : 0) + blk * 2048);
+__device__ __forceinline__ void wfrag_load(WFrag<PREC> &f, const WTerms<PREC> &t, int o, int blk, bool have = true) {
+    const int at = __builtin_amdgcn_readfirstlane(have ? (o ? t.out : 0) + blk * 2048 : 2 * t.out);
     f.h[0] = buf_load16(t.h, t.voff, at);
     f.h[1] = buf_load16(t.h, t.voff + 256, at);
     f.l[0] = buf_load16(t.l, t.voff, at);
@@ -723,11 +725,10 @@ struct Sweep {
 
     __device__ __forceinline__ int row(int i) const { return (i & 1) ? 8 * i + 7 - wc : 8 * i + wc; }
 
-    static constexpr int kNoBlock = 1 << 18;   // 512 MB, beyond any W
     // The block of row i in column c of output o into ring slot q.
     __device__ __forceinline__ void fetch(int q, int i, int o, int c, bool have, const WTerms<PREC> &wt) {
         const int t = row(i), u = t >> 1;
-        wfrag_load<PREC>(ring[q], wt, o, have && c <= t ? 2 * u * (u + 1) + (t & 1) + 2 * c : kNoBlock);
+        wfrag_load<PREC>(ring[q], wt, o, 2 * u * (u + 1) + (t & 1) + 2 * c, have && c <= t);
     }
     // The first four blocks of chunk ci.
     __device__ __forceinline__ void prefetch(int o, int ci, const WTerms<PREC> &wt) {
