@@ -202,8 +202,9 @@ hipError_t combine_alpha(const double *alpha_terr, int n_terr, int Mpad, Terrain
                          float *alpha32, float *alphas, hipStream_t st);
 hipError_t launch_terrain_means(const float *q, int n, const GpDev &g, const double *alpha_terr, int n_terr,
                                 float *out, hipStream_t st);
-// Differentiation form (see grad.hip).  Samples are taken in chunks of Kc; entry (k, s) of a
-// chunk has index n = k Kc + (s - s0), and the chunk arrays below hold N = T Kc of them.
+// Differentiation form (see grad.hip).  Samples are taken in chunks of Kc; the last may have fewer,
+// kc.  Entry (k, s) of a chunk has index n = k kc + (s - s0); the chunk arrays below have room for
+// N = T Kc of them, and their strides are N.  stage alone goes by Kc.
 struct GradArgs {
     GpDev gp;
     Geometry geo;

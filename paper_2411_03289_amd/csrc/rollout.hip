@@ -376,7 +376,9 @@ static hipError_t set_lds(F *fn, size_t bytes) {
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-// The block of more row tiles than the whole layouts hold.
+// The block of more row tiles than the whole layouts hold.  64 samples, 8193 of them, T = 10, serial
+// against sweep where the serial layout's k fits LDS: FP32 M = 300 189 us against 264, 448 263 against
+// 317; BF16x3 300 182 against 239, 512 278 against 313.
 template <int PREC>
 static CoreShape long_shape(int NT, bool big) {
     if (!big) return CoreShape{2, kSerial};
@@ -386,7 +388,14 @@ static CoreShape long_shape(int NT, bool big) {
 // The block of one problem: the smallest that still gives every compute unit at most one
 // workgroup, as the horizon is a serial chain and a block's step gets longer with its
 // samples; 64 samples where the blocks outnumber the compute units anyway.  big: 64-sample
-// blocks are allowed.
+// blocks are allowed.  A rollout on 256 compute units, FP32 (BF16x3 within 13 % and on the same
+// side unless said):
+//   16 samples against 32, T = 20: resident M = 64 K = 4096 67 us, 94; K = 4097 123, 94;
+//     M = 256 106, 149 and 198, 150; streamed against serial M = 300 167, 256 and 309, 255;
+//     M = 448 248, 343 and 448, 343 (BF16x3 M = 576 345, 413 and 640, 414)
+//   32 samples against 64, T = 10: M = 448 K = 8192 191, 263; K = 8193 352, 263; M = 700 331, 548
+//     and 556, 543; M = 1024 603, 932 and 1059, 931; K = 16384 1141, 1023.  M = 700 is level up to
+//     K = 16384 (613, 614; BF16x3 560, 580).
 template <int PREC>
 static CoreShape core_shape_t(int NT, int K, bool big, int cus) {
     const int whole = NT <= kResidentTiles ? kWholeResident : kWholeStream;

@@ -12,8 +12,8 @@
 // and two of them, instead of the loops, integrate pose and covariance and add up the
 // cost.  The next query needs only the GP means, which are complete before the
 // last chunk's contraction starts, so generation (VALU) and contraction (matrix
-// cores) of neighbouring chunks run side by side; half of the waves take them in
-// the opposite order.  Everything that does not feed the next query is delayed:
+// cores) of neighbouring chunks run side by side, half of the waves in the opposite
+// order (not in the serial layout).  Everything that does not feed the next query is delayed:
 // step k's variances enter the covariance in step k + 1, its constraint loops run
 // in step k + 1 and its cost is added in step k + 2.
 //
@@ -25,8 +25,8 @@
 //          five blocks do and the rest come through a four-deep ring
 //   serial two phases per step, one per output: all of its k into LDS, a barrier, its row
 //          tiles dealt to the waves, W through the four-deep ring.  Nothing of the vector
-//          work is hidden, but W streams without a pause: 41K of the 34K cycles a wave's share
-//          of 1024 points takes at the 64 bytes a clock of a compute unit's L1.  32 samples up
+//          work is hidden, but W streams without a pause: 41K cycles for one output of 1024 points,
+//          where 64 bytes a clock, a compute unit's L1, would take 34K.  32 samples up
 //          to 1024 points, 64 where their k fits LDS (448 points, BF16x3 form 512).  Odd steps
 //          take the outputs in the opposite order: one output's W stays in the XCD's 4 MB of
 //          L2 from step to step, both (4.3 MB at 1024 points) would not
@@ -52,10 +52,13 @@
 //           products.  k is scaled to (0, 2^15] (k / sf^2 2^15) and every row of W by a
 //           power of two into FP16's normal range, so neither term loses bits to the
 //           exponent range; the row factors are undone on the FP32 sums.  The FP32
-//           matrix cores run at a sixteenth of this rate.  The error against 64 bits is
-//           that of the FP32 sums (three roundings per 32 columns and product term
-//           instead of sixteen): 0.95 x (M = 64) to 0.35 x (M = 1024) of the variance
-//           error of FP32 operands and sums.
+//           matrix cores run at a sixteenth of this rate.  A sum is rounded (towards zero)
+//           once per 32 columns and product instead of once per two columns: over rollouts
+//           the rms error of s2 against 64 bits is 0.91 (M = 16), 0.84 (64), 0.72 (256),
+//           0.70 (512), 0.68 (1024) of that with FP32 products (sn = 0.1 sf; 1.11 at
+//           M = 16 and sn = 0.01 sf).  Truncation leaves s2 too large on average by
+//           7e-8 sf^2 at M = 1024, a sixth of the rms; gp_predict, FP32 products in one chain,
+//           9e-8.
 //   BF16x3  two BF16 terms each, three products
 // (The BF16 form has its own kernels, rollout_bf16.hip and rollout_pipe.hip.)
 //
@@ -63,14 +66,16 @@
 // generation, contraction, constraint loops and state update one after another, with FP32
 // operands in the FP32 form):
 //   K     T    M     form     before    now      bound now
-//   256   20   50    FP32     219 us    63 us    the pose and covariance chain, 3 us a step
-//   2500  40   300   FP32     2086 us   345 us   W streamed per 16 samples, vector work of k
-//   2048  30   256   FP32 (*) 1951 us   311 us   the chain, twice (nominal sequence first)
+//   256   20   50    FP32     219 us    62 us    the pose and covariance chain, 3 us a step
+//   2500  40   300   FP32     2089 us   317 us   W streamed per 16 samples, vector work of k
+//   2048  30   256   FP32 (*) 1954 us   306 us   the chain, twice (nominal sequence first)
 //   4096  50   256   BF16x3   953 us    272 us   vector work of k beside the products, 5 us a step
-//   16384 100  1024  BF16x3   10.2 ms   9.6 ms   W from L2, some 52 bytes a clock per CU
-//   16384 100  1024  FP32     26.6 ms   10.6 ms  the same
-// (*) three terrains, tightening along the nominal sequence.  Over 12 seeds of the last, the
-// error of the weights against 64 bits went from 4.8e-6 to 3.7e-6 (mean), of U from 9.1e-7 to 7.4e-7.
+//   16384 100  1024  BF16x3   9.9 ms    9.5 ms   W from L2, some 52 bytes a clock per CU
+//   16384 100  1024  FP32     26.5 ms   10.4 ms  the same
+// (*) three terrains, tightening along the nominal sequence.  Geometric ratio of the errors
+// against 64 bits of U, costs and weights, FP32: 1.00, 1.00, 1.00 of the first (60 seeds), 0.97,
+// 0.94, 0.89 of the third (60), 0.92, 0.87, 0.73 of the second (12).  Single draws scatter by
+// a factor of two either way.
 #pragma once
 #include "core_step.hpp"
 #include "device_common.hpp"
@@ -730,7 +735,7 @@ struct Sweep {
         const int t = row(i), u = t >> 1;
         wfrag_load<PREC>(ring[q], wt, o, 2 * u * (u + 1) + (t & 1) + 2 * c, have && c <= t);
     }
-    // The first four blocks of chunk ci.
+    // The first RD blocks of chunk ci.
     __device__ __forceinline__ void prefetch(int o, int ci, const WTerms<PREC> &wt) {
 #pragma unroll
         for (int q = 0; q < RD; ++q) fetch(q, nrows - 1, o, kSweepTiles * ci + q, ci < nrows, wt);
@@ -876,7 +881,7 @@ __device__ __forceinline__ void rollout_core(const RolloutArgs &a, int blk, unsi
     float *ored = reinterpret_cast<float *>(lds + pl.ored); // [parity][2 NS][B]
     const int VR = SWEEP ? kClasses : NT;                   // rows of vp per output
     const int ns = pl.ns;
-    // two waves (on different SIMDs) carry what is not shared out: pose and covariance, and the cost
+    // two waves (3 and 7, of one SIMD) carry what is not shared out: pose and covariance, and the cost
     const bool pose = w == NW / 2 - 1, cost = w == NW - 1;
 
     NoiseParams np = a.noise;

@@ -121,7 +121,7 @@ gpmppi_status set_error(gpmppi_status st, const char *msg) { return fail(st, "%s
 }  // namespace gpmppi
 
 constexpr int kSweepLayout = 2;   // CoreShape::layout from which on a batch's blocks have its GS groups
-constexpr int kGradMaxMpad = 512;   // the gradient's LDS plan holds k for 64 (step, sample) entries
+constexpr int kGradMaxMpad = 512;   // the gradient's LDS plan holds k for 32 (step, sample) entries
 
 // Scratch memory of the allocation-free entry point (gpmppi_grad_noalloc): one
 // array per GPU the library runs on, held until the process ends and shared by
@@ -836,7 +836,11 @@ gpmppi_status batch_enqueue_step(gpmppi_batch *b, hipStream_t st) {
 
 // Whether blocks of more than kResidentTiles row tiles hold 64 samples: where the shape allows
 // them and blocks of 32 would outnumber the compute units (a block's steps are a serial chain,
-// so fewer and longer blocks only pay where every compute unit has one).
+// so fewer and longer blocks only pay where every compute unit has one).  n problems of
+// K = 1000, T = 10, M = 1024, FP32, us a step with blocks of 32 and of 64 (n = 8: 256 blocks of
+// 32): n = 4 571, 927; 8 698, 947; 9 1088, 954; 16 1315, 1144; 24 1951, 2054; 32 2549, 2194.
+// M = 400: 4 205, 281; 8 225, 296; 9 391, 300; 16 434, 341; 24 624, 611; 32 817, 646.
+// BF16x3 crosses at the same places.
 bool batch_big(const gpmppi_batch *b, int groups) {
     long long blocks = 0;
     for (const gpmppi_ctx *c : b->ctx) blocks += (c->params.K + 31) / 32;
