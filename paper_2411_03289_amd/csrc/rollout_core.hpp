@@ -70,10 +70,14 @@
 //   2500  40   300   FP32     2089 us   317 us   W streamed per 16 samples, vector work of k
 //   2048  30   256   FP32 (*) 1954 us   306 us   the chain, twice (nominal sequence first)
 //   4096  50   256   BF16x3   953 us    272 us   vector work of k beside the products, 5 us a step
-//   16384 100  1024  BF16x3   9.9 ms    9.5 ms   W from L2, some 52 bytes a clock per CU
-//   16384 100  1024  FP32     26.5 ms   10.4 ms  the same
+//   16384 100  1024  BF16x3   9.9 ms    9.5 ms   issue of the products, vector work of k between them
+//   16384 100  1024  FP32     26.5 ms   10.3 ms  the same
+// Counters, matrix cores and vector unit busy of the cycles of the compute units in use: 2 % and 36 %
+// (first row), 15 and 42 (second), 15 and 56 (fourth), 51 and 38 at 2.2 GHz (fifth), 47 and 38 (sixth);
+// the sweep reads W at 22 bytes a clock, and two waves of a SIMD issue a 16x16x32 product every 22
+// cycles or so, of which it keeps the matrix core for 16.
 // (*) three terrains, tightening along the nominal sequence.  Geometric ratio of the errors
-// against 64 bits of U, costs and weights, FP32: 1.00, 1.00, 1.00 of the first (60 seeds), 0.97,
+// against 64 bits of U, costs and weights, now over before, FP32: 1.00, 1.00, 1.00 of the first (60 seeds), 0.97,
 // 0.94, 0.89 of the third (60), 0.92, 0.87, 0.73 of the second (12).  Single draws scatter by
 // a factor of two either way.
 #pragma once
